@@ -13,8 +13,8 @@
 //     (v_mfma_f64_16x16x4f64, v_mfma_f32_16x16x4f32) writing per-slab
 //     partial sums, followed by k_stage which reduces the slabs in a fixed
 //     order (deterministic, no atomics) and applies the RK4 combination.
-//   * M <= 256 and B*M <= 4096: k_rk4_small -- one workgroup per system runs
-//     all steps with Q and the stage vectors in LDS.
+//   * M <= 256 and B*M <= 4096: rk4_small.h -- one workgroup per state runs
+//     all steps with Q in registers.
 // State layout inside the library: states are padded to Bp in {16, 32, 64}
 // columns and stored "pair-interleaved", X[(k>>1)*2Bp + 2b + (k&1)], so that
 // the 16-byte load a lane issues holds two consecutive k of one state -- the
@@ -23,6 +23,7 @@
 #include <mutex>
 
 #include "lb_internal.h"
+#include "rk4_small.h"
 #include "rowdot.h"
 #include "sell.h"
 
@@ -770,64 +771,6 @@ __global__ void k_gemv_init(double* const* Vs, int64_t M, double* Wall, int64_t 
 }
 
 // ---------------------------------------------------------------------------
-// Small systems: one workgroup integrates one system for all steps.
-// ---------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void k_rk4_small(const double* const* Qs, const double* const* Ks,
-                                                   double* const* Vs, int M, int64_t ldq, int B, double h,
-                                                   int64_t steps, int q_in_lds) {
-    extern __shared__ double sm[];
-    const int r = blockIdx.x;
-    const double* Qg = Qs[r];
-    const double* K = Ks[r];
-    double* V = Vs[r];
-    const int n = M * B;
-    double* X = sm;           // B x M
-    double* Acc = sm + n;     // B x M
-    double* Ql = sm + 2 * n;  // M x M (optional)
-    for (int e = threadIdx.x; e < n; e += blockDim.x) X[e] = V[e];
-    if (q_in_lds)
-        for (int e = threadIdx.x; e < M * M; e += blockDim.x) Ql[e] = Qg[(int64_t)(e / M) * ldq + e % M];
-    __syncthreads();
-    const double* Q = q_in_lds ? Ql : Qg;
-    const int64_t lq = q_in_lds ? M : ldq;
-    for (int64_t st = 0; st < steps; ++st) {
-        for (int stage = 1; stage <= 4; ++stage) {
-            double kv[16];
-            int cnt = 0;
-            for (int e = threadIdx.x; e < n; e += blockDim.x) {
-                const int b = e / M, i = e % M;
-                const double* q = Q + (int64_t)i * lq;
-                const double* x = X + b * M;
-                double s = 0.0;
-                for (int j = 0; j < M; ++j) s = fma(q[j], x[j], s);
-                kv[cnt++] = s + K[i];
-            }
-            __syncthreads();
-            cnt = 0;
-            for (int e = threadIdx.x; e < n; e += blockDim.x) {
-                const double k = kv[cnt++];
-                double x;
-                if (stage == 1) {
-                    Acc[e] = k;
-                    x = V[e] + 0.5 * h * k;
-                } else if (stage == 2) {
-                    Acc[e] = Acc[e] + 2.0 * k;
-                    x = V[e] + 0.5 * h * k;
-                } else if (stage == 3) {
-                    Acc[e] = Acc[e] + 2.0 * k;
-                    x = V[e] + h * k;
-                } else {
-                    x = V[e] + h / 6.0 * (Acc[e] + k);
-                    V[e] = x;
-                }
-                X[e] = x;
-            }
-            __syncthreads();
-        }
-    }
-}
-
-// ---------------------------------------------------------------------------
 // Sparse RK4 stage: one launch per stage with the stage combination fused in,
 // over the slice layout of sell.h (one wavefront per 64-row slice, one block of
 // 256 threads per long row).
@@ -1104,8 +1047,7 @@ struct Plan {
     int nslab;
     int64_t sstride, s32stride, pstride, wstride;
     size_t o_ptr, o_v, o_acc, o_x, o_x32, o_part, o_w, bytes;
-    size_t shm;
-    int q_in_lds;
+    Rk4Small small;
     bool aligned;
     bool staged;  // every Q and every row of Q 128-byte aligned: LDS-staged GEMM, streaming GEMV loads
     const void** d;
@@ -1130,10 +1072,7 @@ static int plan_make(Plan& p, int R, int64_t M, int64_t ldq, int B, int precisio
     p.o_ptr = take(sizeof(void*) * 5 * R);
     if (allow_small && M <= 256 && (int64_t)B * M <= 4096 && precision == LB_FP64) {
         p.kind = PATH_SMALL;
-        const size_t base = sizeof(double) * 2 * (size_t)B * M;
-        const size_t withq = base + sizeof(double) * (size_t)M * M;
-        p.q_in_lds = withq <= 64 * 1024 ? 1 : 0;
-        p.shm = p.q_in_lds ? withq : base;
+        p.small = rk4_small_pick((int)M);
     } else if (B == 1 && precision == LB_FP64) {
         p.kind = PATH_GEMV;
         p.aligned = ldq % 2 == 0;
@@ -1304,9 +1243,9 @@ static int plan_init_state(const Plan& p, hipStream_t s) {
 static int plan_launch(const Plan& p, hipStream_t s, double dt, int64_t steps) {
     if (steps == 0) return LB_OK;
     if (p.kind == PATH_SMALL) {
-        hipLaunchKernelGGL(k_rk4_small, dim3(p.R), dim3(256), p.shm, s, (const double* const*)p.d,
+        hipLaunchKernelGGL(p.small.fn, dim3(p.R, p.B), dim3(p.small.threads), 0, s, (const double* const*)p.d,
                            (const double* const*)(p.d + 2 * p.R), (double* const*)(p.d + 3 * p.R), (int)p.M, p.ldq,
-                           p.B, dt, steps, p.q_in_lds);
+                           dt, steps);
         LB_CHECK_LAUNCH();
         return LB_OK;
     }
