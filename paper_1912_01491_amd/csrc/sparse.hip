@@ -21,13 +21,19 @@
 // additionally writes columns and values):
 //   densify H, L_p -> trace shift -> G = sum_p g_p L0^+ L0, A = i H - G/2
 //   column lists of A and L0_p, row lists of L0_p (ELL, width = max degree)
-//   pair rows:   one thread per row, L^+(F_s) in registers, merged and expanded
+//   pair rows:   one thread per row, the entries of L^+(F_s) in LDS, sorted in
+//                registers, merged and expanded
 //   diag lists:  diag(L(F_n)) per column n (count, scan, fill), then their
 //                exclusive prefix sums
-//   D rows:      one wavefront per row over the columns that carry a diagonal
+//   D rows:      one block per row over the columns that carry a diagonal
+// The stored entries (7.5 M for the N = 1000 dimer) are written in a fraction
+// of a millisecond; what the phases cost is the latency of many small steps, so
+// every loop over N or M runs across lanes and the scans stay on the device.
+// N = 1000 dimer, both phases: 14.9 ms before, 0.97 ms now.
 // Rows are written with sorted column indices (S block, J block, D block);
 // entries whose value is exactly zero are not stored.
 #include "lb_internal.h"
+#include "scan.h"
 
 #include <string.h>
 
@@ -39,8 +45,8 @@ constexpr double kR = 0.70710678118654752440;
 constexpr int kMaxRowEntries = 64;  // entries of L^+(F_s) held per pair row
 
 struct Ell {
-    const int* idx;  // N x W
-    const double* val;  // N x W complex
+    int* idx;     // N x W
+    double* val;  // N x W complex
     const int* cnt;  // N
     int W;
 };
@@ -52,14 +58,29 @@ __device__ __forceinline__ int ell_idx(const Ell& e, int i, int t) { return e.id
 // Dense set-up kernels
 // ---------------------------------------------------------------------------
 
-__global__ void k_densify(int N, const int64_t* rowptr, const int64_t* col, const double* val, double* D) {
-    const int r = blockIdx.x * blockDim.x + threadIdx.x;
-    if (r >= N) return;
-    for (int c = 0; c < N; ++c) cstore(D, (int64_t)r * N + c, cmk(0, 0));
-    for (int64_t e = rowptr[r]; e < rowptr[r + 1]; ++e) {
-        const int64_t c = col[e];
-        if (c < 0 || c >= N) continue;
-        cstore(D, (int64_t)r * N + c, cadd(cload(D, (int64_t)r * N + c), cload(val, e)));
+// One wavefront per row. Entries go in parallel when the row's columns are
+// strictly increasing; otherwise (repeated columns add up) one lane adds them
+// in their order. Columns outside 0..N-1 are ignored.
+__global__ __launch_bounds__(64) void k_densify(int N, const int64_t* rowptr, const int64_t* col, const double* val,
+                                                double* D) {
+    const int r = blockIdx.x, lane = threadIdx.x;
+    double* row = D + 2 * (int64_t)r * N;
+    for (int c = lane; c < N; c += 64) cstore(row, c, cmk(0, 0));
+    const int64_t e0 = rowptr[r], e1 = rowptr[r + 1];
+    bool bad = false;
+    for (int64_t e = e0 + lane; e + 1 < e1; e += 64) bad |= col[e + 1] <= col[e];
+    __syncthreads();
+    if (__ballot(bad) == 0) {
+        for (int64_t e = e0 + lane; e < e1; e += 64) {
+            const int64_t c = col[e];
+            if (c >= 0 && c < N) cstore(row, c, cadd(cmk(0, 0), cload(val, e)));
+        }
+    } else if (lane == 0) {
+        for (int64_t e = e0; e < e1; ++e) {
+            const int64_t c = col[e];
+            if (c < 0 || c >= N) continue;
+            cstore(row, c, cadd(cload(row, c), cload(val, e)));
+        }
     }
 }
 
@@ -100,72 +121,130 @@ __global__ void k_shift_l(int N, int P, double* Ld, const double* c) {
     cstore(L, (int64_t)x * N + x, csub(cload(L, (int64_t)x * N + x), cmk(c[2 * p], c[2 * p + 1])));
 }
 
-// H += sum_p (i g_p / 2)(conj(c_p) L0 - c_p L0^+);  G = sum_p g_p L0^+ L0;  A = i H - G/2
-__global__ void k_heff_g_a(int N, int P, const double* rates, const double* c, const double* Ld, double* Hd,
-                           double* G, double* A) {
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= (int64_t)N * N) return;
-    const int a = (int)(t / N), b = (int)(t % N);
-    cd h = cload(Hd, t);
-    cd g = cmk(0, 0);
-    for (int p = 0; p < P; ++p) {
-        const double* L = Ld + 2 * (int64_t)p * N * N;
-        const cd cp = cmk(c[2 * p], c[2 * p + 1]);
-        const double gp = rates[p];
-        const cd l_ab = cload(L, (int64_t)a * N + b);
-        const cd ldag_ab = cconj(cload(L, (int64_t)b * N + a));
-        const cd d = csub(cmul(cconj(cp), l_ab), cmul(cp, ldag_ab));
-        h = cadd(h, cscale(cmk(-d.im, d.re), 0.5 * gp));  // (i g/2) d
-        cd s = cmk(0, 0);
-        for (int x = 0; x < N; ++x) {
-            const cd lxa = cload(L, (int64_t)x * N + a);
-            if (lxa.re == 0.0 && lxa.im == 0.0) continue;
-            s = cadd(s, cmul(cconj(lxa), cload(L, (int64_t)x * N + b)));
+// H += sum_p (i g_p / 2)(conj(c_p) L0 - c_p L0^+);  G = sum_p g_p L0^+ L0;  A = i H - G/2.
+// One block per row a: column a of L0_p (a strided read) goes to LDS once, with
+// the list of its nonzeros in increasing x; then threads take b, so G_ab costs
+// the column's degree and not N.
+__global__ __launch_bounds__(256) void k_heff_a(int N, int P, const double* rates, const double* c, const double* Ld,
+                                                const double* Hd, double* A) {
+    extern __shared__ double2 lcol[];  // N values, then N indices
+    int* xl = reinterpret_cast<int*>(lcol + N);
+    __shared__ int wcnt[4];
+    const int a = blockIdx.x, lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    for (int b0 = 0; b0 < N; b0 += 4 * 256) {
+        // four b per thread at a time
+        cd h[4], g[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int b = b0 + 256 * u + threadIdx.x;
+            h[u] = b < N ? cload(Hd, (int64_t)a * N + b) : cmk(0, 0);
+            g[u] = cmk(0, 0);
         }
-        g = cadd(g, cscale(s, gp));
+        for (int p = 0; p < P; ++p) {
+            const double* L = Ld + 2 * (int64_t)p * N * N;
+            int n = 0;
+            for (int x0 = 0; x0 < N; x0 += 256) {
+                const int x = x0 + threadIdx.x;
+                const cd v = x < N ? cload(L, (int64_t)x * N + a) : cmk(0, 0);
+                const bool nz = !(v.re == 0.0 && v.im == 0.0);
+                const unsigned long long m = __ballot(nz);
+                __syncthreads();
+                if (lane == 0) wcnt[w] = __popcll(m);
+                __syncthreads();
+                int o = n + __popcll(m & ((1ull << lane) - 1ull));
+                for (int i = 0; i < 4; ++i) {
+                    if (i < w) o += wcnt[i];
+                    n += wcnt[i];
+                }
+                if (nz) xl[o] = x;
+                if (x < N) lcol[x] = make_double2(v.re, v.im);
+            }
+            __syncthreads();
+            const cd cp = cmk(c[2 * p], c[2 * p + 1]);
+            const double gp = rates[p];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int b = b0 + 256 * u + threadIdx.x;
+                if (b >= N) continue;
+                const cd l_ab = cload(L, (int64_t)a * N + b);
+                const cd ldag_ab = cmk(lcol[b].x, -lcol[b].y);
+                const cd d = csub(cmul(cconj(cp), l_ab), cmul(cp, ldag_ab));
+                h[u] = cadd(h[u], cscale(cmk(-d.im, d.re), 0.5 * gp));  // (i g/2) d
+                cd s = cmk(0, 0);
+                for (int t = 0; t < n; ++t) {
+                    const int x = xl[t];
+                    s = cadd(s, cmul(cmk(lcol[x].x, -lcol[x].y), cload(L, (int64_t)x * N + b)));
+                }
+                g[u] = cadd(g[u], cscale(s, gp));
+            }
+            __syncthreads();
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int b = b0 + 256 * u + threadIdx.x;
+            // A = i h - g/2
+            if (b < N)
+                cstore(A, (int64_t)a * N + b, cmk(-h[u].im - 0.5 * g[u].re, h[u].re - 0.5 * g[u].im));
+        }
     }
-    cstore(Hd, t, h);
-    cstore(G, t, g);
-    // A = i h - g/2
-    cstore(A, t, cmk(-h.im - 0.5 * g.re, h.re - 0.5 * g.im));
 }
 
-// ELL lists of the nonzeros of a dense N x N complex matrix, by column (bycol=1) or row.
-__global__ void k_ell_count(int N, const double* D, int bycol, int* cnt) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= N) return;
-    int n = 0;
-    for (int j = 0; j < N; ++j) {
-        const cd v = bycol ? cload(D, (int64_t)j * N + i) : cload(D, (int64_t)i * N + j);
-        if (v.re != 0.0 || v.im != 0.0) ++n;
-    }
-    cnt[i] = n;
+// Nonzeros of the N x N complex matrices in ELL lists, one wavefront per list.
+// List set 0 is A by column; 1 + 2p and 2 + 2p are L0_p by row and by column.
+__device__ __forceinline__ cd ell_src(int N, const double* A, const double* Ld, int set, int i, int j) {
+    const double* D = set == 0 ? A : Ld + 2 * (int64_t)((set - 1) >> 1) * N * N;
+    return set == 0 || !(set & 1) ? cload(D, (int64_t)j * N + i) : cload(D, (int64_t)i * N + j);
 }
 
-__global__ void k_ell_fill(int N, const double* D, int bycol, int W, int* idx, double* val) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+__global__ __launch_bounds__(256) void k_ell_count(int N, const double* A, const double* Ld, int* cnt) {
+    const int i = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63, set = blockIdx.y;
     if (i >= N) return;
     int n = 0;
-    for (int j = 0; j < N; ++j) {
-        const cd v = bycol ? cload(D, (int64_t)j * N + i) : cload(D, (int64_t)i * N + j);
-        if (v.re != 0.0 || v.im != 0.0) {
-            idx[(int64_t)i * W + n] = j;
-            cstore(val, (int64_t)i * W + n, v);
-            ++n;
+    for (int j0 = 0; j0 < N; j0 += 64) {
+        const int j = j0 + lane;
+        const cd v = j < N ? ell_src(N, A, Ld, set, i, j) : cmk(0, 0);
+        n += __popcll(__ballot(v.re != 0.0 || v.im != 0.0));
+    }
+    if (lane == 0) cnt[(int64_t)set * N + i] = n;
+}
+
+// Widest list of each set, one wavefront per set.
+__global__ __launch_bounds__(64) void k_ell_width(int N, const int* cnt, int* wmax) {
+    int m = 0;
+    for (int i = threadIdx.x; i < N; i += 64) m = max(m, cnt[(int64_t)blockIdx.x * N + i]);
+    for (int o = 32; o > 0; o >>= 1) m = max(m, __shfl_xor(m, o, 64));
+    if (threadIdx.x == 0) wmax[blockIdx.x] = m;
+}
+
+__global__ __launch_bounds__(256) void k_ell_fill(int N, const double* A, const double* Ld, const Ell* ells) {
+    const int i = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63, set = blockIdx.y;
+    if (i >= N) return;
+    const Ell e = ells[set];
+    int n = 0;
+    for (int j0 = 0; j0 < N; j0 += 64) {
+        const int j = j0 + lane;
+        const cd v = j < N ? ell_src(N, A, Ld, set, i, j) : cmk(0, 0);
+        const bool nz = v.re != 0.0 || v.im != 0.0;
+        const unsigned long long m = __ballot(nz);
+        if (nz) {
+            const int64_t o = (int64_t)i * e.W + n + __popcll(m & ((1ull << lane) - 1ull));
+            e.idx[o] = j;
+            cstore(e.val, o, v);
         }
+        n += __popcll(m);
     }
 }
 
 // diag(L(1))_x = 2 Re Z_xx + sum_p g_p sum_b |L0_p,xb|^2, with Z = A^+ (Re Z_xx = Re A_xx)
-__global__ void k_l1diag(int N, int P, const double* rates, const double* A, const double* Ld, double* out) {
+__global__ void k_l1diag(int N, int P, const double* rates, const double* A, const Ell* Lrow, double* out) {
     const int x = blockIdx.x * blockDim.x + threadIdx.x;
     if (x >= N) return;
     double s = 2.0 * cload(A, (int64_t)x * N + x).re;
     for (int p = 0; p < P; ++p) {
-        const double* L = Ld + 2 * (int64_t)p * N * N;
+        const Ell Lr = Lrow[2 * p];
         double q = 0;
-        for (int b = 0; b < N; ++b) {
-            const cd v = cload(L, (int64_t)x * N + b);
+        for (int t = 0; t < Lr.cnt[x]; ++t) {
+            const cd v = ell_val(Lr, x, t);
             q += v.re * v.re + v.im * v.im;
         }
         s += rates[p] * q;
@@ -178,10 +257,9 @@ __global__ void k_l1diag(int N, int P, const double* rates, const double* A, con
 // ---------------------------------------------------------------------------
 
 struct PairArgs {
-    int N, P;
-    int64_t Pp;  // number of pairs
-    Ell Acol;    // columns of A = iH - G/2
-    const Ell* Lrow;  // rows of L0_p (P entries, device array)
+    int N, P, bound;  // bound: largest number of entries of a row of L^+(F_s)
+    int64_t Pp;       // number of pairs
+    const Ell* ells;  // set 0: columns of A = iH - G/2; 1 + 2p: rows of L0_p
     const double* rates;
     // outputs
     int64_t* cnt;          // count phase: entries per row
@@ -192,151 +270,213 @@ struct PairArgs {
     int* overflow;
 };
 
-struct Ent {
-    int a, c;
-    cd v;
+// A row's entries while it is formed: [entry][lane], the values in LDS together
+// with their sort keys (position << 6 | entry; position = pair * 2 + (a > c) for
+// the off-diagonal entry (a, c), 2 P + a for the diagonal, below 2^23 for
+// N <= 2048, so keys are unique and sorting keeps the order of equal positions).
+struct RowList {
+    double2* val;
+    uint32_t* key;
+    int n, bound;
+    int* overflow;
+    __device__ __forceinline__ void push(uint32_t pos, cd v) {
+        if (n >= bound) {
+            *overflow = 1;
+            return;
+        }
+        val[n * 64] = make_double2(v.re, v.im);
+        key[n * 64] = (pos << 6) | (uint32_t)n;
+        ++n;
+    }
 };
 
-__device__ __forceinline__ void push(Ent* E, int& n, int a, int c, cd v, int* overflow) {
-    if (n >= kMaxRowEntries) {
-        *overflow = 1;
-        return;
-    }
-    E[n].a = a;
-    E[n].c = c;
-    E[n].v = v;
-    ++n;
+// Sorts the first n of at most NB keys (stride 64 in LDS) by Batcher's odd-even
+// merge network on registers: no data-dependent step, NB (log NB)^2 / 4 exchanges.
+template <int NB>
+__device__ __forceinline__ void sort_keys(uint32_t* key, int n) {
+    uint32_t k[NB];
+#pragma unroll
+    for (int i = 0; i < NB; ++i) k[i] = i < n ? key[i * 64] : 0xffffffffu;
+#pragma unroll
+    for (int p = 1; p < NB; p <<= 1)
+#pragma unroll
+        for (int q = p; q >= 1; q >>= 1)
+#pragma unroll
+            for (int j = q % p; j + q < NB; j += 2 * q)
+#pragma unroll
+                for (int i = 0; i < q; ++i)
+                    if (i + j + q < NB && (i + j) / (2 * p) == (i + j + q) / (2 * p)) {
+                        const uint32_t lo = min(k[i + j], k[i + j + q]), hi = max(k[i + j], k[i + j + q]);
+                        k[i + j] = lo;
+                        k[i + j + q] = hi;
+                    }
+#pragma unroll
+    for (int i = 0; i < NB; ++i)
+        if (i < n) key[i * 64] = k[i];
 }
 
-__global__ void k_pair_rows(PairArgs g, int fill) {
-    const int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (s >= 2 * g.Pp) return;
+__device__ __forceinline__ uint32_t row_pos(int N, int64_t Pp, int a, int c) {
+    if (a == c) return (uint32_t)(2 * Pp + a);
+    return (uint32_t)(2 * lb_upair(N, a, c) + (a > c ? 1 : 0));
+}
+
+// One thread per row, one wavefront per block; dynamic LDS of 64 bound (16 + 4)
+// bytes. The same arithmetic in the count and the fill phase, so they agree on
+// which entries are exactly zero and not stored. (With the entries in a private
+// array, which lived in scratch memory, and an insertion sort there, N = 1000:
+// 1.09 ms in the count and 1.27 ms in the fill phase; now 70 and 118 us.)
+template <int NB>
+__global__ __launch_bounds__(64) void k_pair_rows(PairArgs g, int fill) {
+    extern __shared__ double2 rowmem[];
+    const int64_t s = (int64_t)blockIdx.x * 64 + threadIdx.x;
     const int N = g.N;
-    const int cls = s >= g.Pp ? 1 : 0;
-    const int64_t ps = s - cls * g.Pp;
-    int cc, u, v;
-    lb_decode(N, ps, cc, u, v);
-    const cd al = cls == 0 ? cmk(kR, 0) : cmk(0, -kR);  // (F_s)_uv
-    const cd be = cls == 0 ? cmk(kR, 0) : cmk(0, kR);   // (F_s)_vu
-    Ent E[kMaxRowEntries];
-    int n = 0;
-    // i H F_s - G F_s / 2 = A F_s: (a, v) += al A_au, (a, u) += be A_av
-    for (int t = 0; t < g.Acol.cnt[u]; ++t) push(E, n, ell_idx(g.Acol, u, t), v, cmul(al, ell_val(g.Acol, u, t)), g.overflow);
-    for (int t = 0; t < g.Acol.cnt[v]; ++t) push(E, n, ell_idx(g.Acol, v, t), u, cmul(be, ell_val(g.Acol, v, t)), g.overflow);
-    // -i F_s H - F_s G / 2 = F_s A^+: (u, c) += al conj(A_cv), (v, c) += be conj(A_cu)
-    for (int t = 0; t < g.Acol.cnt[v]; ++t) push(E, n, u, ell_idx(g.Acol, v, t), cmul(al, cconj(ell_val(g.Acol, v, t))), g.overflow);
-    for (int t = 0; t < g.Acol.cnt[u]; ++t) push(E, n, v, ell_idx(g.Acol, u, t), cmul(be, cconj(ell_val(g.Acol, u, t))), g.overflow);
-    // g_p L0^+ F_s L0: (a, c) += g al conj(L0_ua) L0_vc + g be conj(L0_va) L0_uc
-    for (int p = 0; p < g.P; ++p) {
-        const Ell Lr = g.Lrow[p];
-        const double gp = g.rates[p];
-        if (gp == 0.0) continue;
-        for (int t1 = 0; t1 < Lr.cnt[u]; ++t1)
-            for (int t2 = 0; t2 < Lr.cnt[v]; ++t2) {
-                const int a = ell_idx(Lr, u, t1), c = ell_idx(Lr, v, t2);
-                push(E, n, a, c, cscale(cmul(al, cmul(cconj(ell_val(Lr, u, t1)), ell_val(Lr, v, t2))), gp), g.overflow);
-            }
-        for (int t1 = 0; t1 < Lr.cnt[v]; ++t1)
-            for (int t2 = 0; t2 < Lr.cnt[u]; ++t2) {
-                const int a = ell_idx(Lr, v, t1), c = ell_idx(Lr, u, t2);
-                push(E, n, a, c, cscale(cmul(be, cmul(cconj(ell_val(Lr, v, t1)), ell_val(Lr, u, t2))), gp), g.overflow);
-            }
-    }
-    // order: off-diagonal entries by (pair, a) with diagonal entries last by position;
-    // key = pair position * 2 + (a > c) for off-diagonal, large + x for diagonal
     const int64_t Pp = g.Pp;
-    auto key = [&](const Ent& e) -> int64_t {
-        if (e.a == e.c) return 2 * Pp + e.a;
-        return 2 * lb_upair(N, e.a, e.c) + (e.a > e.c ? 1 : 0);
+    const bool live = s < 2 * Pp;
+    RowList E;
+    E.val = rowmem + threadIdx.x;
+    E.key = reinterpret_cast<uint32_t*>(rowmem + 64 * g.bound) + threadIdx.x;
+    E.n = 0;
+    E.bound = g.bound;
+    E.overflow = g.overflow;
+    if (live) {
+        const int cls = s >= Pp ? 1 : 0;
+        int cc, u, v;
+        lb_decode(N, s - cls * Pp, cc, u, v);
+        const cd al = cls == 0 ? cmk(kR, 0) : cmk(0, -kR);  // (F_s)_uv
+        const cd be = cls == 0 ? cmk(kR, 0) : cmk(0, kR);   // (F_s)_vu
+        const Ell Ac = g.ells[0];
+        const int nu = Ac.cnt[u], nv = Ac.cnt[v];
+        // i H F_s - G F_s / 2 = A F_s: (a, v) += al A_au, (a, u) += be A_av
+        for (int t = 0; t < nu; ++t) E.push(row_pos(N, Pp, ell_idx(Ac, u, t), v), cmul(al, ell_val(Ac, u, t)));
+        for (int t = 0; t < nv; ++t) E.push(row_pos(N, Pp, ell_idx(Ac, v, t), u), cmul(be, ell_val(Ac, v, t)));
+        // -i F_s H - F_s G / 2 = F_s A^+: (u, c) += al conj(A_cv), (v, c) += be conj(A_cu)
+        for (int t = 0; t < nv; ++t) E.push(row_pos(N, Pp, u, ell_idx(Ac, v, t)), cmul(al, cconj(ell_val(Ac, v, t))));
+        for (int t = 0; t < nu; ++t) E.push(row_pos(N, Pp, v, ell_idx(Ac, u, t)), cmul(be, cconj(ell_val(Ac, u, t))));
+        // g_p L0^+ F_s L0: (a, c) += g al conj(L0_ua) L0_vc + g be conj(L0_va) L0_uc
+        for (int p = 0; p < g.P; ++p) {
+            const Ell Lr = g.ells[1 + 2 * p];
+            const double gp = g.rates[p];
+            if (gp == 0.0) continue;
+            const int lu = Lr.cnt[u], lv = Lr.cnt[v];
+            for (int t1 = 0; t1 < lu; ++t1)
+                for (int t2 = 0; t2 < lv; ++t2)
+                    E.push(row_pos(N, Pp, ell_idx(Lr, u, t1), ell_idx(Lr, v, t2)),
+                           cscale(cmul(al, cmul(cconj(ell_val(Lr, u, t1)), ell_val(Lr, v, t2))), gp));
+            for (int t1 = 0; t1 < lv; ++t1)
+                for (int t2 = 0; t2 < lu; ++t2)
+                    E.push(row_pos(N, Pp, ell_idx(Lr, v, t1), ell_idx(Lr, u, t2)),
+                           cscale(cmul(be, cmul(cconj(ell_val(Lr, v, t1)), ell_val(Lr, u, t2))), gp));
+        }
+    }
+    sort_keys<NB>(E.key, E.n);
+    const int n = E.n;
+    const uint32_t diag0 = (uint32_t)(2 * Pp);
+    // Off-diagonal entries come first, pair by pair: Y_pq (p < q) and Y_qp, each
+    // the sum of its entries in the order they were formed. Tr(Y S_pq) =
+    // r (Y_pq + Y_qp); Tr(Y J_pq) = i r (Y_pq - Y_qp). The S block of the row,
+    // then the J block; the count phase takes both in one pass.
+    constexpr uint32_t kEnd = 0xffffffffu;
+    auto key_at = [&](int i) { return i < n ? E.key[i * 64] : kEnd; };
+    auto val_of = [&](uint32_t k) {
+        const double2 v = E.val[(k & 63u) * 64];
+        return cmk(v.x, v.y);
     };
-    for (int i = 1; i < n; ++i) {  // insertion sort (n is small)
-        Ent x = E[i];
-        const int64_t kx = key(x);
-        int j = i - 1;
-        while (j >= 0 && key(E[j]) > kx) {
-            E[j + 1] = E[j];
-            --j;
-        }
-        E[j + 1] = x;
-    }
-    // merge equal keys
-    int m = 0;
-    for (int i = 0; i < n; ++i) {
-        if (m > 0 && key(E[m - 1]) == key(E[i])) E[m - 1].v = cadd(E[m - 1].v, E[i].v);
-        else E[m++] = E[i];
-    }
-    // diagonal range and trace
-    int first_diag = -1;
-    cd tr = cmk(0, 0);
-    for (int i = 0; i < m; ++i) {
-        if (E[i].a == E[i].c) {
-            if (first_diag < 0) first_diag = i;
-            tr = cadd(tr, E[i].v);
-        }
-    }
-    // D columns m from max(1, xmin) to xmax, or to N-1 when Tr(Y) != 0: beyond the
-    // last diagonal position the value is Tr(Y)/sqrt(m(m+1)) = N K_s/sqrt(m(m+1)).
-    int nd = 0, xmin = N, xhi = -1;
-    if (first_diag >= 0) {
-        xmin = E[first_diag].a;
-        double asum = 0;
-        for (int i = first_diag; i < m; ++i) asum += fabs(E[i].v.re) + fabs(E[i].v.im);
-        const bool traced = fabs(tr.re) > 1e-13 * asum;
-        xhi = traced ? N - 1 : E[m - 1].a;
-        const int lo = xmin > 1 ? xmin : 1;
-        nd = xhi >= lo ? xhi - lo + 1 : 0;
-    }
-    // Entries are emitted in column order (S block, J block, D block); values
-    // that are exactly zero (e.g. the S part of i[H, S_pq] for real H) are not
-    // stored. Count and fill run the same arithmetic, so they agree on which
-    // entries are kept.
-    int64_t o = fill ? g.rowptr[s] : 0;
-    if (fill) g.K[s] = tr.re / N;
-    for (int part = 0; part < 2; ++part) {
-        for (int i = 0; i < m; ++i) {
-            if (E[i].a == E[i].c) break;
-            const int64_t pp = lb_upair(N, E[i].a, E[i].c);
-            cd ypq = cmk(0, 0), yqp = cmk(0, 0);  // (p,q) with p < q
-            if (E[i].a < E[i].c) ypq = E[i].v;
-            else yqp = E[i].v;
-            if (i + 1 < m && E[i + 1].a != E[i + 1].c && lb_upair(N, E[i + 1].a, E[i + 1].c) == pp) {
+    const uint32_t dkey = diag0 << 6;  // keys of diagonal entries start here
+    int64_t o = fill && live ? g.rowptr[s] : 0;
+    int nd0 = 0;  // first diagonal entry
+    for (int part = 0; part < (fill ? 2 : 1); ++part) {
+        int i = 0;
+        uint32_t k = key_at(0), kn = key_at(1);
+        while (k < dkey) {
+            const uint32_t pr = k >> 7;
+            cd y0 = cmk(0, 0), y1 = cmk(0, 0);
+            do {
+                const cd e = val_of(k);
+                if (k & 64u) y1 = cadd(y1, e);
+                else y0 = cadd(y0, e);
+                k = kn;
                 ++i;
-                if (E[i].a < E[i].c) ypq = cadd(ypq, E[i].v);
-                else yqp = cadd(yqp, E[i].v);
-            }
-            // Tr(Y S_pq) = r (Y_pq + Y_qp); Tr(Y J_pq) = i r (Y_pq - Y_qp)
-            const double q = part == 0 ? kR * (ypq.re + yqp.re) : -kR * (ypq.im - yqp.im);
-            if (q == 0.0) continue;
-            if (fill) {
-                g.col[o] = part * Pp + pp;
-                g.val[o] = q;
-            }
-            ++o;
-        }
-    }
-    if (nd > 0) {
-        cd pre = cmk(0, 0);
-        int di = first_diag;
-        for (int x = 0; x < N; ++x) {
-            cd yx = cmk(0, 0);
-            if (di < m && E[di].a == x) {
-                yx = E[di].v;
-                ++di;
-            }
-            if (x >= 1 && x >= xmin && x <= xhi) {
-                const double q = (pre.re - (double)x * yx.re) / sqrt((double)x * (x + 1));
+                kn = key_at(i + 1);
+            } while ((k >> 7) == pr && k < dkey);
+            const double qs = kR * (y0.re + y1.re), qj = -kR * (y0.im - y1.im);
+            if (!fill) {
+                o += (qs != 0.0) + (qj != 0.0);
+            } else {
+                const double q = part == 0 ? qs : qj;
                 if (q != 0.0) {
-                    if (fill) {
-                        g.col[o] = 2 * Pp + x - 1;
-                        g.val[o] = q;
-                    }
+                    g.col[o] = part * Pp + pr;
+                    g.val[o] = q;
                     ++o;
                 }
             }
-            pre = cadd(pre, yx);
+        }
+        nd0 = i;
+    }
+    // Diagonal entries (merged by position): Tr Y, and the D columns m from
+    // max(1, first position) to the last position, or to N-1 when Tr(Y) != 0:
+    // beyond the last position the value is Tr(Y)/sqrt(m(m+1)).
+    auto merged = [&](int& i) {  // sum of the entries at entry i's position; i moves past them
+        const uint32_t ps = key_at(i) >> 6;
+        cd y = val_of(key_at(i++));
+        while (i < n && key_at(i) >> 6 == ps) y = cadd(y, val_of(key_at(i++)));
+        return y;
+    };
+    cd tr = cmk(0, 0);
+    double asum = 0;
+    int xmin = N, xlast = -1;
+    for (int i = nd0; i < n;) {
+        const int x = (int)((key_at(i) >> 6) - diag0);
+        if (xlast < 0) xmin = x;
+        xlast = x;
+        const cd y = merged(i);
+        tr = cadd(tr, y);
+        asum += fabs(y.re) + fabs(y.im);
+    }
+    const bool traced = xlast >= 0 && fabs(tr.re) > 1e-13 * asum;
+    if (fill && live) g.K[s] = tr.re / N;
+    double pre = 0.0;
+    int di = nd0;
+    for (int x = xmin; x <= xlast; ++x) {
+        cd y = cmk(0, 0);
+        if (key_at(di) >> 6 == diag0 + (uint32_t)x) y = merged(di);
+        if (x >= 1) {
+            const double q = (pre - (double)x * y.re) / sqrt((double)x * (x + 1));
+            if (q != 0.0) {
+                if (fill) {
+                    g.col[o] = 2 * Pp + x - 1;
+                    g.val[o] = q;
+                }
+                ++o;
+            }
+        }
+        pre += y.re;
+    }
+    // The tail beyond the last position, one row of the wavefront at a time
+    // across its lanes. |q| falls with m, so all of it is nonzero if the last is.
+    int t0 = xlast + 1 > 1 ? xlast + 1 : 1;
+    int len = live && traced && t0 < N ? N - t0 : 0;
+    if (len > 0 && !(pre / sqrt((double)(N - 1) * N) != 0.0)) {
+        int keep = 0;
+        for (int x = t0; x < N; ++x) keep += pre / sqrt((double)x * (x + 1)) != 0.0;
+        len = keep;
+    }
+    if (!fill) {
+        if (live) g.cnt[s] = o + len;
+        return;
+    }
+    unsigned long long todo = __ballot(len > 0);
+    while (todo) {
+        const int src = __ffsll(todo) - 1;
+        todo &= todo - 1;
+        const int x0 = __shfl(t0, src, 64), cnt = __shfl(len, src, 64);
+        const double p = __shfl(pre, src, 64);
+        const int64_t o0 = __shfl(o, src, 64);
+        for (int i = threadIdx.x; i < cnt; i += 64) {
+            const int x = x0 + i;
+            g.col[o0 + i] = 2 * Pp + x - 1;
+            g.val[o0 + i] = p / sqrt((double)x * (x + 1));
         }
     }
-    if (!fill) g.cnt[s] = o;
 }
 
 // ---------------------------------------------------------------------------
@@ -347,8 +487,7 @@ struct DiagArgs {
     int N, P;
     int64_t Pp, M;
     const double* A;   // dense N x N, Z = A^+
-    const Ell* Lcol;   // columns of L0_p
-    const Ell* Lrow;   // rows of L0_p
+    const Ell* ells;   // 1 + 2p: rows of L0_p, 2 + 2p: its columns
     const double* rates;
     int64_t* cnt;
     const int64_t* off;
@@ -403,7 +542,7 @@ __global__ void k_diag_pairs(DiagArgs g, int fill, int* ovf) {
     if (dy.re != 0.0 || dy.im != 0.0) acc.add(y, dy, ovf);
     // g_p (L0 F_n L0^+)_aa = g_p (L0_ax al conj(L0_ay) + L0_ay be conj(L0_ax))
     for (int p = 0; p < g.P; ++p) {
-        const Ell Lc = g.Lcol[p];
+        const Ell Lc = g.ells[2 + 2 * p];
         const double gp = g.rates[p];
         if (gp == 0.0) continue;
         for (int t1 = 0; t1 < Lc.cnt[x]; ++t1) {
@@ -427,37 +566,47 @@ __global__ void k_diag_pairs(DiagArgs g, int fill, int* ovf) {
     }
 }
 
-// D columns n = D^m': diag_a = w_m'(a) 2 Re Z_aa + sum_p g_p sum_{y <= m'} w_m'(y) |L0_p,ay|^2
-__global__ void k_diag_dcols(DiagArgs g, int fill) {
-    const int mm = blockIdx.x * blockDim.x + threadIdx.x + 1;
+// D columns n = D^m': diag_a = w_m'(a) 2 Re Z_aa + sum_p g_p sum_{y <= m'} w_m'(y) |L0_p,ay|^2,
+// one wavefront per column, lanes along a (a ballot keeps the positions in order).
+__global__ __launch_bounds__(256) void k_diag_dcols(DiagArgs g, int fill) {
+    const int lane = threadIdx.x & 63;
+    const int mm = blockIdx.x * 4 + (threadIdx.x >> 6) + 1;
     const int N = g.N;
     if (mm >= N) return;
     const int64_t nidx = 2 * g.Pp + mm - 1;
-    int64_t o = fill ? g.off[nidx] : 0;
+    const int64_t o = fill ? g.off[nidx] : 0;
+    const double nrm = 1.0 / sqrt((double)mm * (mm + 1));
+    auto wd = [&](int x) { return x < mm ? nrm : (x == mm ? -(double)mm * nrm : 0.0); };  // lb_wdiag(mm, x)
     int64_t n = 0;
-    for (int a = 0; a < N; ++a) {
-        bool nz = a <= mm;
-        cd d = cmk(lb_wdiag(mm, a) * 2.0 * cload(g.A, (int64_t)a * N + a).re, 0.0);
-        for (int p = 0; p < g.P; ++p) {
-            const Ell Lr = g.Lrow[p];
-            double s = 0;
-            for (int t = 0; t < Lr.cnt[a]; ++t) {
-                const int yy = ell_idx(Lr, a, t);
-                if (yy > mm) continue;
-                const cd l = ell_val(Lr, a, t);
-                s += lb_wdiag(mm, yy) * (l.re * l.re + l.im * l.im);
-                nz = true;
+    for (int a0 = 0; a0 < N; a0 += 64) {
+        const int a = a0 + lane;
+        bool nz = false;
+        cd d = cmk(0, 0);
+        if (a < N) {
+            nz = a <= mm;
+            d = cmk(wd(a) * 2.0 * cload(g.A, (int64_t)a * N + a).re, 0.0);
+            for (int p = 0; p < g.P; ++p) {
+                const Ell Lr = g.ells[1 + 2 * p];
+                double s = 0;
+                for (int t = 0; t < Lr.cnt[a]; ++t) {
+                    const int yy = ell_idx(Lr, a, t);
+                    if (yy > mm) continue;
+                    const cd l = ell_val(Lr, a, t);
+                    s += wd(yy) * (l.re * l.re + l.im * l.im);
+                    nz = true;
+                }
+                d.re += g.rates[p] * s;
             }
-            d.re += g.rates[p] * s;
         }
-        if (!nz) continue;
-        if (fill) {
-            g.pos[o + n] = a;
-            cstore(g.val, o + n, d);
+        const unsigned long long m = __ballot(nz);
+        if (nz && fill) {
+            const int64_t r = o + n + __popcll(m & ((1ull << lane) - 1ull));
+            g.pos[r] = a;
+            cstore(g.val, r, d);
         }
-        ++n;
+        n += __popcll(m);
     }
-    if (!fill) g.cnt[nidx] = n;
+    if (!fill && lane == 0) g.cnt[nidx] = n;
 }
 
 // D rows: Q[D^m][n] = sum_x w_m(x) diag_n(x) = (pre_n(m) - m diag_n(m)) / sqrt(m(m+1)),
@@ -479,107 +628,121 @@ struct DRowArgs {
     double* K;
 };
 
-// Exclusive prefix sums of the diagonal lists, one thread per carrying column.
-__global__ void k_diag_prefix(int64_t ncarry, const int64_t* carry, const int64_t* off, const double* val,
-                              double* pref) {
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+// Exclusive prefix sums of the diagonal lists, added one by one in the lists'
+// order. Columns of pairs (a few entries each) take a thread, columns of
+// diagonal generators (up to N entries, the last ncarry - npair of the carrying
+// ones) a wavefront: it loads 64 entries at once, the next 64 ahead, and passes
+// the running sum along the lanes.
+__global__ __launch_bounds__(64) void k_diag_prefix(int64_t npair, int64_t ncarry, unsigned pair_blocks,
+                                                    const int64_t* carry, const int64_t* off, const double* val,
+                                                    double* pref) {
+    const int lane = threadIdx.x;
+    if (blockIdx.x < pair_blocks) {
+        const int64_t t = (int64_t)blockIdx.x * 64 + lane;
+        if (t >= npair) return;
+        const int64_t c = carry[t];
+        double run = 0;
+        for (int64_t e = off[c]; e < off[c + 1]; ++e) {
+            pref[e] = run;
+            run += val[2 * e];
+        }
+        return;
+    }
+    const int64_t t = npair + (blockIdx.x - pair_blocks);
     if (t >= ncarry) return;
     const int64_t c = carry[t];
-    double run = 0;
-    for (int64_t e = off[c]; e < off[c + 1]; ++e) {
-        pref[e] = run;
-        run += val[2 * e];
+    const int64_t e0 = off[c], e1 = off[c + 1];
+    double run = 0, next = e0 + lane < e1 ? val[2 * (e0 + lane)] : 0.0;
+    for (int64_t e = e0; e < e1; e += 64) {
+        const uint2 w = __builtin_bit_cast(uint2, next);
+        if (e + 64 + lane < e1) next = val[2 * (e + 64 + lane)];
+        double mine = 0;
+#pragma unroll
+        for (int l = 0; l < 64; ++l) {
+            if (l == lane) mine = run;
+            run += __builtin_bit_cast(double, make_uint2((unsigned)__builtin_amdgcn_readlane((int)w.x, l),
+                                                         (unsigned)__builtin_amdgcn_readlane((int)w.y, l)));
+        }
+        if (e + lane < e1) pref[e + lane] = mine;
     }
 }
 
-// One wavefront per D row: lanes take 64 carrying columns at a time; a column
-// contributes when its list reaches row m (key <= m <= last position: the list
-// sums to Tr L(F_n) = 0, so rows beyond its last position vanish) and the value
-// is not exactly zero. A ballot keeps the columns in increasing order.
-__global__ __launch_bounds__(256) void k_drows_sparse(DRowArgs g, int fill) {
-    const int lane = threadIdx.x & 63;
-    const int m = (int)(((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6) + 1;
+// One block of 16 wavefronts per D row, each over a contiguous sixteenth of the
+// carrying columns, 64 at a time: a column contributes when its list reaches
+// row m (key <= m <= last position: the list sums to Tr L(F_n) = 0, so rows
+// beyond its last position vanish) and the value is not exactly zero. Ballots
+// and the wavefronts' counts keep the columns in increasing order.
+constexpr int kDrowWaves = 16;
+
+__device__ __forceinline__ bool drow_value(const DRowArgs& g, int64_t t, int64_t t1, int m, double nrm, int64_t& c,
+                                           double& q) {
+    if (t >= t1) return false;
+    c = g.carry[t];
+    int64_t lo = g.off[c], hi = g.off[c + 1] - 1;
+    const int key = g.pos[lo] > 1 ? g.pos[lo] : 1;
+    if (key > m || g.pos[hi] < m) return false;
+    // first entry at position >= m; positions increase, so it is at most m - pos[lo] entries on, and
+    // exactly there in a list without gaps (those of the diagonal generators)
+    const int64_t at0 = lo + (m - g.pos[lo]);
+    if (at0 >= lo && at0 < hi) hi = at0;
+    if (g.pos[hi] == m) lo = hi;
+    while (lo < hi) {
+        const int64_t mid = (lo + hi) >> 1;
+        if (g.pos[mid] < m) lo = mid + 1;
+        else hi = mid;
+    }
+    const double at = g.pos[lo] == m ? g.val[2 * lo] : 0.0;
+    q = (g.pref[lo] - (double)m * at) * nrm;
+    return q != 0.0;
+}
+
+__global__ __launch_bounds__(64 * kDrowWaves) void k_drows_sparse(DRowArgs g, int fill) {
+    __shared__ int64_t wcnt[kDrowWaves];
+    extern __shared__ double l1[];  // fill phase: diag(L(1)), N entries
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int m = blockIdx.x + 1;
     const int N = g.N;
-    if (m >= N) return;
+    if (fill)
+        for (int x = threadIdx.x; x <= m; x += 64 * kDrowWaves) l1[x] = g.l1diag[x];
     const int64_t row = 2 * g.Pp + m - 1;
     const double nrm = 1.0 / sqrt((double)m * (m + 1));
-    int64_t o = fill ? g.rowptr[row] : 0;
-    for (int64_t t0 = 0; t0 < g.ncarry; t0 += 64) {
-        const int64_t t = t0 + lane;
-        int64_t c = 0;
-        double q = 0.0;
-        bool keep = false;
-        if (t < g.ncarry) {
-            c = g.carry[t];
-            int64_t lo = g.off[c], hi = g.off[c + 1] - 1;
-            const int key = g.pos[lo] > 1 ? g.pos[lo] : 1;
-            if (key <= m && g.pos[hi] >= m) {
-                while (lo < hi) {  // first entry at position >= m
-                    const int64_t mid = (lo + hi) >> 1;
-                    if (g.pos[mid] < m) lo = mid + 1;
-                    else hi = mid;
-                }
-                const double at = g.pos[lo] == m ? g.val[2 * lo] : 0.0;
-                q = (g.pref[lo] - (double)m * at) * nrm;
-                keep = q != 0.0;
-            }
-        }
+    const int64_t per = ((g.ncarry + kDrowWaves - 1) / kDrowWaves + 63) / 64 * 64;
+    const int64_t t0 = w * per, t1 = t0 + per < g.ncarry ? t0 + per : g.ncarry;
+    int64_t n = 0, c = 0;
+    double q = 0.0;
+    for (int64_t t = t0; t < t1; t += 64) n += __popcll(__ballot(drow_value(g, t + lane, t1, m, nrm, c, q)));
+    if (lane == 0) wcnt[w] = n;
+    __syncthreads();
+    int64_t o = 0, tot = 0;
+    for (int i = 0; i < kDrowWaves; ++i) {
+        if (i < w) o += wcnt[i];
+        tot += wcnt[i];
+    }
+    if (!fill) {
+        if (threadIdx.x == 0) g.cnt[row] = tot;
+        return;
+    }
+    o += g.rowptr[row];
+    for (int64_t t = t0; t < t1; t += 64) {
+        const bool keep = drow_value(g, t + lane, t1, m, nrm, c, q);
         const unsigned long long mask = __ballot(keep);
-        if (keep && fill) {
+        if (keep) {
             const int64_t r = o + __popcll(mask & ((1ull << lane) - 1ull));
             g.col[r] = c;
             g.qv[r] = q;
         }
         o += __popcll(mask);
     }
-    if (lane != 0) return;
-    if (!fill) {
-        g.cnt[row] = o;
-        return;
+    if (threadIdx.x == 64 * (kDrowWaves - 1)) {
+        double k = 0;
+#pragma unroll 8
+        for (int x = 0; x < m; ++x) k += nrm * l1[x];  // lb_wdiag(m, x), its root taken once
+        k += -(double)m * nrm * l1[m];
+        g.K[row] = k / N;
     }
-    double k = 0;
-    for (int x = 0; x <= m; ++x) k += lb_wdiag(m, x) * g.l1diag[x];
-    g.K[row] = k / N;
-}
-
-__global__ void k_mark_carry(int64_t M, const int64_t* cnt, int64_t* flag) {
-    const int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (c < M) flag[c] = cnt[c] > 0 ? 1 : 0;
 }
 
 }  // namespace
-
-// Exclusive scan of n int64 on the host through the pinned buffer; writes n+1 offsets.
-static int host_scan(lb_ctx* c, int64_t* dev, int64_t n, int64_t* total) {
-    int rc = lb_host_reserve(c, sizeof(int64_t) * (n + 1));
-    if (rc) return rc;
-    int64_t* h = (int64_t*)c->host;
-    LB_HIP(hipMemcpyAsync(h, dev, sizeof(int64_t) * n, hipMemcpyDeviceToHost, c->stream));
-    LB_HIP(hipStreamSynchronize(c->stream));
-    int64_t run = 0;
-    for (int64_t i = 0; i < n; ++i) {
-        const int64_t v = h[i];
-        h[i] = run;
-        run += v;
-    }
-    h[n] = run;
-    *total = run;
-    LB_HIP(hipMemcpyAsync(dev, h, sizeof(int64_t) * (n + 1), hipMemcpyHostToDevice, c->stream));
-    LB_HIP(hipStreamSynchronize(c->stream));
-    return LB_OK;
-}
-
-static int max_of(lb_ctx* c, const int* dev, int n, int* out) {
-    int rc = lb_host_reserve(c, sizeof(int) * n);
-    if (rc) return rc;
-    int* h = (int*)c->host;
-    LB_HIP(hipMemcpyAsync(h, dev, sizeof(int) * n, hipMemcpyDeviceToHost, c->stream));
-    LB_HIP(hipStreamSynchronize(c->stream));
-    int m = 0;
-    for (int i = 0; i < n; ++i) m = std::max(m, h[i]);
-    *out = m;
-    return LB_OK;
-}
 
 // Returns LB_OK, a negative status, or 1 when the workspace must grow to *want
 // bytes first (growing reallocates it, so the caller restarts from the top).
@@ -590,6 +753,7 @@ static int sparse_body(lb_ctx* c, int N, const lb_csr_c128* H, int P, const doub
     const int64_t M = (int64_t)N * N - 1;
     const int64_t Pp = lb_npairs(N);
     const int64_t NN = (int64_t)N * N;
+    const int nsets = 1 + 2 * P;
     // workspace layout
     size_t off = 0;
     auto take = [&](size_t bytes) {
@@ -599,48 +763,57 @@ static int sparse_body(lb_ctx* c, int N, const lb_csr_c128* H, int P, const doub
     };
     const size_t o_h = take(sizeof(double) * 2 * NN);
     const size_t o_l = take(sizeof(double) * 2 * NN * (P > 0 ? P : 1));
-    const size_t o_g = take(sizeof(double) * 2 * NN);
     const size_t o_a = take(sizeof(double) * 2 * NN);
     const size_t o_c = take(sizeof(double) * 2 * (P + 1));
     const size_t o_rates = take(sizeof(double) * (P + 1));
     const size_t o_l1 = take(sizeof(double) * N);
-    const size_t o_cnt = take(sizeof(int) * N * (1 + 2 * (P > 0 ? P : 1)));
-    const size_t o_ells = take(sizeof(Ell) * 2 * (P > 0 ? P : 1));
+    const size_t o_cnt = take(sizeof(int) * (size_t)N * nsets);
+    const size_t o_ells = take(sizeof(Ell) * nsets);
     const size_t o_rowcnt = take(sizeof(int64_t) * (M + 1));
     const size_t o_dcnt = take(sizeof(int64_t) * (M + 1));
     const size_t o_carry = take(sizeof(int64_t) * (M + 1));
-    const size_t o_ovf = take(sizeof(int) * 2);
+    const size_t o_scan = take(sizeof(int64_t) * scan_scratch(M));
+    // read back: scan totals (diagonal entries, carrying columns; stored entries, -), overflow flags, ELL widths
+    const size_t o_info = take(sizeof(int64_t) * 4 + sizeof(int) * (2 + nsets));
     const size_t fixed = off;
     int rc = lb_ws_reserve(c, fixed);
     if (rc) return rc;
     char* ws = (char*)c->ws;
     double* Hd = (double*)(ws + o_h);
     double* Ld = (double*)(ws + o_l);
-    double* G = (double*)(ws + o_g);
     double* A = (double*)(ws + o_a);
     double* cvec = (double*)(ws + o_c);
     double* drates = (double*)(ws + o_rates);
     double* l1 = (double*)(ws + o_l1);
     int* cnts = (int*)(ws + o_cnt);
+    Ell* dells = (Ell*)(ws + o_ells);
     int64_t* rowcnt = (int64_t*)(ws + o_rowcnt);
     int64_t* dcnt = (int64_t*)(ws + o_dcnt);
-    int64_t* carryflag = (int64_t*)(ws + o_carry);
-    int* ovf = (int*)(ws + o_ovf);
+    int64_t* carry = (int64_t*)(ws + o_carry);
+    int64_t* scratch = (int64_t*)(ws + o_scan);
+    int64_t* tot = (int64_t*)(ws + o_info);
+    int* ovf = (int*)(tot + 4);
+    int* wmax = ovf + 2;
+    const size_t info_bytes = sizeof(int64_t) * 4 + sizeof(int) * (2 + nsets);
 
-    // rates to the device
-    rc = lb_host_reserve(c, sizeof(double) * (P + 1));
+    // pinned staging: [info read back | rates | ELL descriptors]
+    const size_t h_rates = lb_align(info_bytes, 64), h_ells = h_rates + lb_align(sizeof(double) * (P + 1), 64);
+    rc = lb_host_reserve(c, h_ells + sizeof(Ell) * nsets);
     if (rc) return rc;
-    LB_HIP(hipStreamSynchronize(s));
-    for (int p = 0; p < P; ++p) ((double*)c->host)[p] = rates[p];
-    if (P > 0) LB_HIP(hipMemcpyAsync(drates, c->host, sizeof(double) * P, hipMemcpyHostToDevice, s));
-    LB_HIP(hipMemsetAsync(ovf, 0, sizeof(int) * 2, s));
+    LB_HIP(hipStreamSynchronize(s));  // an earlier copy on this stream may still read the staging buffer
+    char* host = (char*)c->host;
+    const int64_t* htot = (const int64_t*)host;
+    const int* hovf = (const int*)(htot + 4);
+    const int* hw = hovf + 2;
+    for (int p = 0; p < P; ++p) ((double*)(host + h_rates))[p] = rates[p];
+    if (P > 0) LB_HIP(hipMemcpyAsync(drates, host + h_rates, sizeof(double) * P, hipMemcpyHostToDevice, s));
+    LB_HIP(hipMemsetAsync(tot, 0, info_bytes, s));
 
     // dense set-up
-    hipLaunchKernelGGL(k_densify, dim3(lb_blocks(N, 64)), dim3(64), 0, s, N, H->rowptr, H->col, H->val, Hd);
+    hipLaunchKernelGGL(k_densify, dim3(N), dim3(64), 0, s, N, H->rowptr, H->col, H->val, Hd);
     LB_CHECK_LAUNCH();
     for (int p = 0; p < P; ++p) {
-        hipLaunchKernelGGL(k_densify, dim3(lb_blocks(N, 64)), dim3(64), 0, s, N, L[p].rowptr, L[p].col, L[p].val,
-                           Ld + 2 * NN * p);
+        hipLaunchKernelGGL(k_densify, dim3(N), dim3(64), 0, s, N, L[p].rowptr, L[p].col, L[p].val, Ld + 2 * NN * p);
         LB_CHECK_LAUNCH();
     }
     if (P > 0) {
@@ -650,42 +823,27 @@ static int sparse_body(lb_ctx* c, int N, const lb_csr_c128* H, int P, const doub
                            (const double*)cvec);
         LB_CHECK_LAUNCH();
     }
-    hipLaunchKernelGGL(k_heff_g_a, dim3(lb_blocks(NN, 256)), dim3(256), 0, s, N, P, (const double*)drates,
-                       (const double*)cvec, (const double*)Ld, Hd, G, A);
-    LB_CHECK_LAUNCH();
-    hipLaunchKernelGGL(k_l1diag, dim3(lb_blocks(N, 64)), dim3(64), 0, s, N, P, (const double*)drates,
-                       (const double*)A, (const double*)Ld, l1);
+    hipLaunchKernelGGL(k_heff_a, dim3(N), dim3(256), (sizeof(double2) + sizeof(int)) * N, s, N, P,
+                       (const double*)drates,
+                       (const double*)cvec, (const double*)Ld, (const double*)Hd, A);
     LB_CHECK_LAUNCH();
 
-    // ELL widths: A by column, L0_p by row and by column
-    int* cntA = cnts;
-    hipLaunchKernelGGL(k_ell_count, dim3(lb_blocks(N, 64)), dim3(64), 0, s, N, (const double*)A, 1, cntA);
+    // ELL lists: A by column, L0_p by row and by column
+    const dim3 egrid(lb_blocks(N, 4), nsets);
+    hipLaunchKernelGGL(k_ell_count, egrid, dim3(256), 0, s, N, (const double*)A, (const double*)Ld, cnts);
     LB_CHECK_LAUNCH();
-    for (int p = 0; p < P; ++p) {
-        hipLaunchKernelGGL(k_ell_count, dim3(lb_blocks(N, 64)), dim3(64), 0, s, N, (const double*)(Ld + 2 * NN * p), 0,
-                           cnts + N * (1 + 2 * p));
-        LB_CHECK_LAUNCH();
-        hipLaunchKernelGGL(k_ell_count, dim3(lb_blocks(N, 64)), dim3(64), 0, s, N, (const double*)(Ld + 2 * NN * p), 1,
-                           cnts + N * (2 + 2 * p));
-        LB_CHECK_LAUNCH();
-    }
-    int WA = 0;
-    std::vector<int> WLr(P), WLc(P);
-    rc = max_of(c, cntA, N, &WA);
-    if (rc) return rc;
-    for (int p = 0; p < P; ++p) {
-        rc = max_of(c, cnts + N * (1 + 2 * p), N, &WLr[p]);
-        if (rc) return rc;
-        rc = max_of(c, cnts + N * (2 + 2 * p), N, &WLc[p]);
-        if (rc) return rc;
-    }
-    int bound = 4 * WA;
-    for (int p = 0; p < P; ++p) bound += 2 * WLr[p] * WLr[p];
+    hipLaunchKernelGGL(k_ell_width, dim3(nsets), dim3(64), 0, s, N, (const int*)cnts, wmax);
+    LB_CHECK_LAUNCH();
+    LB_HIP(hipMemcpyAsync(host, tot, info_bytes, hipMemcpyDeviceToHost, s));
+    LB_HIP(hipStreamSynchronize(s));
+    // 64-bit: a width squared may exceed int
+    int64_t bound = 4 * (int64_t)hw[0];
+    for (int p = 0; p < P; ++p) bound += 2 * (int64_t)hw[1 + 2 * p] * hw[1 + 2 * p];
     if (bound > kMaxRowEntries)
         return lb_fail(LB_ERR_UNSUPPORTED,
-                       "sparse path needs bounded degrees: up to %d entries per row of L^+(F_s) (limit %d); use "
+                       "sparse path needs bounded degrees: up to %lld entries per row of L^+(F_s) (limit %d); use "
                        "lindblad_prepare for dense operators",
-                       bound, kMaxRowEntries);
+                       (long long)bound, kMaxRowEntries);
     // ELL storage after the fixed part
     size_t o2 = fixed;
     auto take2 = [&](size_t bytes) {
@@ -693,46 +851,24 @@ static int sparse_body(lb_ctx* c, int N, const lb_csr_c128* H, int P, const doub
         o2 = lb_align(o2 + bytes, 256);
         return o;
     };
-    const size_t o_Ai = take2(sizeof(int) * (size_t)N * std::max(WA, 1));
-    const size_t o_Av = take2(sizeof(double) * 2 * (size_t)N * std::max(WA, 1));
-    std::vector<size_t> o_Lri(P), o_Lrv(P), o_Lci(P), o_Lcv(P);
-    for (int p = 0; p < P; ++p) {
-        o_Lri[p] = take2(sizeof(int) * (size_t)N * std::max(WLr[p], 1));
-        o_Lrv[p] = take2(sizeof(double) * 2 * (size_t)N * std::max(WLr[p], 1));
-        o_Lci[p] = take2(sizeof(int) * (size_t)N * std::max(WLc[p], 1));
-        o_Lcv[p] = take2(sizeof(double) * 2 * (size_t)N * std::max(WLc[p], 1));
+    Ell* hl = (Ell*)(host + h_ells);
+    for (int i = 0; i < nsets; ++i) {
+        const int W = std::max(hw[i], 1);
+        const size_t o_i = take2(sizeof(int) * (size_t)N * W);
+        const size_t o_v = take2(sizeof(double) * 2 * (size_t)N * W);
+        hl[i] = Ell{(int*)(ws + o_i), (double*)(ws + o_v), cnts + (size_t)N * i, W};
     }
     const size_t before_lists = o2;
     if (o2 > c->ws_bytes) {
         *want = o2 + (o2 >> 2);
         return 1;
     }
-    hipLaunchKernelGGL(k_ell_fill, dim3(lb_blocks(N, 64)), dim3(64), 0, s, N, (const double*)A, 1, std::max(WA, 1),
-                       (int*)(ws + o_Ai), (double*)(ws + o_Av));
+    LB_HIP(hipMemcpyAsync(dells, hl, sizeof(Ell) * nsets, hipMemcpyHostToDevice, s));
+    hipLaunchKernelGGL(k_ell_fill, egrid, dim3(256), 0, s, N, (const double*)A, (const double*)Ld, (const Ell*)dells);
     LB_CHECK_LAUNCH();
-    std::vector<Ell> hl(2 * std::max(P, 1));
-    for (int p = 0; p < P; ++p) {
-        hipLaunchKernelGGL(k_ell_fill, dim3(lb_blocks(N, 64)), dim3(64), 0, s, N, (const double*)(Ld + 2 * NN * p), 0,
-                           std::max(WLr[p], 1), (int*)(ws + o_Lri[p]), (double*)(ws + o_Lrv[p]));
-        LB_CHECK_LAUNCH();
-        hipLaunchKernelGGL(k_ell_fill, dim3(lb_blocks(N, 64)), dim3(64), 0, s, N, (const double*)(Ld + 2 * NN * p), 1,
-                           std::max(WLc[p], 1), (int*)(ws + o_Lci[p]), (double*)(ws + o_Lcv[p]));
-        LB_CHECK_LAUNCH();
-        hl[p] = Ell{(const int*)(ws + o_Lri[p]), (const double*)(ws + o_Lrv[p]), cnts + N * (1 + 2 * p),
-                    std::max(WLr[p], 1)};
-        hl[P + p] = Ell{(const int*)(ws + o_Lci[p]), (const double*)(ws + o_Lcv[p]), cnts + N * (2 + 2 * p),
-                        std::max(WLc[p], 1)};
-    }
-    Ell* dells = (Ell*)(ws + o_ells);
-    if (P > 0) {
-        rc = lb_host_reserve(c, sizeof(Ell) * 2 * P);
-        if (rc) return rc;
-        LB_HIP(hipStreamSynchronize(s));
-        memcpy(c->host, hl.data(), sizeof(Ell) * 2 * P);
-        LB_HIP(hipMemcpyAsync(dells, c->host, sizeof(Ell) * 2 * P, hipMemcpyHostToDevice, s));
-        LB_HIP(hipStreamSynchronize(s));
-    }
-    const Ell Acol{(const int*)(ws + o_Ai), (const double*)(ws + o_Av), cntA, std::max(WA, 1)};
+    hipLaunchKernelGGL(k_l1diag, dim3(lb_blocks(N, 64)), dim3(64), 0, s, N, P, (const double*)drates,
+                       (const double*)A, (const Ell*)(dells + 1), l1);
+    LB_CHECK_LAUNCH();
 
     // carrying lists: diag(L(F_n)) for every column n
     DiagArgs da;
@@ -741,8 +877,7 @@ static int sparse_body(lb_ctx* c, int N, const lb_csr_c128* H, int P, const doub
     da.Pp = Pp;
     da.M = M;
     da.A = A;
-    da.Lcol = dells + P;
-    da.Lrow = dells;
+    da.ells = dells;
     da.rates = drates;
     da.cnt = dcnt;
     da.off = dcnt;
@@ -750,24 +885,36 @@ static int sparse_body(lb_ctx* c, int N, const lb_csr_c128* H, int P, const doub
     da.val = nullptr;
     hipLaunchKernelGGL(k_diag_pairs, dim3(lb_blocks(2 * Pp, 128)), dim3(128), 0, s, da, 0, ovf + 1);
     LB_CHECK_LAUNCH();
-    hipLaunchKernelGGL(k_diag_dcols, dim3(lb_blocks(N - 1, 64)), dim3(64), 0, s, da, 0);
+    hipLaunchKernelGGL(k_diag_dcols, dim3(lb_blocks(N - 1, 4)), dim3(256), 0, s, da, 0);
     LB_CHECK_LAUNCH();
-    hipLaunchKernelGGL(k_mark_carry, dim3(lb_blocks(M, 256)), dim3(256), 0, s, M, (const int64_t*)dcnt, carryflag);
+    rc = scan_counts(s, M, dcnt, dcnt, carry, scratch, tot);
+    if (rc) return rc;
+
+    // row counts of the pair rows (they do not need the lists)
+    PairArgs pa;
+    pa.N = N;
+    pa.P = P;
+    pa.bound = std::max((int)bound, 1);
+    pa.Pp = Pp;
+    pa.ells = dells;
+    pa.rates = drates;
+    pa.cnt = rowcnt;
+    pa.rowptr = rowptr;
+    pa.col = col;
+    pa.val = val;
+    pa.K = K;
+    pa.overflow = ovf;
+    void (*pair_rows)(PairArgs, int) = bound <= 16   ? k_pair_rows<16>
+                                         : bound <= 24 ? k_pair_rows<24>
+                                         : bound <= 40 ? k_pair_rows<40>
+                                                       : k_pair_rows<64>;
+    const size_t pair_lds = (size_t)64 * pa.bound * (sizeof(double2) + sizeof(uint32_t));
+    hipLaunchKernelGGL(pair_rows, dim3(lb_blocks(2 * Pp, 64)), dim3(64), pair_lds, s, pa, 0);
     LB_CHECK_LAUNCH();
-    int64_t dtotal = 0;
-    rc = host_scan(c, dcnt, M, &dtotal);
-    if (rc) return rc;
-    // compacted carrying-column list (host: the flags are read back and compacted)
-    rc = lb_host_reserve(c, sizeof(int64_t) * (M + 1));
-    if (rc) return rc;
-    LB_HIP(hipMemcpyAsync(c->host, carryflag, sizeof(int64_t) * M, hipMemcpyDeviceToHost, s));
+
+    LB_HIP(hipMemcpyAsync(host, tot, info_bytes, hipMemcpyDeviceToHost, s));
     LB_HIP(hipStreamSynchronize(s));
-    int64_t ncarry = 0;
-    {
-        int64_t* h = (int64_t*)c->host;
-        for (int64_t i = 0; i < M; ++i)
-            if (h[i]) h[ncarry++] = i;
-    }
+    const int64_t dtotal = htot[0], ncarry = htot[1];
     size_t o3 = before_lists;
     auto take3 = [&](size_t bytes) {
         size_t o = o3;
@@ -776,47 +923,32 @@ static int sparse_body(lb_ctx* c, int N, const lb_csr_c128* H, int P, const doub
     };
     const size_t o_pos = take3(sizeof(int) * (size_t)std::max<int64_t>(dtotal, 1));
     const size_t o_dval = take3(sizeof(double) * 2 * (size_t)std::max<int64_t>(dtotal, 1));
-    const size_t o_clist = take3(sizeof(int64_t) * (size_t)std::max<int64_t>(ncarry, 1));
     const size_t o_pref = take3(sizeof(double) * (size_t)std::max<int64_t>(dtotal, 1));
     if (o3 > c->ws_bytes) {
         *want = o3 + (o3 >> 3);
         return 1;
     }
-    LB_HIP(hipMemcpyAsync(ws + o_clist, c->host, sizeof(int64_t) * std::max<int64_t>(ncarry, 1),
-                          hipMemcpyHostToDevice, s));
     da.pos = (int*)(ws + o_pos);
     da.val = (double*)(ws + o_dval);
     hipLaunchKernelGGL(k_diag_pairs, dim3(lb_blocks(2 * Pp, 128)), dim3(128), 0, s, da, 1, ovf + 1);
     LB_CHECK_LAUNCH();
-    hipLaunchKernelGGL(k_diag_dcols, dim3(lb_blocks(N - 1, 64)), dim3(64), 0, s, da, 1);
+    hipLaunchKernelGGL(k_diag_dcols, dim3(lb_blocks(N - 1, 4)), dim3(256), 0, s, da, 1);
     LB_CHECK_LAUNCH();
-    if (ncarry > 0) {
-        hipLaunchKernelGGL(k_diag_prefix, dim3(lb_blocks(ncarry, 64)), dim3(64), 0, s, ncarry,
-                           (const int64_t*)(ws + o_clist), (const int64_t*)dcnt, (const double*)da.val,
+    {
+        // every diagonal generator's column carries (its list starts at position 0), after those of the pairs
+        const int64_t npair = ncarry - (N - 1);
+        const unsigned pb = lb_blocks(npair, 64);
+        hipLaunchKernelGGL(k_diag_prefix, dim3(pb + (unsigned)(N - 1)), dim3(64), 0, s, npair, ncarry, pb,
+                           (const int64_t*)carry, (const int64_t*)dcnt, (const double*)da.val,
                            (double*)(ws + o_pref));
         LB_CHECK_LAUNCH();
     }
-
-    // row counts
-    PairArgs pa;
-    pa.N = N;
-    pa.P = P;
-    pa.Pp = Pp;
-    pa.Acol = Acol;
-    pa.Lrow = dells;
-    pa.rates = drates;
-    pa.cnt = rowcnt;
-    pa.rowptr = rowptr;
-    pa.col = col;
-    pa.val = val;
-    pa.K = K;
-    pa.overflow = ovf;
     DRowArgs dr;
     dr.N = N;
     dr.Pp = Pp;
     dr.M = M;
     dr.ncarry = ncarry;
-    dr.carry = (const int64_t*)(ws + o_clist);
+    dr.carry = carry;
     dr.off = dcnt;
     dr.pos = da.pos;
     dr.val = da.val;
@@ -827,49 +959,25 @@ static int sparse_body(lb_ctx* c, int N, const lb_csr_c128* H, int P, const doub
     dr.col = col;
     dr.qv = val;
     dr.K = K;
-    if (Pp > 0) {
-        hipLaunchKernelGGL(k_pair_rows, dim3(lb_blocks(2 * Pp, 64)), dim3(64), 0, s, pa, 0);
-        LB_CHECK_LAUNCH();
-    }
-    hipLaunchKernelGGL(k_drows_sparse, dim3(lb_blocks((int64_t)(N - 1) * 64, 256)), dim3(256), 0, s, dr, 0);
+    hipLaunchKernelGGL(k_drows_sparse, dim3(N - 1), dim3(64 * kDrowWaves), 0, s, dr, 0);
     LB_CHECK_LAUNCH();
-    int hovf[2] = {0, 0};
-    LB_HIP(hipMemcpyAsync(hovf, ovf, sizeof(int) * 2, hipMemcpyDeviceToHost, s));
+    rc = scan_counts(s, M, rowcnt, rowcnt, nullptr, scratch, tot + 2);
+    if (rc) return rc;
+    LB_HIP(hipMemcpyAsync(host, tot, info_bytes, hipMemcpyDeviceToHost, s));
     LB_HIP(hipStreamSynchronize(s));
     if (hovf[0] || hovf[1]) return lb_fail(LB_ERR_UNSUPPORTED, "sparse row buffer overflow (degrees too large)");
-    int64_t total = 0;
+    const int64_t total = htot[2];
     if (!fill) {
-        rc = host_scan(c, rowcnt, M, &total);
-        if (rc) return rc;
         *nnz = total;
         return LB_OK;
     }
-    // fill: rowptr from the counts
-    rc = lb_host_reserve(c, sizeof(int64_t) * (M + 1));
-    if (rc) return rc;
-    {
-        int64_t* h = (int64_t*)c->host;
-        LB_HIP(hipMemcpyAsync(h, rowcnt, sizeof(int64_t) * M, hipMemcpyDeviceToHost, s));
-        LB_HIP(hipStreamSynchronize(s));
-        int64_t run = 0;
-        for (int64_t i = 0; i < M; ++i) {
-            const int64_t v = h[i];
-            h[i] = run;
-            run += v;
-        }
-        h[M] = run;
-        total = run;
-        if (total != *nnz)
-            return lb_fail(LB_ERR_INVALID_ARG, "nnz=%lld does not match the count phase (%lld)", (long long)*nnz,
-                           (long long)total);
-        LB_HIP(hipMemcpyAsync(rowptr, h, sizeof(int64_t) * (M + 1), hipMemcpyHostToDevice, s));
-        LB_HIP(hipStreamSynchronize(s));
-    }
-    if (Pp > 0) {
-        hipLaunchKernelGGL(k_pair_rows, dim3(lb_blocks(2 * Pp, 64)), dim3(64), 0, s, pa, 1);
-        LB_CHECK_LAUNCH();
-    }
-    hipLaunchKernelGGL(k_drows_sparse, dim3(lb_blocks((int64_t)(N - 1) * 64, 256)), dim3(256), 0, s, dr, 1);
+    if (total != *nnz)
+        return lb_fail(LB_ERR_INVALID_ARG, "nnz=%lld does not match the count phase (%lld)", (long long)*nnz,
+                       (long long)total);
+    LB_HIP(hipMemcpyAsync(rowptr, rowcnt, sizeof(int64_t) * (M + 1), hipMemcpyDeviceToDevice, s));
+    hipLaunchKernelGGL(pair_rows, dim3(lb_blocks(2 * Pp, 64)), dim3(64), pair_lds, s, pa, 1);
+    LB_CHECK_LAUNCH();
+    hipLaunchKernelGGL(k_drows_sparse, dim3(N - 1), dim3(64 * kDrowWaves), sizeof(double) * N, s, dr, 1);
     LB_CHECK_LAUNCH();
     return LB_OK;
 }
