@@ -791,8 +791,8 @@ __device__ __forceinline__ void rk4_update(int stage, double h, double k, double
         Acc[i] = acc + 2.0 * k;
         x = v + h * k;
     } else {
-        x = v + h / 6.0 * (acc + k);
-        V[i] = x;
+        V[i] = v + h / 6.0 * (acc + k);
+        return;
     }
     Xout[i] = x;
 }
@@ -802,7 +802,7 @@ struct SellStage {
     int B;
     const double* K;
     double* V;
-    double* W;  // [accumulator | x ping | x pong], M*B each
+    double* W;  // [accumulator | x ping | x pong], M*B each; stage 1 reads x from V, stage 4 writes only V
 };
 
 // DRIVE: k = (Q0 x) + eps (Q1 x) + K, the two sums formed separately.
@@ -812,21 +812,24 @@ __global__ __launch_bounds__(256) void k_sell_stage(SellMat a, SellStage st, int
     const int64_t M = a.M;
     const int64_t n = M * st.B;
     double* Acc = st.W;
-    const double* Xin = (stage & 1) ? st.W + n : st.W + 2 * n;
+    const double* Xin = stage == 1 ? st.V : (stage & 1) ? st.W + n : st.W + 2 * n;
     double* Xout = (stage & 1) ? st.W + 2 * n : st.W + n;
     const int wk = sell_work(a);
     if (wk < 0) return;
     if (wk < a.nlong) {
-        const int64_t row = a.longrows[wk];
+        const LongRowPtr lr = (LongRowPtr)(a.longrows + wk);
+        const int64_t row = lr->row;
+        const double kr = st.K[row];
         for (int b = 0; b < st.B; ++b) {
+            const int64_t i = (int64_t)b * M + row;
+            const double v = st.V[i], acc = stage > 1 ? Acc[i] : 0.0;
             double q0, q1;
-            block_row_dots<DRIVE>(a, row, Xin + (int64_t)b * M, q0, q1);
+            block_row_dots<DRIVE>(a, lr, Xin + (int64_t)b * M, q0, q1);
             if (threadIdx.x == 0) {
-                const int64_t i = (int64_t)b * M + row;
                 double k = q0;
                 if (DRIVE) k += eps * q1;
-                k += st.K[row];
-                rk4_update(stage, h, k, st.V[i], stage > 1 ? Acc[i] : 0.0, i, st.V, Acc, Xout);
+                k += kr;
+                rk4_update(stage, h, k, v, acc, i, st.V, Acc, Xout);
             }
         }
         return;
@@ -836,20 +839,8 @@ __global__ __launch_bounds__(256) void k_sell_stage(SellMat a, SellStage st, int
     if (sl >= a.S) return;
     const int lane = threadIdx.x & (kSlice - 1);
     const int64_t r = (int64_t)sl * kSlice + lane;
-    const bool mine = r < M && !((a.lmask[sl] >> lane) & 1);
-    const int64_t o0 = a.off0[sl];
-    const int w0 = (int)((a.off0[sl + 1] - o0) / kSlice);
-    const int* c0 = a.scol0 + o0 + lane;
-    const double* v0 = a.sval0 + o0 + lane;
-    int w1 = 0;
-    const int* c1 = nullptr;
-    const double* v1 = nullptr;
-    if (DRIVE) {
-        const int64_t o1 = a.off1[sl];
-        w1 = (int)((a.off1[sl + 1] - o1) / kSlice);
-        c1 = a.scol1 + o1 + lane;
-        v1 = a.sval1 + o1 + lane;
-    }
+    const SellHeadPtr head = (SellHeadPtr)(a.head0 + sl);
+    const bool mine = r < M && !((head->lmask >> lane) & 1);
     const double kr = mine ? st.K[r] : 0.0;
     for (int b0 = 0; b0 < st.B; b0 += SB) {
         const int nb = min(SB, st.B - b0);
@@ -864,8 +855,8 @@ __global__ __launch_bounds__(256) void k_sell_stage(SellMat a, SellStage st, int
             }
         }
         const double* xb = Xin + (int64_t)b0 * M;
-        sell_row<SB>(c0, v0, w0, xb, M, nb, acc);
-        if (DRIVE) sell_row<SB>(c1, v1, w1, xb, M, nb, accd);
+        sell_row<SB>(head, a.scol0, a.sval0, lane, xb, M, nb, acc);
+        if (DRIVE) sell_row<SB>((SellHeadPtr)(a.head1 + sl), a.scol1, a.sval1, lane, xb, M, nb, accd);
 #pragma unroll
         for (int j = 0; j < SB; ++j)
             if (j < nb && mine) {
@@ -874,11 +865,6 @@ __global__ __launch_bounds__(256) void k_sell_stage(SellMat a, SellStage st, int
                 rk4_update(stage, h, k + kr, vv[j], aa[j], (int64_t)(b0 + j) * M + r, st.V, Acc, Xout);
             }
     }
-}
-
-__global__ void k_copy(const double* src, double* dst, int64_t n) {
-    const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (e < n) dst[e] = src[e];
 }
 
 __global__ void k_to_f32(const double* Q, float* Q32, int64_t n) {
@@ -1556,8 +1542,6 @@ static int csr_propagate(lb_ctx* c, int64_t M, const int64_t* rowptr, const int6
     int rc = sell_build(c, M, rowptr, col, val, rowptr1, col1, val1, sizeof(double) * 3 * (size_t)n, &m, &o_w);
     if (rc) return rc;
     double* W = (double*)((char*)c->ws + o_w);
-    hipLaunchKernelGGL(k_copy, dim3(lb_blocks(n, 256)), dim3(256), 0, s, (const double*)V, W + n, n);
-    LB_CHECK_LAUNCH();
     const SellStage st{B, K, V, W};
     const unsigned grid = (unsigned)m.nlong8 + 8u * (unsigned)m.per_xcd;
     typedef void (*stage_fn)(SellMat, SellStage, int, double, double);

@@ -12,23 +12,42 @@
 // rows coupled to them, ~N entries) are left out of the slices and take one
 // block of 256 threads each, with a fixed-order block reduction.
 //
+// In the pair ordering most entries k of a slice have consecutive columns (row
+// (u, v) couples to (u, v + d), (u + d, v), ... with v one more per lane): those
+// groups keep one column for the slice, the lanes' columns follow from it, and
+// the per-entry columns are neither written nor read. 8 bytes per entry instead
+// of 12 (94 % of the groups of the N = 1000 rocked dimer).
+//
 // A second matrix (the drive term Q1 of a time-dependent system) can be
 // regrouped alongside; its long rows are those of the first matrix.
 #pragma once
 
 #include "lb_internal.h"
+#include "scan.h"
+
+#include <algorithm>
 
 namespace {
 
 constexpr int kLongRow = 32;
 constexpr int kSlice = 64;
-constexpr int kChunk = 4;  // slice entries per lane loaded before their products
+// Slice entries per lane loaded before their products. 6, 8 and 9 measured 39.4,
+// 39.9 and 39.6 us a stage on the rocked dimer (18 entries a row), 21.5, 21.0 and
+// 21.0 us on the static one (7 entries).
+constexpr int kChunk = 9;
+
+// A row left out of the slices: its entries in the CSR arrays of the matrix and
+// of the second one.
+struct LongRow {
+    int64_t row, e0, e1, f0, f1;
+};
+typedef const LongRow __attribute__((address_space(4)))* LongRowPtr;
 
 // Slice widths (as 64 * entries, later scanned into offsets), the long-row
 // mask of each slice and the list of long rows. One wavefront per slice.
 __global__ __launch_bounds__(256) void k_sell_widths(int64_t M, int64_t S, const int64_t* rowptr,
                                                      const int64_t* rowptr1, int64_t* off0, int64_t* off1,
-                                                     uint64_t* lmask, int* longrows, int* nlong) {
+                                                     uint64_t* lmask, LongRow* longrows, int* nlong) {
     const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const int64_t sl = r / kSlice;
     if (sl >= S) return;  // whole wavefronts
@@ -41,7 +60,14 @@ __global__ __launch_bounds__(256) void k_sell_widths(int64_t M, int64_t S, const
     if (lng) {
         len0 = 0;
         len1 = 0;
-        longrows[atomicAdd(nlong, 1)] = (int)r;
+        LongRow& lr = longrows[atomicAdd(nlong, 1)];
+        lr.row = r;
+        lr.e0 = rowptr[r];
+        lr.e1 = rowptr[r + 1];
+        if (rowptr1) {
+            lr.f0 = rowptr1[r];
+            lr.f1 = rowptr1[r + 1];
+        }
     }
     for (int o = kSlice / 2; o > 0; o >>= 1) {
         len0 = max(len0, (int64_t)__shfl_xor(len0, o, kSlice));
@@ -55,91 +81,122 @@ __global__ __launch_bounds__(256) void k_sell_widths(int64_t M, int64_t S, const
     }
 }
 
-// Exclusive scan of n sizes in place, total in a[n]; one block of 1024 threads.
-__device__ void block_scan_inplace(int64_t n, int64_t* a, int64_t* part) {
-    const int t = threadIdx.x;
-    const int64_t per = (n + 1023) / 1024;
-    const int64_t b0 = min(n, t * per), b1 = min(n, b0 + per);
-    int64_t sum = 0;
-    for (int64_t i = b0; i < b1; ++i) sum += a[i];
-    part[t] = sum;
-    __syncthreads();
-    if (t == 0) {
-        int64_t run = 0;
-        for (int i = 0; i < 1024; ++i) {
-            const int64_t v = part[i];
-            part[i] = run;
-            run += v;
-        }
-        a[n] = run;
-    }
-    __syncthreads();
-    int64_t run = part[t];
-    for (int64_t i = b0; i < b1; ++i) {
-        const int64_t v = a[i];
-        a[i] = run;
-        run += v;
-    }
-    __syncthreads();
-}
+// What a wavefront needs to know about its slice, read with scalar loads in one
+// go: every dependent read before the loads of values and x costs the stage a
+// memory latency (7 entries per row leave only about three of them).
+struct SellHead {
+    int64_t off;     // first value of the slice
+    uint64_t lmask;  // lanes whose row is long
+    int64_t w;       // entries per row
+    int64_t unused;
+    // first lane's column of entry k if the lanes' columns are consecutive, else -1; from w on: 0.
+    // Not set where w > kLongRow (rows of the second matrix whose row in the first is short).
+    int base[(kLongRow + kChunk - 1) / kChunk * kChunk];
+};
 
-__global__ __launch_bounds__(1024) void k_sell_scan(int64_t S, int64_t* off0, int64_t* off1) {
-    __shared__ int64_t part[1024];
-    block_scan_inplace(S, off0, part);
-    if (off1) block_scan_inplace(S, off1, part);
-}
+// One matrix of one slice into the slice layout, by a wavefront: the rows' runs
+// of CSR entries are read 8 lanes to a row, turned in LDS (row stride odd) and
+// written entry by entry. Rows past M and long rows are all padding. An entry
+// that all 64 rows have, at consecutive columns, gets the first column in the
+// slice's header and no per-lane columns.
+constexpr int kSellLds = kSlice * (kLongRow + 1);
 
-// One matrix into the slice layout: thread per row (rows past M and long rows
-// are all padding).
 __device__ __forceinline__ void sell_put(int64_t r, int64_t M, int64_t sl, bool lng, const int64_t* rowptr,
                                          const int64_t* col, const double* val, const int64_t* off, int* scol,
-                                         double* sval) {
-    const int64_t o = off[sl], w = (off[sl + 1] - o) / kSlice;
-    int64_t e0 = 0, len = 0;
+                                         double* sval, uint64_t lmask, SellHead* head, double* lv, int* lc) {
+    const int64_t o = off[sl];
+    const int w = (int)((off[sl + 1] - o) / kSlice);
+    const int lane = threadIdx.x, stride = w | 1;
+    int64_t e0 = 0;
+    int len = 0;
     if (r < M && !lng) {
         e0 = rowptr[r];
-        len = rowptr[r + 1] - e0;
+        len = (int)(rowptr[r + 1] - e0);
     }
     const int pad = (int)(r < M ? r : M - 1);
-    const int lane = (int)(r & (kSlice - 1));
-    for (int64_t k = 0; k < w; ++k) {
-        const int64_t d = o + k * kSlice + lane;
-        scol[d] = k < len ? (int)col[e0 + k] : pad;
-        sval[d] = k < len ? val[e0 + k] : 0.0;
+    if (lane == 0) {
+        head[sl].off = o;
+        head[sl].lmask = lmask;
+        head[sl].w = w;
     }
+    if (w > kLongRow) {  // wider than the header and the LDS tile: straight from the rows, all columns kept
+        for (int k = 0; k < w; ++k) {
+            const int64_t d = o + (int64_t)k * kSlice + lane;
+            scol[d] = k < len ? (int)col[e0 + k] : pad;
+            sval[d] = k < len ? val[e0 + k] : 0.0;
+        }
+        return;
+    }
+    for (int r0 = 0; r0 < kSlice; r0 += 8) {
+        const int row = r0 + (lane >> 3);
+        const int64_t re = __shfl(e0, row, kSlice);
+        const int rl = __shfl(len, row, kSlice);
+        int64_t c[kLongRow / 8];
+        double v[kLongRow / 8];
+#pragma unroll
+        for (int u = 0; u < kLongRow / 8; ++u) {
+            const int k = (lane & 7) + 8 * u;
+            if (k < rl) {
+                c[u] = col[re + k];
+                v[u] = val[re + k];
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < kLongRow / 8; ++u) {
+            const int k = (lane & 7) + 8 * u;
+            if (k < rl) {
+                lc[row * stride + k] = (int)c[u];
+                lv[row * stride + k] = v[u];
+            }
+        }
+    }
+    __syncthreads();
+    for (int k = 0; k < w; ++k) {
+        const bool have = k < len;
+        const int c = have ? lc[lane * stride + k] : pad;
+        const int c0 = __builtin_amdgcn_readfirstlane(c);
+        const bool run = __ballot(have && c == c0 + lane) == ~0ull;
+        const int64_t d = o + (int64_t)k * kSlice + lane;
+        sval[d] = have ? lv[lane * stride + k] : 0.0;
+        if (!run) scol[d] = c;
+        if (lane == 0) head[sl].base[k] = run ? c0 : -1;
+    }
+    if (lane >= w && lane < (int)(sizeof(head->base) / sizeof(int))) head[sl].base[lane] = 0;
+    __syncthreads();
 }
 
-__global__ __launch_bounds__(256) void k_sell_fill(int64_t M, int64_t S, const uint64_t* lmask, const int64_t* rowptr,
-                                                   const int64_t* col, const double* val, const int64_t* off0,
-                                                   int* scol0, double* sval0, const int64_t* rowptr1,
-                                                   const int64_t* col1, const double* val1, const int64_t* off1,
-                                                   int* scol1, double* sval1) {
-    const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int64_t sl = r / kSlice;
-    if (sl >= S) return;
-    const bool lng = (lmask[sl] >> (r & (kSlice - 1))) & 1;
-    sell_put(r, M, sl, lng, rowptr, col, val, off0, scol0, sval0);
-    if (rowptr1) sell_put(r, M, sl, lng, rowptr1, col1, val1, off1, scol1, sval1);
+// One wavefront per slice (with a thread per row reading its run of entries
+// directly, N = 1000 rocked took 505 us; this 190).
+__global__ __launch_bounds__(64) void k_sell_fill(int64_t M, const uint64_t* lmask, const int64_t* rowptr,
+                                                  const int64_t* col, const double* val, const int64_t* off0,
+                                                  int* scol0, double* sval0, SellHead* head0, const int64_t* rowptr1,
+                                                  const int64_t* col1, const double* val1, const int64_t* off1,
+                                                  int* scol1, double* sval1, SellHead* head1) {
+    __shared__ double lv[kSellLds];
+    __shared__ int lc[kSellLds];
+    const int64_t sl = blockIdx.x;
+    const int64_t r = sl * kSlice + threadIdx.x;
+    const uint64_t lm = lmask[sl];
+    const bool lng = (lm >> threadIdx.x) & 1;
+    sell_put(r, M, sl, lng, rowptr, col, val, off0, scol0, sval0, lm, head0, lv, lc);
+    if (rowptr1) sell_put(r, M, sl, lng, rowptr1, col1, val1, off1, scol1, sval1, lm, head1, lv, lc);
 }
 
 // A matrix (and optionally a second one) in the slice layout, with the CSR it
 // came from (read by the long rows).
 struct SellMat {
     int64_t M, S;
-    const int64_t* rowptr;
-    const int64_t* col;
+    const int64_t* col;  // CSR entries, for the long rows
     const double* val;
-    const int64_t* rowptr1;
     const int64_t* col1;
     const double* val1;
-    const int64_t* off0;  // slice offsets, S + 1 each
-    const int* scol0;
+    const SellHead* head0;
+    const int* scol0;  // columns, of the entries without a base
     const double* sval0;
-    const int64_t* off1;
+    const SellHead* head1;
     const int* scol1;
     const double* sval1;
-    const uint64_t* lmask;  // per slice: lanes whose row is long
-    const int* longrows;
+    const LongRow* longrows;
     int nlong;
     int nlong8;   // long-row blocks padded to a multiple of 8
     int per_xcd;  // slice groups (of four slices) per XCD; launch nlong8 + 8 * per_xcd blocks
@@ -164,49 +221,97 @@ __device__ __forceinline__ int sell_work(const SellMat& m) {
     return g < m.ngroups ? m.nlong + g : -1;
 }
 
-// acc[j] += sum over slice entries [k, k + n) of value * x_j[column], in entry
-// order, for the first nb of SB states; FULL: n == kChunk.
-template <int SB, bool FULL>
-__device__ __forceinline__ void sell_chunk(const int* c0, const double* v0, int k, int n, const double* Xin,
-                                           int64_t M, int nb, double* acc) {
-    int cc[kChunk];
-    double vv[kChunk];
+typedef const SellHead __attribute__((address_space(4)))* SellHeadPtr;  // read through the scalar cache
+
+// acc[j] += sum over entries k .. k + n - 1 of value * x_j[column], in entry
+// order, for the first nb of SB states; base: the entries' header columns. The n
+// values (and x, or columns and then x) are loaded together before the products.
+template <int SB, int n>
+__device__ __forceinline__ void sell_chunk(const int* base, const double* v, const int* c, int lane,
+                                           const double* Xin, int64_t M, int nb, double* acc) {
+    double vv[n];
+    int cc[n], any = 0;
 #pragma unroll
-    for (int u = 0; u < kChunk; ++u)
-        if (FULL || u < n) {
-            cc[u] = c0[(int64_t)(k + u) * kSlice];
-            vv[u] = v0[(int64_t)(k + u) * kSlice];
-        }
+    for (int u = 0; u < n; ++u) {
+        vv[u] = v[u * kSlice];
+        cc[u] = base[u];
+        any |= cc[u];
+    }
+    if (any >= 0) {  // consecutive columns throughout: x is read as 512-byte runs
 #pragma unroll
-    for (int j = 0; j < SB; ++j)
-        if (j < nb) {
-            const double* x = Xin + (int64_t)j * M;
+        for (int j = 0; j < SB; ++j)
+            if (j < nb) {
+                const double* x = Xin + (int64_t)j * M;
+                double xx[n];
 #pragma unroll
-            for (int u = 0; u < kChunk; ++u)
-                if (FULL || u < n) acc[j] = fma(vv[u], x[cc[u]], acc[j]);
-        }
+                for (int u = 0; u < n; ++u) xx[u] = (x + cc[u])[lane];
+#pragma unroll
+                for (int u = 0; u < n; ++u) acc[j] = fma(vv[u], xx[u], acc[j]);
+            }
+    } else {
+#pragma unroll
+        for (int u = 0; u < n; ++u) cc[u] = cc[u] >= 0 ? cc[u] + lane : c[u * kSlice];
+#pragma unroll
+        for (int j = 0; j < SB; ++j)
+            if (j < nb) {
+                const double* x = Xin + (int64_t)j * M;
+                double xx[n];
+#pragma unroll
+                for (int u = 0; u < n; ++u) xx[u] = x[cc[u]];
+#pragma unroll
+                for (int u = 0; u < n; ++u) acc[j] = fma(vv[u], xx[u], acc[j]);
+            }
+    }
+}
+
+// The last r < n + 1 entries of a row as one chunk of exactly that many.
+template <int SB, int n>
+__device__ __forceinline__ void sell_rest(int r, const int* base, const double* v, const int* c, int lane,
+                                          const double* Xin, int64_t M, int nb, double* acc) {
+    if constexpr (n > 0) {
+        if (r == n) sell_chunk<SB, n>(base, v, c, lane, Xin, M, nb, acc);
+        else sell_rest<SB, n - 1>(r, base, v, c, lane, Xin, M, nb, acc);
+    }
 }
 
 template <int SB>
-__device__ __forceinline__ void sell_row(const int* c0, const double* v0, int w, const double* Xin, int64_t M,
-                                         int nb, double* acc) {
+__device__ __forceinline__ void sell_row(SellHeadPtr head, const int* scol, const double* sval, int lane,
+                                         const double* Xin, int64_t M, int nb, double* acc) {
+    const int64_t o = head->off;
+    const int w = (int)head->w;
+    const int* c = scol + o + lane;
+    const double* v = sval + o + lane;
+    if (w > kLongRow) {
+        const int none = -1;
+        for (int k = 0; k < w; ++k, c += kSlice, v += kSlice) sell_chunk<SB, 1>(&none, v, c, lane, Xin, M, nb, acc);
+        return;
+    }
     int k = 0;
-    for (; k + kChunk <= w; k += kChunk) sell_chunk<SB, true>(c0, v0, k, kChunk, Xin, M, nb, acc);
-    if (k < w) sell_chunk<SB, false>(c0, v0, k, w - k, Xin, M, nb, acc);
+    for (; k + kChunk <= w; k += kChunk, c += kChunk * kSlice, v += kChunk * kSlice) {
+        int base[kChunk];
+#pragma unroll
+        for (int u = 0; u < kChunk; ++u) base[u] = head->base[k + u];
+        sell_chunk<SB, kChunk>(base, v, c, lane, Xin, M, nb, acc);
+    }
+    if (k < w) {
+        int base[kChunk];
+#pragma unroll
+        for (int u = 0; u < kChunk; ++u) base[u] = head->base[k + u];
+        sell_rest<SB, kChunk - 1>(w - k, base, v, c, lane, Xin, M, nb, acc);
+    }
 }
-
 
 // Sums of one long row of the matrix (s0) and of the second matrix (s1, when
 // TWO) against x, by a block of 256 threads in a fixed order; every thread
 // receives both.
 template <bool TWO>
-__device__ __forceinline__ void block_row_dots(const SellMat& m, int64_t row, const double* x, double& s0out,
+__device__ __forceinline__ void block_row_dots(const SellMat& m, LongRowPtr lr, const double* x, double& s0out,
                                                double& s1out) {
     __shared__ double red[4], red1[4];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int64_t e0 = m.rowptr[row], e1 = m.rowptr[row + 1];
+    const int64_t e1 = lr->e1;
     double s0 = 0.0, s1 = 0.0;
-    int64_t e = e0 + threadIdx.x;
+    int64_t e = lr->e0 + threadIdx.x;
     for (; e + 256 < e1; e += 512) {
         s0 = fma(m.val[e], x[m.col[e]], s0);
         s1 = fma(m.val[e + 256], x[m.col[e + 256]], s1);
@@ -216,8 +321,7 @@ __device__ __forceinline__ void block_row_dots(const SellMat& m, int64_t row, co
     for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o, 64);
     double sd = 0.0;
     if (TWO) {
-        for (int64_t f = m.rowptr1[row] + threadIdx.x; f < m.rowptr1[row + 1]; f += 256)
-            sd = fma(m.val1[f], x[m.col1[f]], sd);
+        for (int64_t f = lr->f0 + threadIdx.x; f < lr->f1; f += 256) sd = fma(m.val1[f], x[m.col1[f]], sd);
         for (int o = 32; o > 0; o >>= 1) sd += __shfl_xor(sd, o, 64);
     }
     if (lane == 0) {
@@ -259,8 +363,10 @@ static int sell_build(lb_ctx* c, int64_t M, const int64_t* rowptr, const int64_t
     const size_t o_off0 = take(sizeof(int64_t) * (size_t)(S + 1));
     const size_t o_off1 = take(sizeof(int64_t) * (size_t)(S + 1));
     const size_t o_mask = take(sizeof(uint64_t) * (size_t)S);
-    const size_t o_long = take(sizeof(int) * (size_t)M);
+    const size_t o_long = take(sizeof(LongRow) * (size_t)std::min<int64_t>(M, nnz / (kLongRow + 1) + 1));
     const size_t o_nl = take(sizeof(int));
+    const size_t o_head = take(sizeof(SellHead) * (size_t)S * (two ? 2 : 1));
+    const size_t o_scan = take(sizeof(int64_t) * (scan_scratch(S) + 2));
     const size_t o_extra = take(extra_bytes);
     const size_t fixed = off;
     int rc = lb_ws_reserve(c, fixed);
@@ -275,10 +381,12 @@ static int sell_build(lb_ctx* c, int64_t M, const int64_t* rowptr, const int64_t
         int* nlong = (int*)(ws + o_nl);
         LB_HIP(hipMemsetAsync(nlong, 0, sizeof(int), s));
         hipLaunchKernelGGL(k_sell_widths, dim3(rgrid), dim3(256), 0, s, M, S, rowptr, two ? rowptr1 : nullptr, off0,
-                           off1, (uint64_t*)(ws + o_mask), (int*)(ws + o_long), nlong);
+                           off1, (uint64_t*)(ws + o_mask), (LongRow*)(ws + o_long), nlong);
         LB_CHECK_LAUNCH();
-        hipLaunchKernelGGL(k_sell_scan, dim3(1), dim3(1024), 0, s, S, off0, two ? off1 : nullptr);
-        LB_CHECK_LAUNCH();
+        int64_t* scratch = (int64_t*)(ws + o_scan);
+        rc = scan_counts(s, S, off0, off0, nullptr, scratch, scratch + scan_scratch(S));
+        if (!rc && two) rc = scan_counts(s, S, off1, off1, nullptr, scratch, scratch + scan_scratch(S));
+        if (rc) return rc;
         LB_HIP(hipMemcpyAsync(&hl, nlong, sizeof(int), hipMemcpyDeviceToHost, s));
         LB_HIP(hipMemcpyAsync(&tot0, off0 + S, sizeof(int64_t), hipMemcpyDeviceToHost, s));
         if (two) LB_HIP(hipMemcpyAsync(&tot1, off1 + S, sizeof(int64_t), hipMemcpyDeviceToHost, s));
@@ -303,28 +411,28 @@ static int sell_build(lb_ctx* c, int64_t M, const int64_t* rowptr, const int64_t
     SellMat m;
     m.M = M;
     m.S = S;
-    m.rowptr = rowptr;
     m.col = col;
     m.val = val;
-    m.rowptr1 = two ? rowptr1 : nullptr;
     m.col1 = col1;
     m.val1 = val1;
-    m.off0 = (const int64_t*)(ws + o_off0);
+    SellHead* head0 = (SellHead*)(ws + o_head);
+    SellHead* head1 = two ? head0 + S : nullptr;
+    m.head0 = head0;
     m.scol0 = (const int*)(ws + o_sc0);
     m.sval0 = (const double*)(ws + o_sv0);
-    m.off1 = (const int64_t*)(ws + o_off1);
+    m.head1 = head1;
     m.scol1 = (const int*)(ws + o_sc1);
     m.sval1 = (const double*)(ws + o_sv1);
-    m.lmask = (const uint64_t*)(ws + o_mask);
-    m.longrows = (const int*)(ws + o_long);
+    m.longrows = (const LongRow*)(ws + o_long);
     m.nlong = hl;
     m.nlong8 = (hl + 7) / 8 * 8;
     m.ngroups = (int)((S + 3) / 4);
     m.per_xcd = (m.ngroups + 7) / 8;
     m.contig = 3 * 8 * (M / 8) <= ((int64_t)4 << 20);  // three windows of M/8 doubles within 4 MB
-    hipLaunchKernelGGL(k_sell_fill, dim3(rgrid), dim3(256), 0, s, M, S, m.lmask, rowptr, col, val, m.off0,
-                       (int*)(ws + o_sc0), (double*)(ws + o_sv0), two ? rowptr1 : nullptr, col1, val1, m.off1,
-                       (int*)(ws + o_sc1), (double*)(ws + o_sv1));
+    hipLaunchKernelGGL(k_sell_fill, dim3((unsigned)S), dim3(64), 0, s, M, (const uint64_t*)(ws + o_mask), rowptr, col,
+                       val, (const int64_t*)(ws + o_off0), (int*)(ws + o_sc0), (double*)(ws + o_sv0), head0,
+                       two ? rowptr1 : nullptr, col1, val1, (const int64_t*)(ws + o_off1), (int*)(ws + o_sc1),
+                       (double*)(ws + o_sv1), head1);
     LB_CHECK_LAUNCH();
     *out = m;
     *extra_off = o_extra;

@@ -63,21 +63,20 @@ __global__ __launch_bounds__(256) void k_mv_sell(SellMat a, const double* x, dou
     const int wk = sell_work(a);
     if (wk < 0) return;
     if (wk < a.nlong) {
-        const int64_t row = a.longrows[wk];
+        const LongRowPtr lr = (LongRowPtr)(a.longrows + wk);
         double q0, q1;
-        block_row_dots<false>(a, row, x, q0, q1);
-        if (threadIdx.x == 0) y[row] = q0;
+        block_row_dots<false>(a, lr, x, q0, q1);
+        if (threadIdx.x == 0) y[lr->row] = q0;
         return;
     }
     const int sl = __builtin_amdgcn_readfirstlane((wk - a.nlong) * 4 + (int)(threadIdx.x >> 6));
     if (sl >= a.S) return;
     const int lane = threadIdx.x & (kSlice - 1);
     const int64_t r = (int64_t)sl * kSlice + lane;
-    const bool mine = r < a.M && !((a.lmask[sl] >> lane) & 1);
-    const int64_t o0 = a.off0[sl];
-    const int w0 = (int)((a.off0[sl + 1] - o0) / kSlice);
+    const SellHeadPtr head = (SellHeadPtr)(a.head0 + sl);
+    const bool mine = r < a.M && !((head->lmask >> lane) & 1);
     double acc[1] = {0.0};
-    sell_row<1>(a.scol0 + o0 + lane, a.sval0 + o0 + lane, w0, x, a.M, 1, acc);
+    sell_row<1>(head, a.scol0, a.sval0, lane, x, a.M, 1, acc);
     if (mine) y[r] = acc[0];
 }
 
