@@ -957,30 +957,69 @@ int bpad(int B) { return B <= 16 ? 16 : (B <= 32 ? 32 : 64); }
 
 }  // namespace
 
-// Default tile from sweeps on MI355X (LDS-staged kernels): 64 rows per wave for
-// 16-state blocks (32 rows, one wave per block for 32/64 states), and k-slabs
-// sized so that one system alone gives about 2500 row-waves x slabs (5000 for
-// 32/64 states): long slabs keep the streaming loads of a wave going, and at
-// N = 200 a single system still fills the chip. Slabs are a multiple of 32
-// columns (128 bytes of FP32, 256 of FP64) so that every slab starts on a line,
-// and at least 256 (384 for 64 states) long. The slab length fixes the
-// summation order, so it depends on (M, Bp) only and never on the precision
-// or on how many systems share a launch: a system's result is bit-identical
-// alone and batched.
+// Slabs of at least 256 columns (384 for 64 states), for about 2500 row-waves x
+// slabs (5000 for 32 and 64 states) with tiles of 64 (32) rows: the slab length
+// of large M, and the measure of the allocation-free call's limit.
+static int64_t long_slabs(int64_t M, int Bp) {
+    const int CT = Bp / 16;
+    const int64_t rowwaves = CT == 1 ? (M + 63) / 64 : (M + 31) / 32;
+    const int64_t target = CT == 1 ? 2500 : 5000;
+    const int64_t maxslab = std::max<int64_t>(1, M / (CT == 4 ? 384 : 256));
+    return std::max<int64_t>(1, std::min((target + rowwaves - 1) / rowwaves, maxslab));
+}
+
+// Default tile from sweeps on MI355X (LDS-staged kernels). A stage of one system
+// is fastest with one wave per SIMD (1024, just under rather than just over) and
+// as few slabs as that takes: more waves mean more partial sums, more rows in
+// flight at once and a second round that is nearly empty. With 16 states, in us
+// a stage (2500 waves of 64 rows before / now):
+//   N = 20   16 rows   25 / 9.4       N = 80   32 rows   81 / 58
+//   N = 30   16 rows   22 / 11        N = 100  64 rows  162 / 132
+//   N = 60   32 rows   36 / 27        N = 128  64 rows  409 / 333
+// Hence tiles of 16 rows below M = 2500, of 32 below 8200, of 64 beyond (32 for
+// 64 states in FP64, which fits two waves of that size on a SIMD), and as many
+// slabs as keep row tiles x slabs within 1024, or within 2048 where that fills
+// the last round better. From M = 32768 on the waves of one system fill the chip
+// several times over and the stage runs at the read stream's rate: about 2500
+// waves there (N = 200, two systems: 3857 us a stage; with 1875 waves 3932).
+// FP32 keeps the long rule's slabs at every size: a slab is summed in FP32, so its
+// length is the sum's accuracy (N = 99, 50 states: with 6 slabs instead of 17 the
+// stage is 1.3 times as fast and the error 1.7 times as large).
+// Slabs are a multiple of 32 columns (128 bytes of FP32, 256 of FP64) so that
+// every slab starts on a line. The slab length fixes the summation order, so it
+// depends on (M, Bp) and the precision only and never on how many systems share
+// a launch: a system's result is bit-identical alone and batched.
 lb_tile lb_default_tile(int64_t M, int Bp, int precision, int R) {
     lb_tile t;
     const int CT = Bp / 16;
-    t.rows = CT == 1 ? 64 : 32;
-    t.waves = CT == 1 ? 2 : 1;
     (void)R;
-    (void)precision;
-    const int64_t rowwaves = (M + t.rows - 1) / t.rows;
-    const int64_t target = CT == 1 ? 2500 : 5000;
-    int64_t nslab = (target + rowwaves - 1) / rowwaves;
-    const int64_t minslab = CT == 4 ? 384 : 256;
-    const int64_t maxslab = std::max<int64_t>(1, M / minslab);
-    if (nslab > maxslab) nslab = maxslab;
-    if (nslab < 1) nslab = 1;
+    t.rows = M < (precision == LB_FP32 ? 2500 : 3000) ? 16 : M < 8200 ? 32 : 64;
+    t.waves = 4;
+    int64_t nslab;
+    if (M >= 32768) {
+        t.rows = CT == 1 || precision == LB_FP32 ? 64 : 32;
+        t.waves = CT == 1 ? 2 : 1;
+        nslab = long_slabs(M, Bp);
+    } else if (precision == LB_FP32) {
+        t.waves = 1;
+        nslab = long_slabs(M, Bp);
+    } else {
+        const int64_t tiles = (M + t.rows - 1) / t.rows, groups = (tiles + 3) / 4;
+        if (t.rows == 16) {
+            nslab = std::min<int64_t>(5, (M + 63) / 64);
+        } else {
+            const int64_t n1 = std::max<int64_t>(1, 1024 / tiles), n2 = std::max<int64_t>(1, 2048 / tiles);
+            // two rounds, with twice the partial sums, where they are filled 15 % better than one
+            nslab = std::min<int64_t>(t.rows == 64 && n2 * 100 > n1 * 2 * 115 ? n2 : n1, 9);
+        }
+        // workgroups of four waves (they share X's lines) where those do not start another round
+        if (groups * nslab > 256 * ((tiles * nslab + 1023) / 1024)) t.waves = 1;
+        // no more partial sums than the allocation-free call holds, where the longer slabs fit it
+        // (three and a half packed states besides them)
+        const int64_t lim = (((int64_t)LB_NOALLOC_SCRATCH_BYTES - 4096) / (4 * (M + 16) * Bp) - 7) / 2;
+        nslab = std::min(nslab, std::max(lim, long_slabs(M, Bp)));
+        if (CT == 4 && t.rows == 64) t.rows = 32;
+    }
     int64_t ks = (M + nslab - 1) / nslab;
     ks = (ks + 31) / 32 * 32;
     t.kslab = (int)ks;
@@ -1000,6 +1039,17 @@ static void load_tune_cache(lb_ctx* c) {
     while (fscanf(f, "%lld %d %d %d %d %d", &M, &Bp, &prec, &rows, &ks, &waves) == 6)
         c->tuned[std::make_tuple((int64_t)M, Bp, prec)] = lb_tile{rows, ks, waves};
     fclose(f);
+}
+
+// The tile whose scratch the allocation-free call's limit is stated for: the long
+// slabs, whatever the default tile of that size (a size refused stays refused).
+static lb_tile limit_tile(int64_t M, int Bp) {
+    lb_tile t;
+    t.rows = Bp == 16 ? 64 : 32;
+    t.waves = 1;
+    const int64_t ns = long_slabs(M, Bp);
+    t.kslab = (int)(((M + ns - 1) / ns + 31) / 32 * 32);
+    return t;
 }
 
 static lb_tile choose_tile(lb_ctx* c, int64_t M, int Bp, int precision, int R) {
@@ -1372,12 +1422,20 @@ int lb_impl_propagate_noalloc(lb_ctx* c, int64_t M, const lb_prop_sys* sys, int6
     }
     if (!base) return lb_fail(LB_ERR_DEVICE, "the static scratch of device %d is not set up", c->device);
     Plan p;
-    int rc = plan_make(p, 1, M, ldq, B, precision, choose_tile(c, M, bpad(B), precision, 1), true);
+    const int Bp = bpad(B);
+    int rc = plan_make(p, 1, M, ldq, B, precision, choose_tile(c, M, Bp, precision, 1), true);
     if (rc) return rc;
-    if (p.bytes > kScratchBytes)
+    size_t need = p.bytes;
+    if (p.kind == PATH_MFMA && c->tuned.find(std::make_tuple(M, Bp, precision)) == c->tuned.end()) {
+        Plan lim;
+        rc = plan_make(lim, 1, M, ldq, B, precision, limit_tile(M, Bp), true);
+        if (rc) return rc;
+        need = std::max(need, lim.bytes);
+    }
+    if (need > kScratchBytes)
         return lb_fail(LB_ERR_UNSUPPORTED,
                        "M=%lld with %d states needs %zu bytes of scratch; the allocation-free propagate holds %zu",
-                       (long long)M, B, p.bytes, kScratchBytes);
+                       (long long)M, B, need, kScratchBytes);
     rc = plan_align(p, sys);
     if (rc) return rc;
     plan_buffers(p, (char*)base);
