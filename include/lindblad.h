@@ -193,6 +193,9 @@ int lindblad_prepare_sparse_fill(lb_ctx* ctx, int N, const lb_csr_c128* H, int P
  * of leading dimension ldq. precision LB_FP64 uses Q directly; LB_FP32
  * requires Q32 (device float, same ldq) from lindblad_q_to_f32 and ignores
  * Q. Bit-for-bit deterministic for fixed inputs and launch configuration.
+ * One FP64 state of 256 < M <= 4096 runs as one cooperative launch that takes the
+ * whole GPU for the call (HIP runs one such launch at a time; a launch per stage,
+ * with the same bits, where it is not available or the stream is being captured).
  * When Q (or Q32) starts on a 128-byte boundary and its rows are 128-byte
  * multiples (ldq a multiple of 16 in FP64, 32 in FP32), the stage GEMM stages
  * Q through LDS with full-line streaming loads; otherwise it loads the matrix

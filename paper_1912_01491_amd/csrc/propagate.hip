@@ -8,7 +8,9 @@
 //
 // Dense paths (per stage):
 //   * B = 1: k_gemv -- one wavefront per group of rows, lanes along the row,
-//     cross-lane reduction, stage combine fused into the same kernel.
+//     cross-lane reduction, stage combine fused into the same kernel; for one
+//     system of 256 < M <= 4096, rk4_resident.h -- one cooperative launch runs
+//     all steps with Q on the chip.
 //   * B >= 2: k_gemm64 / k_gemm32 -- split-K GEMM on the matrix cores
 //     (v_mfma_f64_16x16x4f64, v_mfma_f32_16x16x4f32) writing per-slab
 //     partial sums, followed by k_stage which reduces the slabs in a fixed
@@ -23,6 +25,7 @@
 #include <mutex>
 
 #include "lb_internal.h"
+#include "rk4_resident.h"
 #include "rk4_small.h"
 #include "rowdot.h"
 #include "sell.h"
@@ -1072,6 +1075,10 @@ int lb_impl_q_to_f32(lb_ctx* c, int64_t M, const double* Q, int64_t ldq, float* 
 
 namespace {
 
+// The cooperative launch and the load of Q cost about 45 us: two steps of a launch
+// per stage (N = 37: 78 us resident against 85; one step 55 us).
+constexpr int64_t kResidentSteps = 2;
+
 enum PathKind { PATH_SMALL, PATH_GEMV, PATH_MFMA };
 
 struct Plan {
@@ -1276,8 +1283,23 @@ static int plan_init_state(const Plan& p, hipStream_t s) {
 
 // Enqueues the whole integration (kernels only: no synchronization, no copies),
 // so it can be recorded into a graph.
-static int plan_launch(const Plan& p, hipStream_t s, double dt, int64_t steps) {
+static int plan_launch(const Plan& p, hipStream_t s, double dt, int64_t steps, const Rk4Resident& res) {
     if (steps == 0) return LB_OK;
+    if (res.fn) {
+        const int64_t n = 3 * (int64_t)lb_align(p.M, 32);
+        hipLaunchKernelGGL(k_resident_init, dim3(lb_blocks(n, 256)), dim3(256), 0, s, p.W, n);
+        LB_CHECK_LAUNCH();
+        const double* const* q = (const double* const*)p.d;
+        const double* const* k = (const double* const*)(p.d + 2 * p.R);
+        double* const* v = (double* const*)(p.d + 3 * p.R);
+        int M = (int)p.M, spins = 1 << 20;
+        int64_t ldq = p.ldq, stride = lb_align(p.M, 32);
+        double* w = p.W;
+        void* args[] = {&q, &k, &v, &M, &ldq, &w, &stride, &dt, &steps, &spins};
+        if (hipLaunchCooperativeKernel((const void*)res.fn, dim3(res.grid), dim3(256), args, 0, s) == hipSuccess)
+            return LB_OK;
+        (void)hipGetLastError();  // not launched: a launch per stage, with the same bits
+    }
     if (p.kind == PATH_SMALL) {
         hipLaunchKernelGGL(p.small.fn, dim3(p.R, p.B), dim3(p.small.threads), 0, s, (const double* const*)p.d,
                            (const double* const*)(p.d + 2 * p.R), (double* const*)(p.d + 3 * p.R), (int)p.M, p.ldq,
@@ -1348,6 +1370,20 @@ static int plan_for(lb_ctx* c, Plan& p, int R, int64_t M, const lb_prop_sys* sys
     return plan_bind(c, p, (char*)c->ws, sys);
 }
 
+// The resident kernel for this plan, or none: one system, one state, enough steps
+// to pay for the cooperative launch and the load of Q, and a stream that is not
+// being captured. It sums a row as k_gemv does: the same bits either way.
+static Rk4Resident plan_resident(lb_ctx* c, const Plan& p, int64_t steps) {
+    Rk4Resident r;
+    if (p.kind != PATH_GEMV || p.R != 1 || steps < kResidentSteps) return r;
+    r = rk4_resident_pick(p.M);
+    if (!r.fn) return r;
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(c->stream, &cap) != hipSuccess) (void)hipGetLastError();
+    if (cap != hipStreamCaptureStatusNone || !rk4_resident_fits(c->device, r.grid)) r.fn = nullptr;
+    return r;
+}
+
 }  // namespace
 
 // R systems of size M, B states each.
@@ -1357,7 +1393,7 @@ int lb_impl_propagate(lb_ctx* c, int R, int64_t M, const lb_prop_sys* sys, int64
     Plan p;
     int rc = plan_for(c, p, R, M, sys, ldq, B, precision, force_tile, true);
     if (rc) return rc;
-    return plan_launch(p, c->stream, dt, steps);
+    return plan_launch(p, c->stream, dt, steps, plan_resident(c, p, steps));
 }
 
 int lb_impl_time_stage(lb_ctx* c, int R, int64_t M, const lb_prop_sys* sys, int64_t ldq, int B, int precision,
@@ -1442,7 +1478,7 @@ int lb_impl_propagate_noalloc(lb_ctx* c, int64_t M, const lb_prop_sys* sys, int6
     hipLaunchKernelGGL(k_set_ptrs, dim3(1), dim3(64), 0, c->stream, p.d, (const void*)sys->Q, (const void*)sys->Q32,
                        (const void*)sys->K, (void*)sys->V);
     LB_CHECK_LAUNCH();
-    return plan_launch(p, c->stream, dt, steps);
+    return plan_launch(p, c->stream, dt, steps, plan_resident(c, p, steps));
 }
 
 struct lb_graph_entry {
@@ -1504,7 +1540,7 @@ int lb_impl_propagate_graph(lb_ctx* c, int64_t M, const lb_prop_sys* sys, int64_
         hipGraph_t graph = nullptr;
         e = hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal);
         if (e == hipSuccess) {
-            rc = plan_launch(g->plan, cs, dt, steps);
+            rc = plan_launch(g->plan, cs, dt, steps, Rk4Resident());
             hipError_t e2 = hipStreamEndCapture(cs, &graph);
             if (!rc && e2 != hipSuccess) rc = lb_fail(LB_ERR_DEVICE, "hipStreamEndCapture: %s", hipGetErrorString(e2));
         } else {
