@@ -18,25 +18,27 @@
 // projections of gamma's D-rows onto diagonal positions (table Pt) and
 // prefix sums over the diagonal, so the whole assembly is O(M^2) work.
 //
-// Kernels, in launch order:
-//   k_pt       Pt[a][k] = sum_l w_l(a) gamma[D^l][k]              (N x M)
-//   k_cdd      Cdd[a][c] = C(a,a,c,c)                              (N x N)
-//   k_gth_a/c  partial sums over chunks of b of G and Theta from the 2x2
+// Kernels, in launch order (each launch holds independent pieces, told apart by
+// block index; small N is bound by launches, so there are three of them):
+//   k_pre1     Pt[a][k] = sum_l w_l(a) gamma[D^l][k]              (N x M)
+//              and partial sums over chunks of b of G and Theta from the 2x2
 //              gamma blocks of pairs sharing a vertex (coalesced along a or c)
-//   k_gth_fin  G, Theta, Z = -iH - G/2, Lambda = L(1)               (N x N)
-//   k_expand   K_s = Tr(F_s Lambda)/N
-//   then, concurrently on two streams:
+//   k_pre2     Cdd[a][c] = C(a,a,c,c)                              (N x N)
+//              and G, Theta, Z = -iH - G/2, Lambda = L(1)           (N x N)
+//   k_rest     N <= kFuseN: everything below in one launch
+//   beyond, concurrently on two streams:
 //   k_quad     Q[pair][pair] for disjoint pairs (the bulk: ~M^2 elements) and
 //              the shared-vertex elements inside the segments it owns; one
 //              workgroup per pair (a, c) reads gamma at exactly the positions
 //              of Q it writes, so gamma is read once and Q written once
 //   k_segpp    shared-vertex elements in a row pair's own-vertex segments
-//   k_drows    Q[D][pair]          (prefix sums over the diagonal)
-//   k_dcols    Q[pair][D]
+//   k_dvec     Q[D][pair] and Q[pair][D] (prefix sums over the diagonal)
 //   k_dd1/2    Q[D][D]
-//   k_zero_pad the padding columns of Q
+//   k_tail     K_s = Tr(F_s Lambda)/N and the padding columns of Q
 // gamma is read assuming exact Hermiticity: an entry may be read from
 // either triangle, whichever keeps the wavefront's loads contiguous.
+#include <string.h>
+
 #include <algorithm>
 #include <vector>
 
@@ -115,35 +117,48 @@ __device__ __forceinline__ cd ecoef(int Y, double s, cd v) { return Y == 0 ? csc
 // ---------------------------------------------------------------------------
 
 // Pt[a][k] = sum_l w_l(a) gamma[D^l][k]: w_l(a) = 1/sqrt(l(l+1)) for l > a,
-// -a/sqrt(a(a+1)) for l = a, 0 otherwise -> a suffix sum over l per column k.
-__global__ void k_pt(GV v, double* Pt) {
-    const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+// -a/sqrt(a(a+1)) for l = a, 0 otherwise -> a suffix sum over l per column k,
+// with the loads of eight l ahead of their sums (one at a time the chain waited
+// for each load).
+__device__ __forceinline__ void pt_column(const GV& v, double* Pt, int64_t k) {
     if (k >= v.M) return;
     const int N = v.N;
     const int64_t D0 = 2 * v.P - 1;  // row of D^l is D0 + l
     cd S = cmk(0, 0);
-    for (int a = N - 1; a >= 0; --a) {
-        cd val = S;
-        if (a >= 1) {
-            const cd ga = gam(v, D0 + a, k);
-            const double nrm = 1.0 / sqrt((double)a * (a + 1));
-            val = cadd(val, cscale(ga, -(double)a * nrm));
-            S = cadd(S, cscale(ga, nrm));
+    for (int a1 = N - 1; a1 >= 0; a1 -= 8) {
+        cd g[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) g[i] = a1 - i >= 1 ? gam(v, D0 + a1 - i, k) : cmk(0, 0);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const int a = a1 - i;
+            if (a < 0) break;
+            cd val = S;
+            if (a >= 1) {
+                const double nrm = 1.0 / sqrt((double)a * (a + 1));
+                val = cadd(val, cscale(g[i], -(double)a * nrm));
+                S = cadd(S, cscale(g[i], nrm));
+            }
+            cstore(Pt, (int64_t)a * v.M + k, val);
         }
-        cstore(Pt, (int64_t)a * v.M + k, val);
     }
 }
 
 // Cdd[a][c] = sum_l' Pt[a][D^l'] w_l'(c)
-__global__ void k_cdd(GV v, double* Cdd) {
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int N = v.N;
-    if (t >= (int64_t)N * N) return;
-    const int a = (int)(t / N), c = (int)(t % N);
+__device__ __forceinline__ cd cdd_elem(const GV& v, int a, int c) {
     const int64_t D0 = 2 * v.P - 1;
+    const double* row = v.Pt + 2 * ((int64_t)a * v.M + D0);
     cd s = cmk(0, 0);
-    for (int l = (c > 1 ? c : 1); l < N; ++l) s = cadd(s, cscale(cload(v.Pt, (int64_t)a * v.M + D0 + l), lb_wdiag(l, c)));
-    cstore(Cdd, t, s);
+    int l = c > 1 ? c : 1;
+    for (; l + 4 <= v.N; l += 4) {
+        cd x[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) x[i] = cload(row, l + i);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) s = cadd(s, cscale(x[i], lb_wdiag(l + i, c)));
+    }
+    for (; l < v.N; ++l) s = cadd(s, cscale(cload(row, l), lb_wdiag(l, c)));
+    return s;
 }
 
 // ---------------------------------------------------------------------------
@@ -229,57 +244,63 @@ __device__ __forceinline__ void pp_store_plain(double* Q, int64_t ldq, int64_t P
 //   b < a            beta itself: row {b,c} fixed per c, columns p(b,a) along a
 //   a < b < c        beta = (gamma[{a,b}][{b,c}])^H: row p(a,b), columns p(b,c) along c
 //   b > max(a,c)     beta itself (strided: columns p(a,b) of different segments)
-// k_gth_a (lanes along a) takes the first and last ranges, k_gth_c (lanes along
+// gth_a (lanes along a) takes the first and last ranges, gth_c (lanes along
 // c) the middle one; both split b into chunks of kGthChunk and write one partial
-// sum per chunk; k_gth_fin adds the chunks in order of b, then the b = a and
+// sum per chunk; gth_fin adds the chunks in order of b, then the b = a and
 // b = c terms. Partial layout: Gp[k][a][c] (G_ac), Tp[k][x][y] (Theta_xy).
-constexpr int kGthChunk = 16;
+constexpr int kGthChunk = 8;
 
 __device__ __forceinline__ void gth_add(cd& g, cd& th, const Blk& B, int a, int b, int c) {
     g = cadd(g, blk_c(B.ss, B.sa, B.as, B.aa, sgn(b, c), sgn(a, b)));
     th = cadd(th, blk_c(B.ss, B.sa, B.as, B.aa, sgn(c, b), sgn(b, a)));
 }
 
-__global__ void k_gth_a(GV v, double* Gp, double* Tp) {
+__device__ __forceinline__ void gth_a(const GV& v, double* Gp, double* Tp, int64_t t, int k) {
     const int N = v.N;
     const int64_t NN = (int64_t)N * N;
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (t >= NN) return;
     const int a = (int)(t % N), c = (int)(t / N);
-    const int b0 = (int)blockIdx.y * kGthChunk, b1 = min(N, b0 + kGthChunk);
+    const int b0 = k * kGthChunk, b1 = min(N, b0 + kGthChunk);
     const int hi = a > c ? a : c;
     cd g = cmk(0, 0), th = cmk(0, 0);
-    for (int b = b0; b < b1; ++b) {
-        if (b == a || b == c || (b > a && b < hi)) continue;
-        gth_add(g, th, blk_load(v, lb_upair(N, b, c), lb_upair(N, a, b)), a, b, c);
+    for (int b4 = b0; b4 < b1; b4 += 4) {  // four blocks on their way at once
+        Blk B[4];
+        bool use[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int b = b4 + i;
+            use[i] = b < b1 && b != a && b != c && !(b > a && b < hi);
+            B[i] = use[i] ? blk_load(v, lb_upair(N, b, c), lb_upair(N, a, b)) : Blk{};
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            if (use[i]) gth_add(g, th, B[i], a, b4 + i, c);
     }
-    const int64_t k = blockIdx.y;
-    cstore(Gp, k * NN + (int64_t)a * N + c, g);
-    cstore(Tp, k * NN + (int64_t)c * N + a, th);
+    cstore(Gp, (int64_t)k * NN + (int64_t)a * N + c, g);
+    cstore(Tp, (int64_t)k * NN + (int64_t)c * N + a, th);
 }
 
-__global__ void k_gth_c(GV v, double* Gp, double* Tp) {
+__device__ __forceinline__ void gth_c(const GV& v, double* Gp, double* Tp, int64_t t, int k) {
     const int N = v.N;
     const int64_t NN = (int64_t)N * N;
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (t >= NN) return;
     const int c = (int)(t % N), a = (int)(t / N);
-    const int k0 = (int)blockIdx.y * kGthChunk;
+    const int k0 = k * kGthChunk;
     const int b0 = max(k0, a + 1), b1 = min(min(N, k0 + kGthChunk), c);
     cd g = cmk(0, 0), th = cmk(0, 0);
+#pragma unroll 4
     for (int b = b0; b < b1; ++b)
         gth_add(g, th, blk_t(blk_load(v, lb_pair(N, a, b), lb_pair(N, b, c))), a, b, c);
-    const int64_t k = blockIdx.y;
-    cstore(Gp, k * NN + (int64_t)a * N + c, g);
-    cstore(Tp, k * NN + (int64_t)c * N + a, th);
+    cstore(Gp, (int64_t)k * NN + (int64_t)a * N + c, g);
+    cstore(Tp, (int64_t)k * NN + (int64_t)c * N + a, th);
 }
 
 // Z = -iH - G/2 and Lambda = Theta - G = L(1).
-__global__ void k_gth_fin(GV v, const double* H, const double* GpA, const double* TpA, const double* GpC,
-                          const double* TpC, int nch, double* Z, double* Lam) {
+__device__ __forceinline__ void gth_fin(const GV& v, const double* H, const double* GpA, const double* TpA,
+                                        const double* GpC, const double* TpC, int nch, double* Z, double* Lam,
+                                        int64_t t) {
     const int N = v.N;
     const int64_t NN = (int64_t)N * N;
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (t >= NN) return;
     const int a = (int)(t / N), c = (int)(t % N);
     cd G = cmk(0, 0), Th = cmk(0, 0);
@@ -288,8 +309,9 @@ __global__ void k_gth_fin(GV v, const double* H, const double* GpA, const double
         Th = cadd(Th, cadd(cload(TpA, k * NN + t), cload(TpC, k * NN + t)));
     }
     if (a == c) {
-        G = cadd(G, chat(v, a, a, a, a));
-        Th = cadd(Th, chat(v, a, a, a, a));
+        const cd d = cdd_elem(v, a, a);  // C(a,a,a,a); the table is being written by this launch
+        G = cadd(G, d);
+        Th = cadd(Th, d);
     } else {
         G = cadd(G, chat(v, a, c, a, a));   // b = a
         G = cadd(G, chat(v, c, c, a, c));   // b = c
@@ -299,6 +321,44 @@ __global__ void k_gth_fin(GV v, const double* H, const double* GpA, const double
     const cd h = cload(H, t);
     cstore(Z, t, cmk(h.im - 0.5 * G.re, -h.re - 0.5 * G.im));
     cstore(Lam, t, csub(Th, G));
+}
+
+// The two set-up launches: blocks of Pt columns, then of each half of the partial
+// sums; blocks of Cdd, then of Z and Lambda. As five kernels one after the other,
+// with one block of gamma on its way per thread, they took 145 us at N = 100 and
+// 524 us at N = 200; these take 98 and 475 us (6 and 3 us at N = 16, where the
+// launches were most of it).
+struct PreArgs {
+    GV v;
+    const double* H;
+    double *Pt, *Cdd, *GpA, *TpA, *GpC, *TpC, *Z, *Lam;
+    int nch;
+    unsigned nbm, nbn;  // blocks of 256 over M columns, over N x N elements
+};
+
+__global__ __launch_bounds__(256) void k_pre1(PreArgs p) {
+    unsigned b = blockIdx.x;
+    if (b < p.nbm) {
+        pt_column(p.v, p.Pt, (int64_t)b * 256 + threadIdx.x);
+        return;
+    }
+    b -= p.nbm;
+    const unsigned half = p.nbn * (unsigned)p.nch;
+    const bool second = b >= half;
+    if (second) b -= half;
+    const int64_t t = (int64_t)(b % p.nbn) * 256 + threadIdx.x;
+    const int k = (int)(b / p.nbn);
+    if (!second) gth_a(p.v, p.GpA, p.TpA, t, k);
+    else gth_c(p.v, p.GpC, p.TpC, t, k);
+}
+
+__global__ __launch_bounds__(256) void k_pre2(PreArgs p) {
+    const int64_t t = (int64_t)(blockIdx.x % p.nbn) * 256 + threadIdx.x;
+    if (blockIdx.x < p.nbn) {
+        if (t < (int64_t)p.v.N * p.v.N) cstore(p.Cdd, t, cdd_elem(p.v, (int)(t / p.v.N), (int)(t % p.v.N)));
+    } else {
+        gth_fin(p.v, p.H, p.GpA, p.TpA, p.GpC, p.TpC, p.nch, p.Z, p.Lam, t);
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -374,15 +434,19 @@ __device__ __forceinline__ Blk quad_stage_get(double (*hb)[16][kQuadPad], int zl
                cmk(hb[4][zl][xl], hb[5][zl][xl]), cmk(hb[6][zl][xl], hb[7][zl][xl])};
 }
 
-// One workgroup per pair (a, c) of the work order (entries with a < 0 pad the
-// order to whole groups). Latency is hidden by occupancy rather than by
+// One workgroup per pair (a, c). Latency is hidden by occupancy rather than by
 // register prefetch: one LDS buffer per tile, two barriers per tile.
-__global__ __launch_bounds__(256) void k_quad(GV v, const double* Zm, const int2* order, double* Q, int64_t ldq) {
-    __shared__ double h[8][16][kQuadPad];  // gamma blocks at positions R[z][x], staged [z][x]
-    __shared__ double e[4][16][kQuadPad];  // outputs R[z][x], staged [z][x]
-    __shared__ double sb[4][16][33];       // line windows of the S row, one per x of the block
-    const int a = order[blockIdx.x].x, c = order[blockIdx.x].y;
-    if (a < 0) return;
+struct QuadLds {
+    double h[8][16][kQuadPad];  // gamma blocks at positions R[z][x], staged [z][x]
+    double e[4][16][kQuadPad];  // outputs R[z][x], staged [z][x]
+    double sb[4][16][33];       // line windows of the S row, one per x of the block
+};
+
+__device__ __forceinline__ void quad_pair(const GV& v, const double* Zm, int a, int c, double* Q, int64_t ldq,
+                                          QuadLds& lds) {
+    auto& h = lds.h;
+    auto& e = lds.e;
+    auto& sb = lds.sb;
     const int L = c - a - 1;
     if (L <= 0) return;
     const int N = v.N;
@@ -481,6 +545,13 @@ __global__ __launch_bounds__(256) void k_quad(GV v, const double* Zm, const int2
     }
 }
 
+// Pairs in the work order (entries with a < 0 pad the order to whole groups).
+__global__ __launch_bounds__(256) void k_quad(GV v, const double* Zm, const int2* order, double* Q, int64_t ldq) {
+    __shared__ QuadLds lds;
+    const int2 o = order[blockIdx.x];
+    if (o.x >= 0) quad_pair(v, Zm, o.x, o.y, Q, ldq, lds);
+}
+
 // C(a,b,c,d) where the pairs {u,vv} (= s) and {x,y} (= n) share a vertex and
 // sn = gamma[s][n]: block terms from sn or its transpose, diagonal terms (the
 // projections Pt) as in chat.
@@ -519,13 +590,13 @@ __device__ __forceinline__ Acc4 pp_shared_pre(const GV& v, const double* Zm, int
 // Segments x and y of pair row {x,y}: the elements whose column pair shares a
 // vertex with the row pair (and the diagonal element). One wavefront per row
 // pair, lanes along the column pair's second vertex.
-__global__ __launch_bounds__(256) void k_segpp(GV v, const double* Zm, const int2* pairs, double* Q, int64_t ldq) {
+__device__ __forceinline__ void segpp_row(const GV& v, const double* Zm, int64_t ps, int lane, double* Q,
+                                          int64_t ldq) {
     const int N = v.N;
     const int64_t P = v.P;
-    const int64_t ps = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
-    const int lane = threadIdx.x & 63;
     if (ps >= P) return;
-    const int x = pairs[ps].x, y = pairs[ps].y;
+    int cls, x, y;
+    lb_decode(N, ps, cls, x, y);
     for (int z = x + 1 + lane; z < N; z += 64) {
         const int64_t pn = lb_pair(N, x, z);
         pp_store_plain(Q, ldq, P, ps, pn, pp_shared_pre(v, Zm, x, y, x, z, blk_load(v, ps, pn)));
@@ -536,138 +607,198 @@ __global__ __launch_bounds__(256) void k_segpp(GV v, const double* Zm, const int
     }
 }
 
-// ---------------------------------------------------------------------------
-// Rows of the diagonal generators: Q[D^m][n] = sum_a w_m(a) (L(F_n))_aa
-// ---------------------------------------------------------------------------
-
-// One thread per pair (x, y) -> columns S(x,y) and J(x,y). The diagonal of
-// L(F_n) is accumulated along a with a running prefix sum, which gives all
-// N-1 rows D^m (w_m(a) = 1/sqrt(m(m+1)) for a < m, -m/sqrt(m(m+1)) at a = m).
-__global__ void k_drows(GV v, const double* Zm, const int2* pairs, double* Q, int64_t ldq) {
-    const int64_t pn = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int64_t P = v.P;
-    if (pn >= P) return;
-    const int N = v.N;
-    const int x = pairs[pn].x, y = pairs[pn].y;
-    const cd zxy = cload(Zm, (int64_t)x * N + y), zyx = cload(Zm, (int64_t)y * N + x);
-    cd preS = cmk(0, 0), preA = cmk(0, 0);
-    for (int a = 0; a < N; ++a) {
-        cd c1, c2;  // C(a,x,y,a), C(a,y,x,a)
-        if (a != x && a != y) {
-            const int64_t p_ax = lb_upair(N, a, x), p_ay = lb_upair(N, a, y);
-            const cd ss = gam(v, p_ax, p_ay), sa = gam(v, p_ax, P + p_ay);
-            const cd as = gam(v, P + p_ax, p_ay), aa = gam(v, P + p_ax, P + p_ay);
-            c1 = blk_c(ss, sa, as, aa, sgn(a, x), sgn(y, a));
-            c2 = blk_c(cconj(ss), cconj(as), cconj(sa), cconj(aa), sgn(a, y), sgn(x, a));
-        } else {
-            c1 = chat(v, a, x, y, a);
-            c2 = chat(v, a, y, x, a);
-        }
-        // sum_{(b,c)} (F_n)_{bc} C(a,b,c,a): (x,y) has sigma +1, (y,x) has -1
-        cd gS = cadd(ecoef(0, 1, c1), ecoef(0, -1, c2));
-        cd gA = cadd(ecoef(1, 1, c1), ecoef(1, -1, c2));
-        // (Z F_n)_aa + (F_n Z^+)_aa
-        if (a == x) {
-            gS = cadd(gS, cadd(ecoef(0, -1, zxy), ecoef(0, 1, cconj(zxy))));
-            gA = cadd(gA, cadd(ecoef(1, -1, zxy), ecoef(1, 1, cconj(zxy))));
-        } else if (a == y) {
-            gS = cadd(gS, cadd(ecoef(0, 1, zyx), ecoef(0, -1, cconj(zyx))));
-            gA = cadd(gA, cadd(ecoef(1, 1, zyx), ecoef(1, -1, cconj(zyx))));
-        }
-        if (a >= 1) {
-            const double nrm = 1.0 / sqrt((double)a * (a + 1));
-            const double* row = Q + (2 * P + a - 1) * ldq;
-            const double qS = (preS.re - (double)a * gS.re) * nrm;
-            const double qA = (preA.re - (double)a * gA.re) * nrm;
-            __builtin_nontemporal_store(qS, const_cast<double*>(row) + pn);
-            __builtin_nontemporal_store(qA, const_cast<double*>(row) + P + pn);
-        }
-        preS = cadd(preS, gS);
-        preA = cadd(preA, gA);
-    }
+__global__ __launch_bounds__(256) void k_segpp(GV v, const double* Zm, double* Q, int64_t ldq) {
+    segpp_row(v, Zm, ((int64_t)blockIdx.x * 256 + threadIdx.x) >> 6, threadIdx.x & 63, Q, ldq);
 }
 
 // ---------------------------------------------------------------------------
-// Columns of the diagonal generators: Q[s][D^m] = sum_a w_m(a) (L^+(F_s))_aa
-// with L^+(Y) = sum_jk gamma_jk F_k Y F_j + Z^+ Y + Y Z.
+// Rows and columns of the diagonal generators against pairs
 // ---------------------------------------------------------------------------
-
-__global__ void k_dcols(GV v, const double* Zm, const int2* pairs, double* Q, int64_t ldq) {
-    const int64_t ps = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+// Q[D^m][n] = sum_a w_m(a) (L(F_n))_aa and Q[n][D^m] = sum_a w_m(a) (L^+(F_n))_aa,
+// L^+(Y) = sum_jk gamma_jk F_k Y F_j + Z^+ Y + Y Z, w_m(a) = 1/sqrt(m(m+1)) for
+// a < m, -m/sqrt(m(m+1)) at a = m. For a pair n = {x, y} both diagonals come from
+// the same 2x2 blocks of gamma, between {a, x} and {a, y}. A workgroup takes PB
+// consecutive pairs: (pair, a) over its threads with all of them loading at once,
+// the diagonals in LDS, a running sum along a per chain, then rows written along
+// the pairs and columns along m. (One thread per pair, walking a with its four
+// loads on the chain, took 322 us for the rows and 249 us for the columns at
+// N = 100 and kept 77 wavefronts on the chip; this takes 99 us for both.)
+// LDS: 4 N (PB + 1) + N doubles.
+template <int PB>
+__device__ __forceinline__ void dvec_block(const GV& v, const double* Zm, int64_t pn0, double* Q, int64_t ldq,
+                                           double* lds) {
+    constexpr int LD = PB + 1, A = 256 / PB;
+    const int N = v.N, t = threadIdx.x;
     const int64_t P = v.P;
-    if (ps >= P) return;
-    const int N = v.N;
-    const int u = pairs[ps].x, w = pairs[ps].y;
-    const cd zuw = cload(Zm, (int64_t)u * N + w), zwu = cload(Zm, (int64_t)w * N + u);
-    double* rowS = Q + ps * ldq + 2 * P;
-    double* rowA = Q + (P + ps) * ldq + 2 * P;
-    cd preS = cmk(0, 0), preA = cmk(0, 0);
-    for (int a = 0; a < N; ++a) {
-        cd c1, c2;  // C(u,a,a,w) [(b,c) = (w,u)], C(w,a,a,u) [(b,c) = (u,w)]
-        if (a != u && a != w) {
-            const int64_t p_ua = lb_upair(N, u, a), p_wa = lb_upair(N, w, a);
-            const cd ss = gam(v, p_ua, p_wa), sa = gam(v, p_ua, P + p_wa);
-            const cd as = gam(v, P + p_ua, p_wa), aa = gam(v, P + p_ua, P + p_wa);
-            c1 = blk_c(ss, sa, as, aa, sgn(u, a), sgn(a, w));
-            c2 = blk_c(cconj(ss), cconj(as), cconj(sa), cconj(aa), sgn(w, a), sgn(a, u));
-        } else {
-            c1 = chat(v, u, a, a, w);
-            c2 = chat(v, w, a, a, u);
+    double* nrm = lds;
+    double* d[4];  // diagonals of L(S), L(J), L^+(S), L^+(J): [a][pair]
+#pragma unroll
+    for (int i = 0; i < 4; ++i) d[i] = lds + N + (size_t)i * N * LD;
+    for (int m = t; m < N; m += 256) nrm[m] = m ? 1.0 / sqrt((double)m * (m + 1)) : 0.0;
+    const int pl = t % PB;
+    const int64_t pn = pn0 + pl;
+    if (pn < P) {
+        int cls, x, y;
+        lb_decode(N, pn, cls, x, y);
+        const cd zxy = cload(Zm, (int64_t)x * N + y), zyx = cload(Zm, (int64_t)y * N + x);
+        for (int a = t / PB; a < N; a += A) {
+            cd c1, c2, e1, e2;  // C(a,x,y,a), C(a,y,x,a); C(x,a,a,y), C(y,a,a,x)
+            if (a != x && a != y) {
+                const Blk b = blk_load(v, lb_upair(N, a, x), lb_upair(N, a, y));
+                const Blk h = blk_t(b);
+                c1 = blk_c(b.ss, b.sa, b.as, b.aa, sgn(a, x), sgn(y, a));
+                c2 = blk_c(h.ss, h.sa, h.as, h.aa, sgn(a, y), sgn(x, a));
+                e1 = blk_c(b.ss, b.sa, b.as, b.aa, sgn(x, a), sgn(a, y));
+                e2 = blk_c(h.ss, h.sa, h.as, h.aa, sgn(y, a), sgn(a, x));
+            } else {
+                c1 = chat(v, a, x, y, a);
+                c2 = chat(v, a, y, x, a);
+                e1 = chat(v, x, a, a, y);
+                e2 = chat(v, y, a, a, x);
+            }
+            // sum_{(b,c)} (F_n)_{bc} C(a,b,c,a): (x,y) has sigma +1, (y,x) has -1
+            cd gS = cadd(ecoef(0, 1, c1), ecoef(0, -1, c2));
+            cd gA = cadd(ecoef(1, 1, c1), ecoef(1, -1, c2));
+            // sum_{(b,c)} (F_n)_{bc} C(c,a,a,b): (x,y) sigma +1 -> C(y,a,a,x); (y,x) -1 -> C(x,a,a,y)
+            cd hS = cadd(ecoef(0, 1, e2), ecoef(0, -1, e1));
+            cd hA = cadd(ecoef(1, 1, e2), ecoef(1, -1, e1));
+            // (Z F_n)_aa + (F_n Z^+)_aa and (F_n Z)_aa + (Z^+ F_n)_aa
+            if (a == x) {
+                gS = cadd(gS, cadd(ecoef(0, -1, zxy), ecoef(0, 1, cconj(zxy))));
+                gA = cadd(gA, cadd(ecoef(1, -1, zxy), ecoef(1, 1, cconj(zxy))));
+                hS = cadd(hS, cadd(ecoef(0, 1, zyx), ecoef(0, -1, cconj(zyx))));
+                hA = cadd(hA, cadd(ecoef(1, 1, zyx), ecoef(1, -1, cconj(zyx))));
+            } else if (a == y) {
+                gS = cadd(gS, cadd(ecoef(0, 1, zyx), ecoef(0, -1, cconj(zyx))));
+                gA = cadd(gA, cadd(ecoef(1, 1, zyx), ecoef(1, -1, cconj(zyx))));
+                hS = cadd(hS, cadd(ecoef(0, -1, zxy), ecoef(0, 1, cconj(zxy))));
+                hA = cadd(hA, cadd(ecoef(1, -1, zxy), ecoef(1, 1, cconj(zxy))));
+            }
+            d[0][a * LD + pl] = gS.re;
+            d[1][a * LD + pl] = gA.re;
+            d[2][a * LD + pl] = hS.re;
+            d[3][a * LD + pl] = hA.re;
         }
-        // sum_{(b,c)} (F_s)_{bc} C(c,a,a,b): (b,c) = (u,w) sigma +1 -> C(w,a,a,u); (w,u) -1 -> C(u,a,a,w)
-        cd hS = cadd(ecoef(0, 1, c2), ecoef(0, -1, c1));
-        cd hA = cadd(ecoef(1, 1, c2), ecoef(1, -1, c1));
-        // (F_s Z)_aa + (Z^+ F_s)_aa
-        if (a == u) {
-            hS = cadd(hS, cadd(ecoef(0, 1, zwu), ecoef(0, -1, cconj(zwu))));
-            hA = cadd(hA, cadd(ecoef(1, 1, zwu), ecoef(1, -1, cconj(zwu))));
-        } else if (a == w) {
-            hS = cadd(hS, cadd(ecoef(0, -1, zuw), ecoef(0, 1, cconj(zuw))));
-            hA = cadd(hA, cadd(ecoef(1, -1, zuw), ecoef(1, 1, cconj(zuw))));
-        }
-        if (a >= 1) {
-            const double nrm = 1.0 / sqrt((double)a * (a + 1));
-            rowS[a - 1] = (preS.re - (double)a * hS.re) * nrm;
-            rowA[a - 1] = (preA.re - (double)a * hA.re) * nrm;
-        }
-        preS = cadd(preS, hS);
-        preA = cadd(preA, hA);
     }
+    __syncthreads();
+    if (t < 4 * PB && pn0 + t % PB < P) {
+        double* col = lds + N + (size_t)(t / PB) * N * LD + t % PB;
+        double pre = 0.0;
+#pragma unroll 8
+        for (int a = 0; a < N; ++a) {
+            const double g = col[a * LD];
+            col[a * LD] = (pre - (double)a * g) * nrm[a];
+            pre += g;
+        }
+    }
+    __syncthreads();
+    if (pn < P)
+        for (int m = 1 + t / PB; m < N; m += A) {
+            double* row = Q + (2 * P + m - 1) * ldq + pn;
+            __builtin_nontemporal_store(d[0][m * LD + pl], row);
+            __builtin_nontemporal_store(d[1][m * LD + pl], row + P);
+        }
+    const int np = (int)(P - pn0 < PB ? P - pn0 : PB);
+    for (int i = t / 64; i < 2 * np; i += 4) {
+        const int cl = i >= np ? 1 : 0, p = i - cl * np;
+        double* row = Q + (cl * P + pn0 + p) * ldq + 2 * P - 1;
+        for (int m = 1 + t % 64; m < N; m += 64) row[m] = d[2 + cl][m * LD + p];
+    }
+}
+
+template <int PB>
+__global__ __launch_bounds__(256) void k_dvec(GV v, const double* Zm, double* Q, int64_t ldq) {
+    extern __shared__ double dvec_lds[];
+    dvec_block<PB>(v, Zm, (int64_t)blockIdx.x * PB, Q, ldq, dvec_lds);
 }
 
 // ---------------------------------------------------------------------------
 // Diagonal x diagonal block: (L(D^m'))_aa = sum_b C(a,b,b,a) w_m'(b) + 2 Re Z_aa w_m'(a)
 // ---------------------------------------------------------------------------
+// T[a][m'] by running sums over b of r_ab = Re C(a,b,b,a) (+ 2 Re Z_aa at b = a),
+// then Q[D^m][D^m'] by running sums of T over a.
 
-__global__ void k_dd1(GV v, const double* Zm, double* T) {
+// Row a of T by one workgroup; lds: N doubles. Row stride N.
+__device__ __forceinline__ void dd_row(const GV& v, const double* Zm, int a, double* T, double* lds) {
     const int N = v.N;
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= (int64_t)N * (N - 1)) return;
-    const int a = (int)(t / (N - 1)), m2 = (int)(t % (N - 1)) + 1;
-    cd s = cmk(0, 0);
-    for (int b = 0; b <= m2; ++b) {
-        cd r = chat(v, a, b, b, a);
-        if (b == a) r.re += 2.0 * cload(Zm, (int64_t)a * N + a).re;
-        s = cadd(s, cscale(r, lb_wdiag(m2, b)));
+    for (int b = threadIdx.x; b < N; b += blockDim.x) {
+        double r = chat(v, a, b, b, a).re;
+        if (b == a) r += 2.0 * cload(Zm, (int64_t)a * N + a).re;
+        lds[b] = r;
     }
-    cstore(T, t, s);
+    __syncthreads();
+    for (int m = 1 + threadIdx.x; m < N; m += blockDim.x) {
+        double pre = 0.0;
+#pragma unroll 8
+        for (int b = 0; b < m; ++b) pre += lds[b];
+        T[(int64_t)a * N + m] = (pre - (double)m * lds[m]) / sqrt((double)m * (m + 1));
+    }
+    __syncthreads();
 }
 
-__global__ void k_dd2(GV v, const double* T, double* Q, int64_t ldq) {
+// The whole block by one workgroup of at least N threads. LDS: N (N + 2) doubles.
+__device__ __forceinline__ void dd_block(const GV& v, const double* Zm, double* Q, int64_t ldq, double* lds) {
+    const int N = v.N, LD = N + 1, t = threadIdx.x;
+    double *r = lds, *nrm = lds + (size_t)N * LD;
+    for (int i = t; i < N * N; i += blockDim.x) {
+        const int a = i / N, b = i - a * N;
+        double x = chat(v, a, b, b, a).re;
+        if (b == a) x += 2.0 * cload(Zm, (int64_t)a * N + a).re;
+        r[a * LD + b] = x;
+    }
+    for (int m = t; m < N; m += blockDim.x) nrm[m] = m ? 1.0 / sqrt((double)m * (m + 1)) : 0.0;
+    __syncthreads();
+    if (t < N) {
+        double pre = 0.0;
+#pragma unroll 8
+        for (int b = 0; b < N; ++b) {
+            const double x = r[t * LD + b];
+            r[t * LD + b] = (pre - (double)b * x) * nrm[b];
+            pre += x;
+        }
+    }
+    __syncthreads();
+    if (t >= 1 && t < N) {
+        double pre = 0.0;
+#pragma unroll 8
+        for (int a = 0; a < N; ++a) {
+            const double x = r[a * LD + t];
+            if (a) Q[(2 * v.P + a - 1) * ldq + 2 * v.P + t - 1] = (pre - (double)a * x) * nrm[a];
+            pre += x;
+        }
+    }
+}
+
+// Column m' of the block: a running sum down T.
+__device__ __forceinline__ void dd_col(const GV& v, const double* T, int m2, double* Q, int64_t ldq) {
     const int N = v.N;
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= (int64_t)(N - 1) * (N - 1)) return;
-    const int m = (int)(t / (N - 1)) + 1, m2 = (int)(t % (N - 1)) + 1;
-    double s = 0;
-    for (int a = 0; a <= m; ++a) s += lb_wdiag(m, a) * cload(T, (int64_t)a * (N - 1) + (m2 - 1)).re;
-    Q[(2 * v.P + m - 1) * ldq + 2 * v.P + m2 - 1] = s;
+    double pre = m2 < N ? T[m2] : 0.0;
+    for (int m = 1; m2 < N && m < N; m += 8) {
+        double x[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) x[i] = m + i < N ? T[(int64_t)(m + i) * N + m2] : 0.0;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            if (m + i >= N) break;
+            const int mm = m + i;
+            Q[(2 * v.P + mm - 1) * ldq + 2 * v.P + m2 - 1] = (pre - (double)mm * x[i]) / sqrt((double)mm * (mm + 1));
+            pre += x[i];
+        }
+    }
 }
 
-__global__ void k_zero_pad(double* Q, int64_t M, int64_t ldq) {
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+__global__ __launch_bounds__(256) void k_dd1(GV v, const double* Zm, double* T) {
+    extern __shared__ double dd_lds[];
+    dd_row(v, Zm, blockIdx.x, T, dd_lds);
+}
+
+__global__ __launch_bounds__(64) void k_dd2(GV v, const double* T, double* Q, int64_t ldq) {
+    dd_col(v, T, (int)(blockIdx.x * 64 + threadIdx.x) + 1, Q, ldq);
+}
+
+__device__ __forceinline__ void zero_pad(double* Q, int64_t M, int64_t ldq, int64_t t) {
     const int64_t w = ldq - M;
-    if (t >= M * w) return;
-    Q[(t / w) * ldq + M + t % w] = 0.0;
+    if (t < M * w) Q[(t / w) * ldq + M + t % w] = 0.0;
 }
 
 // ---------------------------------------------------------------------------
@@ -675,9 +806,8 @@ __global__ void k_zero_pad(double* Q, int64_t M, int64_t ldq) {
 // ---------------------------------------------------------------------------
 
 // a[b][s] = scale * Re Tr(F_s A_b)
-__global__ void k_expand(int N, int B, const double* A, double* out, double scale) {
+__device__ __forceinline__ void expand_elem(int N, int B, const double* A, double* out, double scale, int64_t t) {
     const int64_t M = (int64_t)N * N - 1;
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (t >= M * B) return;
     const int b = (int)(t / M);
     const int64_t s = t % M;
@@ -691,9 +821,16 @@ __global__ void k_expand(int N, int B, const double* A, double* out, double scal
         r = cls == 0 ? kR * (akj.re + ajk.re) : kR * (akj.im - ajk.im);
     } else {
         r = 0;
-        for (int x = 0; x <= j; ++x) r += lb_wdiag(j, x) * Ab[2 * ((int64_t)x * N + x)];
+        const double nrm = 1.0 / sqrt((double)j * (double)(j + 1));  // lb_wdiag(j, x), its root taken once
+#pragma unroll 8
+        for (int x = 0; x < j; ++x) r += nrm * Ab[2 * ((int64_t)x * N + x)];
+        r += -(double)j * nrm * Ab[2 * ((int64_t)j * N + j)];
     }
     out[t] = scale * r;
+}
+
+__global__ void k_expand(int N, int B, const double* A, double* out, double scale) {
+    expand_elem(N, B, A, out, scale, (int64_t)blockIdx.x * blockDim.x + threadIdx.x);
 }
 
 // V[b][s] = <psi_b| F_s |psi_b>
@@ -771,6 +908,64 @@ __global__ void k_herm(int64_t n, const double* A, double* out) {
         out[2 * blockIdx.x] = sd[0];
         out[2 * blockIdx.x + 1] = sa[0];
     }
+}
+
+// K and the padding columns of Q.
+__global__ __launch_bounds__(256) void k_tail(GV v, const double* Lam, double* K, double* Q, int64_t ldq, unsigned nbk) {
+    const int64_t t = (int64_t)(blockIdx.x < nbk ? blockIdx.x : blockIdx.x - nbk) * 256 + threadIdx.x;
+    if (blockIdx.x < nbk) expand_elem(v.N, 1, Lam, K, 1.0 / v.N, t);
+    else zero_pad(Q, v.M, ldq, t);
+}
+
+// Up to kFuseN everything after the set-up is one launch: no piece is worth a
+// launch of its own there (2 to 12 us each at N = 8), nor are the second stream's
+// events and the upload of the work order (pairs come in pair order, decoded from
+// the block index). The line lies where the LDS of the largest piece, the diagonal
+// block's table, still lets three workgroups share a CU, as k_quad's does. Time of
+// a whole preparation, 13 launches / launch by launch on two streams / fused: N = 8
+// 90 / 66 / 23 us, N = 33 199 / 91 / 51, N = 64 471 / 247 / 207, N = 80 689 / 479 /
+// 421; from N = 100 the work order's L2 reuse is worth more (974 and 982 us).
+constexpr int kFuseN = 80;
+
+struct RestArgs {
+    GV v;
+    const double *Zm, *Lam;
+    double *Q, *K;
+    int64_t ldq;
+    unsigned nquad, nseg, ndv, nbk;  // blocks of each piece, after one for the diagonal block and before the padding's
+};
+
+static size_t rest_lds(int N) {
+    return std::max(sizeof(QuadLds), std::max(sizeof(double) * (4 * (size_t)N * 17 + N), sizeof(double) * (size_t)N * (N + 2)));
+}
+
+__global__ __launch_bounds__(256) void k_rest(RestArgs p) {
+    extern __shared__ double rest_smem[];
+    unsigned b = blockIdx.x;
+    if (b == 0) {
+        dd_block(p.v, p.Zm, p.Q, p.ldq, rest_smem);
+        return;
+    }
+    b -= 1;
+    if (b < p.nquad) {
+        int cls, a, c;
+        lb_decode(p.v.N, b, cls, a, c);
+        quad_pair(p.v, p.Zm, a, c, p.Q, p.ldq, *reinterpret_cast<QuadLds*>(rest_smem));
+        return;
+    }
+    b -= p.nquad;
+    if (b < p.ndv) {
+        dvec_block<16>(p.v, p.Zm, (int64_t)b * 16, p.Q, p.ldq, rest_smem);
+        return;
+    }
+    b -= p.ndv;
+    if (b < p.nseg) {
+        segpp_row(p.v, p.Zm, ((int64_t)b * 256 + threadIdx.x) >> 6, threadIdx.x & 63, p.Q, p.ldq);
+        return;
+    }
+    b -= p.nseg;
+    if (b < p.nbk) expand_elem(p.v.N, 1, p.Lam, p.K, 1.0 / p.v.N, (int64_t)b * 256 + threadIdx.x);
+    else zero_pad(p.Q, p.v.M, p.ldq, (int64_t)(b - p.nbk) * 256 + threadIdx.x);
 }
 
 }  // namespace
@@ -875,8 +1070,10 @@ int lb_impl_prepare_dense(lb_ctx* c, int N, const double* H, const double* gamma
                           double* K) {
     const int64_t M = (int64_t)N * N - 1;
     const int64_t P = lb_npairs(N);
+    const int64_t NN = (int64_t)N * N;
+    const bool fused = N <= kFuseN;
     std::vector<int2> order;
-    const int64_t norder = N >= 3 ? quad_order(N, order) : 0;
+    const int64_t norder = fused ? 0 : quad_order(N, order);
     const int nch = (N + kGthChunk - 1) / kGthChunk;
     // workspace layout
     size_t off = 0;
@@ -886,28 +1083,31 @@ int lb_impl_prepare_dense(lb_ctx* c, int N, const double* H, const double* gamma
         return o;
     };
     const size_t o_pt = take(sizeof(double) * 2 * (size_t)N * M);
-    const size_t o_cdd = take(sizeof(double) * 2 * (size_t)N * N);
-    const size_t o_z = take(sizeof(double) * 2 * (size_t)N * N);
-    const size_t o_lam = take(sizeof(double) * 2 * (size_t)N * N);
-    const size_t o_t = take(sizeof(double) * 2 * (size_t)N * N);
-    const size_t o_gp = take(sizeof(double) * 2 * 4 * (size_t)nch * N * N);  // GpA, TpA, GpC, TpC
-    const size_t o_pairs = take(sizeof(int2) * ((size_t)P + (size_t)norder) + 8);  // pairs, then the quad order
+    const size_t o_cdd = take(sizeof(double) * 2 * (size_t)NN);
+    const size_t o_z = take(sizeof(double) * 2 * (size_t)NN);
+    const size_t o_lam = take(sizeof(double) * 2 * (size_t)NN);
+    const size_t o_t = take(sizeof(double) * (size_t)NN);
+    const size_t o_gp = take(sizeof(double) * 2 * 4 * (size_t)nch * NN);  // GpA, TpA, GpC, TpC
+    const size_t o_order = take(sizeof(int2) * (size_t)norder + 8);
     int rc = lb_ws_reserve(c, off);
     if (rc) return rc;
-    rc = lb_aux_stream(c);
-    if (rc) return rc;
-    const size_t hb = sizeof(int2) * ((size_t)P + (size_t)norder);
-    rc = lb_host_reserve(c, hb);
-    if (rc) return rc;
     char* ws = (char*)c->ws;
-    int2* h = (int2*)c->host;
-    // the pinned staging buffer may still be read by an earlier copy on this stream
-    LB_HIP(hipStreamSynchronize(c->stream));
-    int64_t hp = 0;
-    for (int a = 0; a + 1 < N; ++a)
-        for (int b = a + 1; b < N; ++b) h[hp++] = make_int2(a, b);
-    for (int64_t i = 0; i < norder; ++i) h[P + i] = order[i];
-    LB_HIP(hipMemcpyAsync(ws + o_pairs, h, hb, hipMemcpyHostToDevice, c->stream));
+    hipStream_t s = c->stream;
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &cap) != hipSuccess) (void)hipGetLastError();
+    if (cap != hipStreamCaptureStatusNone)  // a recorded preparation would keep a workspace that later calls replace
+        return lb_fail(LB_ERR_DEVICE, "lindblad_prepare cannot be captured");
+    if (!fused) {
+        rc = lb_aux_stream(c);
+        if (rc) return rc;
+        const size_t hb = sizeof(int2) * (size_t)norder;
+        rc = lb_host_reserve(c, hb);
+        if (rc) return rc;
+        // the pinned staging buffer may still be read by an earlier copy on this stream
+        LB_HIP(hipStreamSynchronize(s));
+        memcpy(c->host, order.data(), hb);
+        LB_HIP(hipMemcpyAsync(ws + o_order, c->host, hb, hipMemcpyHostToDevice, s));
+    }
 
     GV v;
     v.g = gamma;
@@ -919,56 +1119,67 @@ int lb_impl_prepare_dense(lb_ctx* c, int N, const double* H, const double* gamma
     double* Zm = (double*)(ws + o_z);
     double* Lam = (double*)(ws + o_lam);
     double* T = (double*)(ws + o_t);
-    const int2* pd = (const int2*)(ws + o_pairs);
-    const int2* od = pd + P;
-    const size_t part = (size_t)2 * nch * N * N;  // doubles per partial array
-    double* GpA = (double*)(ws + o_gp);
-    double* TpA = GpA + part;
-    double* GpC = TpA + part;
-    double* TpC = GpC + part;
-    hipStream_t s = c->stream;
+    const int2* od = (const int2*)(ws + o_order);
+    const size_t part = (size_t)2 * nch * NN;  // doubles per partial array
 
-    hipLaunchKernelGGL(k_pt, dim3(lb_blocks(M, 256)), dim3(256), 0, s, v, (double*)(ws + o_pt));
+    PreArgs pre;
+    pre.v = v;
+    pre.H = H;
+    pre.Pt = (double*)(ws + o_pt);
+    pre.Cdd = (double*)(ws + o_cdd);
+    pre.GpA = (double*)(ws + o_gp);
+    pre.TpA = pre.GpA + part;
+    pre.GpC = pre.TpA + part;
+    pre.TpC = pre.GpC + part;
+    pre.Z = Zm;
+    pre.Lam = Lam;
+    pre.nch = nch;
+    pre.nbm = lb_blocks(M, 256);
+    pre.nbn = lb_blocks(NN, 256);
+    hipLaunchKernelGGL(k_pre1, dim3(pre.nbm + 2 * pre.nbn * (unsigned)nch), dim3(256), 0, s, pre);
     LB_CHECK_LAUNCH();
-    hipLaunchKernelGGL(k_cdd, dim3(lb_blocks((int64_t)N * N, 256)), dim3(256), 0, s, v, (double*)(ws + o_cdd));
+    hipLaunchKernelGGL(k_pre2, dim3(2 * pre.nbn), dim3(256), 0, s, pre);
     LB_CHECK_LAUNCH();
-    const dim3 ggrid(lb_blocks((int64_t)N * N, 256), (unsigned)nch);
-    hipLaunchKernelGGL(k_gth_a, ggrid, dim3(256), 0, s, v, GpA, TpA);
-    LB_CHECK_LAUNCH();
-    hipLaunchKernelGGL(k_gth_c, ggrid, dim3(256), 0, s, v, GpC, TpC);
-    LB_CHECK_LAUNCH();
-    hipLaunchKernelGGL(k_gth_fin, dim3(lb_blocks((int64_t)N * N, 256)), dim3(256), 0, s, v, H, (const double*)GpA,
-                       (const double*)TpA, (const double*)GpC, (const double*)TpC, nch, Zm, Lam);
-    LB_CHECK_LAUNCH();
-    hipLaunchKernelGGL(k_expand, dim3(lb_blocks(M, 256)), dim3(256), 0, s, N, 1, (const double*)Lam, K, 1.0 / N);
-    LB_CHECK_LAUNCH();
+    const unsigned nbk = lb_blocks(M, 256), npad = ldq > M ? lb_blocks(M * (ldq - M), 256) : 0;
+    if (fused) {
+        RestArgs r;
+        r.v = v;
+        r.Zm = Zm;
+        r.Lam = Lam;
+        r.Q = Q;
+        r.K = K;
+        r.ldq = ldq;
+        r.nquad = (unsigned)P;
+        r.nseg = lb_blocks(P * 64, 256);
+        r.ndv = lb_blocks(P, 16);
+        r.nbk = nbk;
+        hipLaunchKernelGGL(k_rest, dim3(r.nquad + r.ndv + 1 + r.nseg + nbk + npad), dim3(256), rest_lds(N), s, r);
+        LB_CHECK_LAUNCH();
+        return LB_OK;
+    }
     // the segments of pair rows on this stream; the shared-vertex segments, the
-    // rows and columns of the diagonal generators and the padding on the
+    // rows and columns of the diagonal generators, K and the padding on the
     // auxiliary stream, concurrently (they write other elements of Q)
     LB_HIP(hipEventRecord(c->ev_fork, s));
     LB_HIP(hipStreamWaitEvent(c->aux, c->ev_fork, 0));
     hipStream_t s2 = c->aux;
-    if (norder > 0) {
-        hipLaunchKernelGGL(k_quad, dim3((unsigned)norder), dim3(256), 0, s, v, (const double*)Zm, od, Q, ldq);
-        LB_CHECK_LAUNCH();
-    }
-    if (P > 0) {
-        hipLaunchKernelGGL(k_segpp, dim3(lb_blocks(P * 64, 256)), dim3(256), 0, s2, v, (const double*)Zm, pd, Q, ldq);
-        LB_CHECK_LAUNCH();
-        hipLaunchKernelGGL(k_drows, dim3(lb_blocks(P, 64)), dim3(64), 0, s2, v, (const double*)Zm, pd, Q, ldq);
-        LB_CHECK_LAUNCH();
-        hipLaunchKernelGGL(k_dcols, dim3(lb_blocks(P, 64)), dim3(64), 0, s2, v, (const double*)Zm, pd, Q, ldq);
-        LB_CHECK_LAUNCH();
-    }
-    hipLaunchKernelGGL(k_dd1, dim3(lb_blocks((int64_t)N * (N - 1), 64)), dim3(64), 0, s2, v, (const double*)Zm, T);
+    hipLaunchKernelGGL(k_quad, dim3((unsigned)norder), dim3(256), 0, s, v, (const double*)Zm, od, Q, ldq);
     LB_CHECK_LAUNCH();
-    hipLaunchKernelGGL(k_dd2, dim3(lb_blocks((int64_t)(N - 1) * (N - 1), 64)), dim3(64), 0, s2, v,
-                       (const double*)T, Q, ldq);
+    hipLaunchKernelGGL(k_segpp, dim3(lb_blocks(P * 64, 256)), dim3(256), 0, s2, v, (const double*)Zm, Q, ldq);
     LB_CHECK_LAUNCH();
-    if (ldq > M) {
-        hipLaunchKernelGGL(k_zero_pad, dim3(lb_blocks(M * (ldq - M), 256)), dim3(256), 0, s2, Q, M, ldq);
-        LB_CHECK_LAUNCH();
-    }
+    // pairs per workgroup of the diagonal generators' rows and columns: 16, or what
+    // fits in LDS (gamma and Q alone fill the memory at N = 330)
+    const int pb = N <= 256 ? 16 : 4;
+    const size_t dl = sizeof(double) * (4 * (size_t)N * (pb + 1) + N);
+    void (*dvec)(GV, const double*, double*, int64_t) = pb == 16 ? k_dvec<16> : k_dvec<4>;
+    hipLaunchKernelGGL(dvec, dim3(lb_blocks(P, pb)), dim3(256), dl, s2, v, (const double*)Zm, Q, ldq);
+    LB_CHECK_LAUNCH();
+    hipLaunchKernelGGL(k_dd1, dim3(N), dim3(256), sizeof(double) * N, s2, v, (const double*)Zm, T);
+    LB_CHECK_LAUNCH();
+    hipLaunchKernelGGL(k_dd2, dim3(lb_blocks(N - 1, 64)), dim3(64), 0, s2, v, (const double*)T, Q, ldq);
+    LB_CHECK_LAUNCH();
+    hipLaunchKernelGGL(k_tail, dim3(nbk + npad), dim3(256), 0, s2, v, (const double*)Lam, K, Q, ldq, nbk);
+    LB_CHECK_LAUNCH();
     LB_HIP(hipEventRecord(c->ev_join, s2));
     LB_HIP(hipStreamWaitEvent(s, c->ev_join, 0));
     return LB_OK;
