@@ -183,6 +183,22 @@ int lindblad_prepare_sparse_fill(lb_ctx* ctx, int N, const lb_csr_c128* H, int P
                                  const double* rates, const lb_csr_c128* L, int64_t nnz,
                                  int64_t* rowptr, int64_t* col, double* val, double* K);
 
+/* Where the caller wants Q and K (device; sizes as for phase 2). */
+typedef struct lb_sparse_out {
+    int64_t* rowptr;
+    int64_t* col;
+    double* val;
+    double* K;
+} lb_sparse_out;
+
+/* Both phases in one call, with the work they share done once: alloc(user, nnz,
+ * out) is called on this thread when nnz is known and no work is enqueued that
+ * uses its memory; a nonzero return ends the call with LB_ERR_OOM. It must not
+ * call into this context. Results as from the two phases. */
+typedef int (*lb_sparse_alloc)(void* user, int64_t nnz, lb_sparse_out* out);
+int lindblad_prepare_sparse(lb_ctx* ctx, int N, const lb_csr_c128* H, int P, const double* rates,
+                            const lb_csr_c128* L, lb_sparse_alloc alloc, void* user, int64_t* nnz);
+
 /* ------------------------------------------------------------------ */
 /* RK4 propagation of dv/dt = Q v + K (Eq. (10); Table 1 step 3.1)      */
 /* ------------------------------------------------------------------ */

@@ -79,6 +79,14 @@ def load():
     return lib
 
 
+class _SparseOut(ctypes.Structure):
+    _fields_ = [("rowptr", ctypes.c_void_p), ("col", ctypes.c_void_p), ("val", ctypes.c_void_p),
+                ("K", ctypes.c_void_p)]
+
+
+_SPARSE_ALLOC = ctypes.CFUNCTYPE(ctypes.c_int, ctypes.c_void_p, ctypes.c_int64, ctypes.POINTER(_SparseOut))
+
+
 def signatures():
     """ctypes argument types of every C entry point."""
     V, I, I64, D, U = ctypes.c_void_p, ctypes.c_int, ctypes.c_int64, ctypes.c_double, ctypes.c_uint
@@ -100,6 +108,7 @@ def signatures():
         "lindblad_prepare": [V, I, V, V, V, I64, V, U],
         "lindblad_prepare_sparse_count": [V, I, V, I, V, V, V],
         "lindblad_prepare_sparse_fill": [V, I, V, I, V, V, I64, V, V, V, V],
+        "lindblad_prepare_sparse": [V, I, V, I, V, V, _SPARSE_ALLOC, V, V],
         "lindblad_propagate": [V, I64, V, V, I64, V, V, I, D, I64, I],
         "lindblad_propagate_noalloc": [V, I64, V, V, I64, V, V, I, D, I64, I],
         "lindblad_q_to_f32": [V, I64, V, I64, V],
@@ -350,14 +359,27 @@ def lindblad_prepare_sparse(ctx: Context, N: int, H_csr, rates, L_csrs):
     Ls = (_CSR * max(P, 1))(*[_csr_struct(*l) for l in L_csrs])
     r = (ctypes.c_double * max(P, 1))(*[float(x) for x in rates])
     nnz = ctypes.c_int64()
-    _check(lib.lindblad_prepare_sparse_count(ctx.handle, N, ctypes.byref(Hs), P, r, Ls, ctypes.byref(nnz)))
     dev = _dev(ctx)
-    rowptr = torch.empty(M + 1, dtype=torch.int64, device=dev)
-    col = torch.empty(max(nnz.value, 1), dtype=torch.int64, device=dev)
-    val = torch.empty(max(nnz.value, 1), dtype=torch.float64, device=dev)
-    K = torch.empty(M, dtype=torch.float64, device=dev)
-    _check(lib.lindblad_prepare_sparse_fill(ctx.handle, N, ctypes.byref(Hs), P, r, Ls, nnz.value,
-                                            _ptr(rowptr), _ptr(col), _ptr(val), _ptr(K)))
+    got, error = [], []
+
+    def alloc(_, n, out):
+        try:
+            got[:] = [torch.empty(M + 1, dtype=torch.int64, device=dev),
+                      torch.empty(max(n, 1), dtype=torch.int64, device=dev),
+                      torch.empty(max(n, 1), dtype=torch.float64, device=dev),
+                      torch.empty(M, dtype=torch.float64, device=dev)]
+        except BaseException as e:  # raised again below: nothing passes through the C frames
+            error.append(e)
+            return 1
+        out[0] = _SparseOut(*[t.data_ptr() for t in got])
+        return 0
+
+    rc = lib.lindblad_prepare_sparse(ctx.handle, N, ctypes.byref(Hs), P, r, Ls, _SPARSE_ALLOC(alloc), None,
+                                     ctypes.byref(nnz))
+    if error:
+        raise error[0]
+    _check(rc)
+    rowptr, col, val, K = got
     return rowptr, col[:nnz.value], val[:nnz.value], K
 
 

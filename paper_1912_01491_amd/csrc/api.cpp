@@ -260,17 +260,24 @@ int lindblad_prepare(lb_ctx* c, int N, const double* H, const double* gamma, dou
     return lb_impl_prepare_dense(c, N, H, gamma, Q, ldq, K);
 }
 
+static int check_jumps(int P, const double* rates, const lb_csr_c128* L) {
+    if (P < 0 || (P > 0 && (!rates || !L))) return lb_fail(LB_ERR_INVALID_ARG, "bad jump-operator arguments");
+    for (int p = 0; p < P; ++p)
+        if (!(rates[p] >= 0) || !isfinite(rates[p])) return lb_fail(LB_ERR_INVALID_ARG, "rate %d must be finite and >= 0", p);
+    return LB_OK;
+}
+
 int lindblad_prepare_sparse_count(lb_ctx* c, int N, const lb_csr_c128* H, int P, const double* rates,
                                   const lb_csr_c128* L, int64_t* nnz) {
     CHECK_CTX(c);
     CHECK_N(N);
     CHECK_PTR(H);
     CHECK_PTR(nnz);
-    if (P < 0 || (P > 0 && (!rates || !L))) return lb_fail(LB_ERR_INVALID_ARG, "bad jump-operator arguments");
-    for (int p = 0; p < P; ++p)
-        if (!(rates[p] >= 0) || !isfinite(rates[p])) return lb_fail(LB_ERR_INVALID_ARG, "rate %d must be finite and >= 0", p);
-    return lb_impl_sparse(c, N, H, P, rates, L, nnz, nullptr, nullptr, nullptr, nullptr);
+    const int rc = check_jumps(P, rates, L);
+    if (rc) return rc;
+    return lb_impl_sparse(c, N, H, P, rates, L, nullptr, nullptr, nnz);
 }
+
 
 int lindblad_prepare_sparse_fill(lb_ctx* c, int N, const lb_csr_c128* H, int P, const double* rates,
                                  const lb_csr_c128* L, int64_t nnz, int64_t* rowptr, int64_t* col, double* val,
@@ -284,11 +291,50 @@ int lindblad_prepare_sparse_fill(lb_ctx* c, int N, const lb_csr_c128* H, int P, 
         CHECK_PTR(col);
         CHECK_PTR(val);
     }
-    if (P < 0 || (P > 0 && (!rates || !L))) return lb_fail(LB_ERR_INVALID_ARG, "bad jump-operator arguments");
-    for (int p = 0; p < P; ++p)
-        if (!(rates[p] >= 0) || !isfinite(rates[p])) return lb_fail(LB_ERR_INVALID_ARG, "rate %d must be finite and >= 0", p);
-    int64_t n = nnz;
-    return lb_impl_sparse(c, N, H, P, rates, L, &n, rowptr, col, val, K);
+    const int rc = check_jumps(P, rates, L);
+    if (rc) return rc;
+    struct Given {
+        int64_t nnz;
+        lb_sparse_out out;
+    } given = {nnz, {rowptr, col, val, K}};
+    auto place = [](void* user, int64_t total, lb_sparse_out* out) -> int {
+        const Given& g = *(const Given*)user;
+        if (total != g.nnz)
+            return lb_fail(LB_ERR_INVALID_ARG, "nnz=%lld does not match the count phase (%lld)", (long long)g.nnz,
+                           (long long)total);
+        *out = g.out;
+        return LB_OK;
+    };
+    int64_t n = 0;
+    return lb_impl_sparse(c, N, H, P, rates, L, place, &given, &n);
+}
+
+int lindblad_prepare_sparse(lb_ctx* c, int N, const lb_csr_c128* H, int P, const double* rates, const lb_csr_c128* L,
+                            lb_sparse_alloc alloc, void* user, int64_t* nnz) {
+    CHECK_CTX(c);
+    CHECK_N(N);
+    CHECK_PTR(H);
+    CHECK_PTR(alloc);
+    CHECK_PTR(nnz);
+    const int rc = check_jumps(P, rates, L);
+    if (rc) return rc;
+    struct Asked {
+        lb_sparse_alloc alloc;
+        void* user;
+    } asked = {alloc, user};
+    auto place = [](void* u, int64_t total, lb_sparse_out* out) -> int {
+        const Asked& a = *(const Asked*)u;
+        if (a.alloc(a.user, total, out))
+            return lb_fail(LB_ERR_OOM, "the caller has no memory for %lld entries", (long long)total);
+        CHECK_PTR(out->rowptr);
+        CHECK_PTR(out->K);
+        if (total > 0) {
+            CHECK_PTR(out->col);
+            CHECK_PTR(out->val);
+        }
+        return LB_OK;
+    };
+    return lb_impl_sparse(c, N, H, P, rates, L, place, &asked, nnz);
 }
 
 static int check_prop(int64_t M, int64_t ldq, int B, double dt, int64_t steps, int precision) {

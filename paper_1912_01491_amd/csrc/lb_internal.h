@@ -198,9 +198,10 @@ int lb_impl_prepare_dense(lb_ctx* c, int N, const double* H, const double* gamma
                           int64_t ldq, double* K);
 int lb_impl_hermitian_check(lb_ctx* c, int64_t n, const double* A, double* maxdev, double* maxabs);
 
+// Counts the entries of Q, then asks alloc for its arrays and fills them; alloc
+// returns an error code (negative) and may be null (count only).
 int lb_impl_sparse(lb_ctx* c, int N, const lb_csr_c128* H, int P, const double* rates,
-                   const lb_csr_c128* L, int64_t* nnz, int64_t* rowptr, int64_t* col, double* val,
-                   double* K);
+                   const lb_csr_c128* L, lb_sparse_alloc alloc, void* user, int64_t* nnz);
 
 struct lb_prop_sys {
     const double* Q;

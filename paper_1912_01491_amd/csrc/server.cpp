@@ -239,18 +239,19 @@ static int run_batch(lb_server* s, int slot, std::vector<Ticket*>& batch) {
     } else {
         const lb_request& r = r0;
         int64_t nnz = 0;
-        if (!rc) rc = lb_impl_sparse(c, N, &r.Hs, r.P, r.rates, r.L, &nnz, nullptr, nullptr, nullptr, nullptr);
-        void *rp = nullptr, *col = nullptr, *val = nullptr, *K = nullptr;
-        if (!rc) rc = dalloc(sizeof(int64_t) * (M + 1), &rp);
-        if (!rc) rc = dalloc(sizeof(int64_t) * (nnz > 0 ? nnz : 1), &col);
-        if (!rc) rc = dalloc(sizeof(double) * (nnz > 0 ? nnz : 1), &val);
-        if (!rc) rc = dalloc(sizeof(double) * M, &K);
+        lb_sparse_out q = {};
+        auto place = [&](int64_t n, lb_sparse_out* o) -> int {
+            int e = dalloc(sizeof(int64_t) * (M + 1), (void**)&o->rowptr);
+            if (!e) e = dalloc(sizeof(int64_t) * (n > 0 ? n : 1), (void**)&o->col);
+            if (!e) e = dalloc(sizeof(double) * (n > 0 ? n : 1), (void**)&o->val);
+            if (!e) e = dalloc(sizeof(double) * M, (void**)&o->K);
+            q = *o;
+            return e;
+        };
+        auto call = [](void* u, int64_t n, lb_sparse_out* o) -> int { return (*(decltype(place)*)u)(n, o); };
+        if (!rc) rc = lb_impl_sparse(c, N, &r.Hs, r.P, r.rates, r.L, call, &place, &nnz);
         if (!rc)
-            rc = lb_impl_sparse(c, N, &r.Hs, r.P, r.rates, r.L, &nnz, (int64_t*)rp, (int64_t*)col, (double*)val,
-                                (double*)K);
-        if (!rc)
-            rc = lb_impl_propagate_csr(c, M, (const int64_t*)rp, (const int64_t*)col, (const double*)val,
-                                       (const double*)K, X[0], Brun, r.dt, r.steps);
+            rc = lb_impl_propagate_csr(c, M, q.rowptr, q.col, q.val, q.K, X[0], Brun, r.dt, r.steps);
     }
     for (size_t i = 0; i < batch.size() && !rc; ++i) {
         const lb_request& r = batch[i]->req;
@@ -395,7 +396,7 @@ int lindblad_server_register(lb_server* s, const lb_request* r, int64_t* system)
         y->bytes = sizeof(double) * ((size_t)M * y->ldq + M) +
                    (y->precision == LB_FP32 ? sizeof(float) * (size_t)M * y->ldq : 0);
     } else {
-        rc = lb_impl_sparse(c, r->N, &r->Hs, r->P, r->rates, r->L, &y->nnz, nullptr, nullptr, nullptr, nullptr);
+        rc = lb_impl_sparse(c, r->N, &r->Hs, r->P, r->rates, r->L, nullptr, nullptr, &y->nnz);
         if (rc) {
             delete y;
             return rc;
@@ -429,8 +430,8 @@ int lindblad_server_register(lb_server* s, const lb_request* r, int64_t* system)
         if (!rc) rc = dalloc(sizeof(double) * (size_t)std::max<int64_t>(y->nnz, 1), &y->val);
         if (!rc) rc = dalloc(sizeof(double) * M, &y->K);
         if (!rc)
-            rc = lb_impl_sparse(c, r->N, &r->Hs, r->P, r->rates, r->L, &y->nnz, (int64_t*)y->rp, (int64_t*)y->col,
-                                (double*)y->val, (double*)y->K);
+            rc = lindblad_prepare_sparse_fill(c, r->N, &r->Hs, r->P, r->rates, r->L, y->nnz, (int64_t*)y->rp,
+                                              (int64_t*)y->col, (double*)y->val, (double*)y->K);
     }
     hipError_t e = hipStreamSynchronize(st);
     if (!rc && e != hipSuccess) rc = lb_fail(LB_ERR_DEVICE, "registration stream: %s", hipGetErrorString(e));

@@ -17,8 +17,8 @@
 // Hamiltonian (H += (i g_p/2)(conj(c) L0 - c L0^+), L0 = L_p - c 1), because
 // the generator basis has no identity element.
 //
-// Pipeline (count phase and fill phase run the same kernels; the fill phase
-// additionally writes columns and values):
+// Pipeline (a count ends before the last step, where a fill knows the number of
+// entries and asks for the arrays, then writes columns and values):
 //   densify H, L_p -> trace shift -> G = sum_p g_p L0^+ L0, A = i H - G/2
 //   column lists of A and L0_p, row lists of L0_p (ELL, width = max degree)
 //   pair rows:   one thread per row, the entries of L^+(F_s) in LDS, sorted in
@@ -29,7 +29,8 @@
 // The stored entries (7.5 M for the N = 1000 dimer) are written in a fraction
 // of a millisecond; what the phases cost is the latency of many small steps, so
 // every loop over N or M runs across lanes and the scans stay on the device.
-// N = 1000 dimer, both phases: 14.9 ms before, 0.97 ms now.
+// N = 1000 dimer: 14.9 ms before, 0.97 ms as two calls (a count, and a fill that
+// has to count again), 0.58 ms as one.
 // Rows are written with sorted column indices (S block, J block, D block);
 // entries whose value is exactly zero are not stored.
 #include "lb_internal.h"
@@ -747,8 +748,7 @@ __global__ __launch_bounds__(64 * kDrowWaves) void k_drows_sparse(DRowArgs g, in
 // Returns LB_OK, a negative status, or 1 when the workspace must grow to *want
 // bytes first (growing reallocates it, so the caller restarts from the top).
 static int sparse_body(lb_ctx* c, int N, const lb_csr_c128* H, int P, const double* rates, const lb_csr_c128* L,
-                       int64_t* nnz, int64_t* rowptr, int64_t* col, double* val, double* K, size_t* want) {
-    const bool fill = rowptr != nullptr;
+                       lb_sparse_alloc alloc, void* user, int64_t* nnz, size_t* want) {
     hipStream_t s = c->stream;
     const int64_t M = (int64_t)N * N - 1;
     const int64_t Pp = lb_npairs(N);
@@ -899,10 +899,10 @@ static int sparse_body(lb_ctx* c, int N, const lb_csr_c128* H, int P, const doub
     pa.ells = dells;
     pa.rates = drates;
     pa.cnt = rowcnt;
-    pa.rowptr = rowptr;
-    pa.col = col;
-    pa.val = val;
-    pa.K = K;
+    pa.rowptr = nullptr;
+    pa.col = nullptr;
+    pa.val = nullptr;
+    pa.K = nullptr;
     pa.overflow = ovf;
     void (*pair_rows)(PairArgs, int) = bound <= 16   ? k_pair_rows<16>
                                          : bound <= 24 ? k_pair_rows<24>
@@ -955,10 +955,10 @@ static int sparse_body(lb_ctx* c, int N, const lb_csr_c128* H, int P, const doub
     dr.pref = (const double*)(ws + o_pref);
     dr.l1diag = l1;
     dr.cnt = rowcnt;
-    dr.rowptr = rowptr;
-    dr.col = col;
-    dr.qv = val;
-    dr.K = K;
+    dr.rowptr = nullptr;
+    dr.col = nullptr;
+    dr.qv = nullptr;
+    dr.K = nullptr;
     hipLaunchKernelGGL(k_drows_sparse, dim3(N - 1), dim3(64 * kDrowWaves), 0, s, dr, 0);
     LB_CHECK_LAUNCH();
     rc = scan_counts(s, M, rowcnt, rowcnt, nullptr, scratch, tot + 2);
@@ -966,15 +966,16 @@ static int sparse_body(lb_ctx* c, int N, const lb_csr_c128* H, int P, const doub
     LB_HIP(hipMemcpyAsync(host, tot, info_bytes, hipMemcpyDeviceToHost, s));
     LB_HIP(hipStreamSynchronize(s));
     if (hovf[0] || hovf[1]) return lb_fail(LB_ERR_UNSUPPORTED, "sparse row buffer overflow (degrees too large)");
-    const int64_t total = htot[2];
-    if (!fill) {
-        *nnz = total;
-        return LB_OK;
-    }
-    if (total != *nnz)
-        return lb_fail(LB_ERR_INVALID_ARG, "nnz=%lld does not match the count phase (%lld)", (long long)*nnz,
-                       (long long)total);
-    LB_HIP(hipMemcpyAsync(rowptr, rowcnt, sizeof(int64_t) * (M + 1), hipMemcpyDeviceToDevice, s));
+    *nnz = htot[2];
+    if (!alloc) return LB_OK;
+    lb_sparse_out out = {};
+    rc = alloc(user, *nnz, &out);
+    if (rc) return rc;
+    dr.rowptr = pa.rowptr = out.rowptr;
+    dr.col = pa.col = out.col;
+    dr.qv = pa.val = out.val;
+    dr.K = pa.K = out.K;
+    LB_HIP(hipMemcpyAsync(out.rowptr, rowcnt, sizeof(int64_t) * (M + 1), hipMemcpyDeviceToDevice, s));
     hipLaunchKernelGGL(pair_rows, dim3(lb_blocks(2 * Pp, 64)), dim3(64), pair_lds, s, pa, 1);
     LB_CHECK_LAUNCH();
     hipLaunchKernelGGL(k_drows_sparse, dim3(N - 1), dim3(64 * kDrowWaves), sizeof(double) * N, s, dr, 1);
@@ -983,14 +984,14 @@ static int sparse_body(lb_ctx* c, int N, const lb_csr_c128* H, int P, const doub
 }
 
 int lb_impl_sparse(lb_ctx* c, int N, const lb_csr_c128* H, int P, const double* rates, const lb_csr_c128* L,
-                   int64_t* nnz, int64_t* rowptr, int64_t* col, double* val, double* K) {
+                   lb_sparse_alloc alloc, void* user, int64_t* nnz) {
     size_t want = 0;
     for (int attempt = 0; attempt < 4; ++attempt) {
         if (want) {
             int rc = lb_ws_reserve(c, want);
             if (rc) return rc;
         }
-        int rc = sparse_body(c, N, H, P, rates, L, nnz, rowptr, col, val, K, &want);
+        int rc = sparse_body(c, N, H, P, rates, L, alloc, user, nnz, &want);
         if (rc != 1) return rc;
     }
     return lb_fail(LB_ERR_OOM, "sparse workspace sizing did not converge");
