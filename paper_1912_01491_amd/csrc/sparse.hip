@@ -30,7 +30,8 @@
 // of a millisecond; what the phases cost is the latency of many small steps, so
 // every loop over N or M runs across lanes and the scans stay on the device.
 // N = 1000 dimer: 14.9 ms before, 0.97 ms as two calls (a count, and a fill that
-// has to count again), 0.58 ms as one.
+// has to count again), 0.58 ms as one, 0.51 ms with the pair rows' counts beside the
+// diagonals' lists and the two fills beside each other on a second stream.
 // Rows are written with sorted column indices (S block, J block, D block);
 // entries whose value is exactly zero are not stored.
 #include "lb_internal.h"
@@ -85,8 +86,8 @@ __global__ __launch_bounds__(64) void k_densify(int N, const int64_t* rowptr, co
     }
 }
 
-// single block: c_p = Tr(L_p)/N for all p
-__global__ void k_traces(int N, int P, const double* Ld, double* c) {
+// single block: c_p = Tr(L_p)/N for all p, and L0_p = L_p - c_p 1 in place
+__global__ void k_shift_l(int N, int P, double* Ld, double* c) {
     __shared__ double sr[256], si[256];
     for (int p = 0; p < P; ++p) {
         double r = 0, i = 0;
@@ -105,21 +106,13 @@ __global__ void k_traces(int N, int P, const double* Ld, double* c) {
             }
             __syncthreads();
         }
-        if (threadIdx.x == 0) {
-            c[2 * p] = sr[0] / N;
-            c[2 * p + 1] = si[0] / N;
-        }
+        const cd t = cmk(sr[0] / N, si[0] / N);
+        if (threadIdx.x == 0) cstore(c, p, t);
+        double* L = Ld + 2 * (int64_t)p * N * N;
+        for (int x = threadIdx.x; x < N; x += blockDim.x)
+            cstore(L, (int64_t)x * N + x, csub(cload(L, (int64_t)x * N + x), t));
         __syncthreads();
     }
-}
-
-// L0_p = L_p - c_p 1 (in place)
-__global__ void k_shift_l(int N, int P, double* Ld, const double* c) {
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= (int64_t)P * N) return;
-    const int p = (int)(t / N), x = (int)(t % N);
-    double* L = Ld + 2 * (int64_t)p * N * N;
-    cstore(L, (int64_t)x * N + x, csub(cload(L, (int64_t)x * N + x), cmk(c[2 * p], c[2 * p + 1])));
 }
 
 // H += sum_p (i g_p / 2)(conj(c_p) L0 - c_p L0^+);  G = sum_p g_p L0^+ L0;  A = i H - G/2.
@@ -524,8 +517,7 @@ struct DAcc {
     }
 };
 
-__global__ void k_diag_pairs(DiagArgs g, int fill, int* ovf) {
-    const int64_t nidx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+__device__ __forceinline__ void diag_pair(const DiagArgs& g, int64_t nidx, int fill, int* ovf) {
     if (nidx >= 2 * g.Pp) return;
     const int N = g.N;
     const int cls = nidx >= g.Pp ? 1 : 0;
@@ -569,9 +561,7 @@ __global__ void k_diag_pairs(DiagArgs g, int fill, int* ovf) {
 
 // D columns n = D^m': diag_a = w_m'(a) 2 Re Z_aa + sum_p g_p sum_{y <= m'} w_m'(y) |L0_p,ay|^2,
 // one wavefront per column, lanes along a (a ballot keeps the positions in order).
-__global__ __launch_bounds__(256) void k_diag_dcols(DiagArgs g, int fill) {
-    const int lane = threadIdx.x & 63;
-    const int mm = blockIdx.x * 4 + (threadIdx.x >> 6) + 1;
+__device__ __forceinline__ void diag_dcol(const DiagArgs& g, int mm, int lane, int fill) {
     const int N = g.N;
     if (mm >= N) return;
     const int64_t nidx = 2 * g.Pp + mm - 1;
@@ -608,6 +598,14 @@ __global__ __launch_bounds__(256) void k_diag_dcols(DiagArgs g, int fill) {
         n += __popcll(m);
     }
     if (!fill && lane == 0) g.cnt[nidx] = n;
+}
+
+// The N - 1 columns of diagonal generators, four to a block, then those of the
+// pairs, 256 to a block: two independent chains of latency side by side (one
+// after the other 43 us at N = 1000).
+__global__ __launch_bounds__(256) void k_diag(DiagArgs g, unsigned nd, int fill, int* ovf) {
+    if (blockIdx.x < nd) diag_dcol(g, (int)(blockIdx.x * 4 + (threadIdx.x >> 6)) + 1, threadIdx.x & 63, fill);
+    else diag_pair(g, (int64_t)(blockIdx.x - nd) * 256 + threadIdx.x, fill, ovf);
 }
 
 // D rows: Q[D^m][n] = sum_x w_m(x) diag_n(x) = (pre_n(m) - m diag_n(m)) / sqrt(m(m+1)),
@@ -745,6 +743,30 @@ __global__ __launch_bounds__(64 * kDrowWaves) void k_drows_sparse(DRowArgs g, in
 
 }  // namespace
 
+// Work on the context's second stream between fork() and join(). A return in
+// between (an error, a workspace to be grown) waits for it: it uses the workspace.
+struct AuxWork {
+    lb_ctx* c;
+    bool open = false;
+    explicit AuxWork(lb_ctx* c) : c(c) {}
+    AuxWork(const AuxWork&) = delete;
+    ~AuxWork() {
+        if (open) (void)hipStreamSynchronize(c->aux);
+    }
+    int fork() {
+        LB_HIP(hipEventRecord(c->ev_fork, c->stream));
+        LB_HIP(hipStreamWaitEvent(c->aux, c->ev_fork, 0));
+        open = true;
+        return LB_OK;
+    }
+    int join() {
+        LB_HIP(hipEventRecord(c->ev_join, c->aux));
+        LB_HIP(hipStreamWaitEvent(c->stream, c->ev_join, 0));
+        open = false;
+        return LB_OK;
+    }
+};
+
 // Returns LB_OK, a negative status, or 1 when the workspace must grow to *want
 // bytes first (growing reallocates it, so the caller restarts from the top).
 static int sparse_body(lb_ctx* c, int N, const lb_csr_c128* H, int P, const double* rates, const lb_csr_c128* L,
@@ -817,10 +839,7 @@ static int sparse_body(lb_ctx* c, int N, const lb_csr_c128* H, int P, const doub
         LB_CHECK_LAUNCH();
     }
     if (P > 0) {
-        hipLaunchKernelGGL(k_traces, dim3(1), dim3(256), 0, s, N, P, (const double*)Ld, cvec);
-        LB_CHECK_LAUNCH();
-        hipLaunchKernelGGL(k_shift_l, dim3(lb_blocks((int64_t)P * N, 256)), dim3(256), 0, s, N, P, Ld,
-                           (const double*)cvec);
+        hipLaunchKernelGGL(k_shift_l, dim3(1), dim3(256), 0, s, N, P, Ld, cvec);
         LB_CHECK_LAUNCH();
     }
     hipLaunchKernelGGL(k_heff_a, dim3(N), dim3(256), (sizeof(double2) + sizeof(int)) * N, s, N, P,
@@ -883,14 +902,8 @@ static int sparse_body(lb_ctx* c, int N, const lb_csr_c128* H, int P, const doub
     da.off = dcnt;
     da.pos = nullptr;
     da.val = nullptr;
-    hipLaunchKernelGGL(k_diag_pairs, dim3(lb_blocks(2 * Pp, 128)), dim3(128), 0, s, da, 0, ovf + 1);
-    LB_CHECK_LAUNCH();
-    hipLaunchKernelGGL(k_diag_dcols, dim3(lb_blocks(N - 1, 4)), dim3(256), 0, s, da, 0);
-    LB_CHECK_LAUNCH();
-    rc = scan_counts(s, M, dcnt, dcnt, carry, scratch, tot);
-    if (rc) return rc;
-
-    // row counts of the pair rows (they do not need the lists)
+    // row counts of the pair rows, which do not need the diagonals' lists, beside
+    // the lists' set-up
     PairArgs pa;
     pa.N = N;
     pa.P = P;
@@ -909,9 +922,19 @@ static int sparse_body(lb_ctx* c, int N, const lb_csr_c128* H, int P, const doub
                                          : bound <= 40 ? k_pair_rows<40>
                                                        : k_pair_rows<64>;
     const size_t pair_lds = (size_t)64 * pa.bound * (sizeof(double2) + sizeof(uint32_t));
-    hipLaunchKernelGGL(pair_rows, dim3(lb_blocks(2 * Pp, 64)), dim3(64), pair_lds, s, pa, 0);
+    rc = lb_aux_stream(c);
+    if (rc) return rc;
+    AuxWork aux(c);
+    rc = aux.fork();
+    if (rc) return rc;
+    hipLaunchKernelGGL(pair_rows, dim3(lb_blocks(2 * Pp, 64)), dim3(64), pair_lds, c->aux, pa, 0);
     LB_CHECK_LAUNCH();
 
+    const unsigned nd = lb_blocks(N - 1, 4), ndiag = nd + lb_blocks(2 * Pp, 256);
+    hipLaunchKernelGGL(k_diag, dim3(ndiag), dim3(256), 0, s, da, nd, 0, ovf + 1);
+    LB_CHECK_LAUNCH();
+    rc = scan_counts(s, M, dcnt, dcnt, carry, scratch, tot);
+    if (rc) return rc;
     LB_HIP(hipMemcpyAsync(host, tot, info_bytes, hipMemcpyDeviceToHost, s));
     LB_HIP(hipStreamSynchronize(s));
     const int64_t dtotal = htot[0], ncarry = htot[1];
@@ -930,9 +953,7 @@ static int sparse_body(lb_ctx* c, int N, const lb_csr_c128* H, int P, const doub
     }
     da.pos = (int*)(ws + o_pos);
     da.val = (double*)(ws + o_dval);
-    hipLaunchKernelGGL(k_diag_pairs, dim3(lb_blocks(2 * Pp, 128)), dim3(128), 0, s, da, 1, ovf + 1);
-    LB_CHECK_LAUNCH();
-    hipLaunchKernelGGL(k_diag_dcols, dim3(lb_blocks(N - 1, 4)), dim3(256), 0, s, da, 1);
+    hipLaunchKernelGGL(k_diag, dim3(ndiag), dim3(256), 0, s, da, nd, 1, ovf + 1);
     LB_CHECK_LAUNCH();
     {
         // every diagonal generator's column carries (its list starts at position 0), after those of the pairs
@@ -961,6 +982,8 @@ static int sparse_body(lb_ctx* c, int N, const lb_csr_c128* H, int P, const doub
     dr.K = nullptr;
     hipLaunchKernelGGL(k_drows_sparse, dim3(N - 1), dim3(64 * kDrowWaves), 0, s, dr, 0);
     LB_CHECK_LAUNCH();
+    rc = aux.join();
+    if (rc) return rc;
     rc = scan_counts(s, M, rowcnt, rowcnt, nullptr, scratch, tot + 2);
     if (rc) return rc;
     LB_HIP(hipMemcpyAsync(host, tot, info_bytes, hipMemcpyDeviceToHost, s));
@@ -976,11 +999,13 @@ static int sparse_body(lb_ctx* c, int N, const lb_csr_c128* H, int P, const doub
     dr.qv = pa.val = out.val;
     dr.K = pa.K = out.K;
     LB_HIP(hipMemcpyAsync(out.rowptr, rowcnt, sizeof(int64_t) * (M + 1), hipMemcpyDeviceToDevice, s));
+    rc = aux.fork();
+    if (rc) return rc;
+    hipLaunchKernelGGL(k_drows_sparse, dim3(N - 1), dim3(64 * kDrowWaves), sizeof(double) * N, c->aux, dr, 1);
+    LB_CHECK_LAUNCH();
     hipLaunchKernelGGL(pair_rows, dim3(lb_blocks(2 * Pp, 64)), dim3(64), pair_lds, s, pa, 1);
     LB_CHECK_LAUNCH();
-    hipLaunchKernelGGL(k_drows_sparse, dim3(N - 1), dim3(64 * kDrowWaves), sizeof(double) * N, s, dr, 1);
-    LB_CHECK_LAUNCH();
-    return LB_OK;
+    return aux.join();
 }
 
 int lb_impl_sparse(lb_ctx* c, int N, const lb_csr_c128* H, int P, const double* rates, const lb_csr_c128* L,
