@@ -709,7 +709,7 @@ __global__ void k_unpack(double* const* Vu, int64_t M, int B, int Bp, const doub
 // One state: GEMV with the stage combine fused in (rows are complete per wave).
 // A wave owns R rows; lanes read 16 bytes each along the row, so one load
 // instruction covers 1 KB of a row (full lines when rows are 128-byte aligned,
-// then read with the nontemporal hint: Q is streamed once per stage). A row's
+// then read with the nontemporal hint where Q exceeds the last-level cache). A row's
 // sum does not depend on R, so R only trades waves for loads in flight.
 // ---------------------------------------------------------------------------
 template <int R, bool ALIGNED, bool NT>
@@ -1227,12 +1227,17 @@ static int plan_gemm(const Plan& p, hipStream_t s, int stage, double dt) {
         const int64_t rows_total = p.M * p.R;
         const int RW = rows_total >= 8 * 8192 ? 8 : rows_total >= 4 * 8192 ? 4 : rows_total >= 2 * 8192 ? 2 : 1;
         const unsigned gx = lb_blocks((p.M + RW - 1) / RW, 4);
+        // The nontemporal hint pays once the systems' Q no longer fit the last-level
+        // cache (256 MB), where a stage evicts what the next one reads first. One
+        // stage with and without it: N = 70 (192 MB) 33.0 and 29.8 us, N = 75
+        // (253 MB) 43.2 and 38.1, N = 80 (328 MB) 56.3 and 59.6.
+        const bool streamed = (size_t)p.R * p.M * p.ldq * sizeof(double) > (256u << 20);
         typedef void (*gemv_fn)(const double* const*, const double* const*, double* const*, int64_t, int64_t,
                                 double*, int64_t, int, double);
         gemv_fn fn;
         if (!p.aligned) fn = RW == 8 ? k_gemv<8, false, false> : RW == 4 ? k_gemv<4, false, false>
                            : RW == 2 ? k_gemv<2, false, false> : k_gemv<1, false, false>;
-        else if (p.staged) fn = RW == 8 ? k_gemv<8, true, true> : RW == 4 ? k_gemv<4, true, true>
+        else if (p.staged && streamed) fn = RW == 8 ? k_gemv<8, true, true> : RW == 4 ? k_gemv<4, true, true>
                               : RW == 2 ? k_gemv<2, true, true> : k_gemv<1, true, true>;
         else fn = RW == 8 ? k_gemv<8, true, false> : RW == 4 ? k_gemv<4, true, false>
                 : RW == 2 ? k_gemv<2, true, false> : k_gemv<1, true, false>;
