@@ -119,8 +119,8 @@ __device__ __forceinline__ cd ecoef(int Y, double s, cd v) { return Y == 0 ? csc
 // Pt[a][k] = sum_l w_l(a) gamma[D^l][k]: w_l(a) = 1/sqrt(l(l+1)) for l > a,
 // -a/sqrt(a(a+1)) for l = a, 0 otherwise -> a suffix sum over l per column k,
 // with the loads of eight l ahead of their sums (one at a time the chain waited
-// for each load).
-__device__ __forceinline__ void pt_column(const GV& v, double* Pt, int64_t k) {
+// for each load). nrm[l] = 1/sqrt(l(l+1)), nrm[0] = 0 (see diag_norms).
+__device__ __forceinline__ void pt_column(const GV& v, double* Pt, int64_t k, const double* nrm) {
     if (k >= v.M) return;
     const int N = v.N;
     const int64_t D0 = 2 * v.P - 1;  // row of D^l is D0 + l
@@ -135,30 +135,33 @@ __device__ __forceinline__ void pt_column(const GV& v, double* Pt, int64_t k) {
             if (a < 0) break;
             cd val = S;
             if (a >= 1) {
-                const double nrm = 1.0 / sqrt((double)a * (a + 1));
-                val = cadd(val, cscale(g[i], -(double)a * nrm));
-                S = cadd(S, cscale(g[i], nrm));
+                val = cadd(val, cscale(g[i], -(double)a * nrm[a]));
+                S = cadd(S, cscale(g[i], nrm[a]));
             }
             cstore(Pt, (int64_t)a * v.M + k, val);
         }
     }
 }
 
-// Cdd[a][c] = sum_l' Pt[a][D^l'] w_l'(c)
-__device__ __forceinline__ cd cdd_elem(const GV& v, int a, int c) {
+// Cdd[a][c] = sum_l' Pt[a][D^l'] w_l'(c), eight loads ahead of their sums.
+__device__ __forceinline__ cd cdd_elem(const GV& v, int a, int c, const double* nrm) {
     const int64_t D0 = 2 * v.P - 1;
     const double* row = v.Pt + 2 * ((int64_t)a * v.M + D0);
-    cd s = cmk(0, 0);
-    int l = c > 1 ? c : 1;
-    for (; l + 4 <= v.N; l += 4) {
-        cd x[4];
+    cd s = c > 0 ? cscale(cload(row, c), -(double)c * nrm[c]) : cmk(0, 0);
+    for (int l = c + 1; l < v.N; l += 8) {
+        cd x[8];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) x[i] = cload(row, l + i);
+        for (int i = 0; i < 8; ++i) x[i] = l + i < v.N ? cload(row, l + i) : cmk(0, 0);
 #pragma unroll
-        for (int i = 0; i < 4; ++i) s = cadd(s, cscale(x[i], lb_wdiag(l + i, c)));
+        for (int i = 0; i < 8; ++i)
+            if (l + i < v.N) s = cadd(s, cscale(x[i], nrm[l + i]));
     }
-    for (; l < v.N; ++l) s = cadd(s, cscale(cload(row, l), lb_wdiag(l, c)));
     return s;
+}
+
+// The diagonal generators' norms into N doubles of LDS, by the whole workgroup.
+__device__ __forceinline__ void diag_norms(double* nrm, int N) {
+    for (int m = threadIdx.x; m < N; m += blockDim.x) nrm[m] = m ? 1.0 / sqrt((double)m * (m + 1)) : 0.0;
 }
 
 // ---------------------------------------------------------------------------
@@ -247,7 +250,9 @@ __device__ __forceinline__ void pp_store_plain(double* Q, int64_t ldq, int64_t P
 // gth_a (lanes along a) takes the first and last ranges, gth_c (lanes along
 // c) the middle one; both split b into chunks of kGthChunk and write one partial
 // sum per chunk; gth_fin adds the chunks in order of b, then the b = a and
-// b = c terms. Partial layout: Gp[k][a][c] (G_ac), Tp[k][x][y] (Theta_xy).
+// b = c terms. G and Theta are Hermitian, as gamma is, so a <= c is enough: half
+// of the blocks (all of them: k_pre1 79 us at N = 100, now 56; 436 us at N = 200,
+// now 260). Partial layout: Gp[k][a][c] (G_ac), Tp[k][a][c] (Theta_ca).
 constexpr int kGthChunk = 8;
 
 __device__ __forceinline__ void gth_add(cd& g, cd& th, const Blk& B, int a, int b, int c) {
@@ -260,8 +265,8 @@ __device__ __forceinline__ void gth_a(const GV& v, double* Gp, double* Tp, int64
     const int64_t NN = (int64_t)N * N;
     if (t >= NN) return;
     const int a = (int)(t % N), c = (int)(t / N);
+    if (a > c) return;
     const int b0 = k * kGthChunk, b1 = min(N, b0 + kGthChunk);
-    const int hi = a > c ? a : c;
     cd g = cmk(0, 0), th = cmk(0, 0);
     for (int b4 = b0; b4 < b1; b4 += 4) {  // four blocks on their way at once
         Blk B[4];
@@ -269,7 +274,7 @@ __device__ __forceinline__ void gth_a(const GV& v, double* Gp, double* Tp, int64
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             const int b = b4 + i;
-            use[i] = b < b1 && b != a && b != c && !(b > a && b < hi);
+            use[i] = b < b1 && b != a && b != c && !(b > a && b < c);
             B[i] = use[i] ? blk_load(v, lb_upair(N, b, c), lb_upair(N, a, b)) : Blk{};
         }
 #pragma unroll
@@ -277,7 +282,7 @@ __device__ __forceinline__ void gth_a(const GV& v, double* Gp, double* Tp, int64
             if (use[i]) gth_add(g, th, B[i], a, b4 + i, c);
     }
     cstore(Gp, (int64_t)k * NN + (int64_t)a * N + c, g);
-    cstore(Tp, (int64_t)k * NN + (int64_t)c * N + a, th);
+    cstore(Tp, (int64_t)k * NN + (int64_t)a * N + c, th);
 }
 
 __device__ __forceinline__ void gth_c(const GV& v, double* Gp, double* Tp, int64_t t, int k) {
@@ -285,6 +290,7 @@ __device__ __forceinline__ void gth_c(const GV& v, double* Gp, double* Tp, int64
     const int64_t NN = (int64_t)N * N;
     if (t >= NN) return;
     const int c = (int)(t % N), a = (int)(t / N);
+    if (a > c) return;
     const int k0 = k * kGthChunk;
     const int b0 = max(k0, a + 1), b1 = min(min(N, k0 + kGthChunk), c);
     cd g = cmk(0, 0), th = cmk(0, 0);
@@ -292,24 +298,27 @@ __device__ __forceinline__ void gth_c(const GV& v, double* Gp, double* Tp, int64
     for (int b = b0; b < b1; ++b)
         gth_add(g, th, blk_t(blk_load(v, lb_pair(N, a, b), lb_pair(N, b, c))), a, b, c);
     cstore(Gp, (int64_t)k * NN + (int64_t)a * N + c, g);
-    cstore(Tp, (int64_t)k * NN + (int64_t)c * N + a, th);
+    cstore(Tp, (int64_t)k * NN + (int64_t)a * N + c, th);
 }
 
 // Z = -iH - G/2 and Lambda = Theta - G = L(1).
 __device__ __forceinline__ void gth_fin(const GV& v, const double* H, const double* GpA, const double* TpA,
                                         const double* GpC, const double* TpC, int nch, double* Z, double* Lam,
-                                        int64_t t) {
+                                        int64_t t, const double* nrm) {
     const int N = v.N;
     const int64_t NN = (int64_t)N * N;
     if (t >= NN) return;
     const int a = (int)(t / N), c = (int)(t % N);
-    cd G = cmk(0, 0), Th = cmk(0, 0);
+    if (a > c) return;
+    cd G = cmk(0, 0), Th = cmk(0, 0);  // G_ac and Theta_ca, then Theta_ac
+#pragma unroll 4
     for (int k = 0; k < nch; ++k) {
         G = cadd(G, cadd(cload(GpA, k * NN + t), cload(GpC, k * NN + t)));
         Th = cadd(Th, cadd(cload(TpA, k * NN + t), cload(TpC, k * NN + t)));
     }
+    Th = cconj(Th);
     if (a == c) {
-        const cd d = cdd_elem(v, a, a);  // C(a,a,a,a); the table is being written by this launch
+        const cd d = cdd_elem(v, a, a, nrm);  // C(a,a,a,a); the table is being written by this launch
         G = cadd(G, d);
         Th = cadd(Th, d);
     } else {
@@ -318,15 +327,20 @@ __device__ __forceinline__ void gth_fin(const GV& v, const double* H, const doub
         Th = cadd(Th, chat(v, a, a, a, c));  // b = a
         Th = cadd(Th, chat(v, a, c, c, c));  // b = c
     }
-    const cd h = cload(H, t);
-    cstore(Z, t, cmk(h.im - 0.5 * G.re, -h.re - 0.5 * G.im));
-    cstore(Lam, t, csub(Th, G));
+    const cd L = csub(Th, G);
+    auto put = [&](int64_t e, cd g, cd l) {
+        const cd h = cload(H, e);
+        cstore(Z, e, cmk(h.im - 0.5 * g.re, -h.re - 0.5 * g.im));
+        cstore(Lam, e, l);
+    };
+    put(t, G, L);
+    if (a != c) put((int64_t)c * N + a, cconj(G), cconj(L));
 }
 
 // The two set-up launches: blocks of Pt columns, then of each half of the partial
 // sums; blocks of Cdd, then of Z and Lambda. As five kernels one after the other,
 // with one block of gamma on its way per thread, they took 145 us at N = 100 and
-// 524 us at N = 200; these take 98 and 475 us (6 and 3 us at N = 16, where the
+// 524 us at N = 200; these take 71 and 289 us (4 and 5 us at N = 16, where the
 // launches were most of it).
 struct PreArgs {
     GV v;
@@ -339,7 +353,10 @@ struct PreArgs {
 __global__ __launch_bounds__(256) void k_pre1(PreArgs p) {
     unsigned b = blockIdx.x;
     if (b < p.nbm) {
-        pt_column(p.v, p.Pt, (int64_t)b * 256 + threadIdx.x);
+        extern __shared__ double pre_nrm[];
+        diag_norms(pre_nrm, p.v.N);
+        __syncthreads();
+        pt_column(p.v, p.Pt, (int64_t)b * 256 + threadIdx.x, pre_nrm);
         return;
     }
     b -= p.nbm;
@@ -353,11 +370,14 @@ __global__ __launch_bounds__(256) void k_pre1(PreArgs p) {
 }
 
 __global__ __launch_bounds__(256) void k_pre2(PreArgs p) {
+    extern __shared__ double pre_nrm[];
+    diag_norms(pre_nrm, p.v.N);
+    __syncthreads();
     const int64_t t = (int64_t)(blockIdx.x % p.nbn) * 256 + threadIdx.x;
     if (blockIdx.x < p.nbn) {
-        if (t < (int64_t)p.v.N * p.v.N) cstore(p.Cdd, t, cdd_elem(p.v, (int)(t / p.v.N), (int)(t % p.v.N)));
+        if (t < (int64_t)p.v.N * p.v.N) cstore(p.Cdd, t, cdd_elem(p.v, (int)(t / p.v.N), (int)(t % p.v.N), pre_nrm));
     } else {
-        gth_fin(p.v, p.H, p.GpA, p.TpA, p.GpC, p.TpC, p.nch, p.Z, p.Lam, t);
+        gth_fin(p.v, p.H, p.GpA, p.TpA, p.GpC, p.TpC, p.nch, p.Z, p.Lam, t, pre_nrm);
     }
 }
 
@@ -634,7 +654,7 @@ __device__ __forceinline__ void dvec_block(const GV& v, const double* Zm, int64_
     double* d[4];  // diagonals of L(S), L(J), L^+(S), L^+(J): [a][pair]
 #pragma unroll
     for (int i = 0; i < 4; ++i) d[i] = lds + N + (size_t)i * N * LD;
-    for (int m = t; m < N; m += 256) nrm[m] = m ? 1.0 / sqrt((double)m * (m + 1)) : 0.0;
+    diag_norms(nrm, N);
     const int pl = t % PB;
     const int64_t pn = pn0 + pl;
     if (pn < P) {
@@ -746,7 +766,7 @@ __device__ __forceinline__ void dd_block(const GV& v, const double* Zm, double* 
         if (b == a) x += 2.0 * cload(Zm, (int64_t)a * N + a).re;
         r[a * LD + b] = x;
     }
-    for (int m = t; m < N; m += blockDim.x) nrm[m] = m ? 1.0 / sqrt((double)m * (m + 1)) : 0.0;
+    diag_norms(nrm, N);
     __syncthreads();
     if (t < N) {
         double pre = 0.0;
@@ -923,8 +943,8 @@ __global__ __launch_bounds__(256) void k_tail(GV v, const double* Lam, double* K
 // the block index). The line lies where the LDS of the largest piece, the diagonal
 // block's table, still lets three workgroups share a CU, as k_quad's does. Time of
 // a whole preparation, 13 launches / launch by launch on two streams / fused: N = 8
-// 90 / 66 / 23 us, N = 33 199 / 91 / 51, N = 64 471 / 247 / 207, N = 80 689 / 479 /
-// 421; from N = 100 the work order's L2 reuse is worth more (974 and 982 us).
+// 90 / 66 / 23 us, N = 33 199 / 91 / 48, N = 64 471 / 247 / 194, N = 80 689 / 479 /
+// 403; from N = 100 the work order's L2 reuse is worth more (974 and 982 us).
 constexpr int kFuseN = 80;
 
 struct RestArgs {
@@ -1136,9 +1156,10 @@ int lb_impl_prepare_dense(lb_ctx* c, int N, const double* H, const double* gamma
     pre.nch = nch;
     pre.nbm = lb_blocks(M, 256);
     pre.nbn = lb_blocks(NN, 256);
-    hipLaunchKernelGGL(k_pre1, dim3(pre.nbm + 2 * pre.nbn * (unsigned)nch), dim3(256), 0, s, pre);
+    const size_t pre_lds = sizeof(double) * N;
+    hipLaunchKernelGGL(k_pre1, dim3(pre.nbm + 2 * pre.nbn * (unsigned)nch), dim3(256), pre_lds, s, pre);
     LB_CHECK_LAUNCH();
-    hipLaunchKernelGGL(k_pre2, dim3(2 * pre.nbn), dim3(256), 0, s, pre);
+    hipLaunchKernelGGL(k_pre2, dim3(2 * pre.nbn), dim3(256), pre_lds, s, pre);
     LB_CHECK_LAUNCH();
     const unsigned nbk = lb_blocks(M, 256), npad = ldq > M ? lb_blocks(M * (ldq - M), 256) : 0;
     if (fused) {
