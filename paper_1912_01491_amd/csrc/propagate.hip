@@ -169,11 +169,12 @@ __global__ __launch_bounds__(256) void k_gemm64(const double* const* Qs, int64_t
 
 // ---------------------------------------------------------------------------
 // Matrix-core stage GEMM, FP32 operands: Q32 and X32 in FP32, FP32 products and
-// accumulation within a k-slab, FP64 partial sums across slabs.
+// accumulation within a k-slab, FP64 sums across slabs. A slab's sum is an FP32
+// value and is stored as one (17 of them at N = 99: 43 MB a stage instead of 85).
 // ---------------------------------------------------------------------------
 template <int RT, int CT, bool ALIGNED>
 __global__ __launch_bounds__(256) void k_gemm32(const float* const* Qs, int64_t M, int64_t Mp, int64_t ldq,
-                                                const float* Xall, int64_t xstride, double* Pall,
+                                                const float* Xall, int64_t xstride, float* Pall,
                                                 int64_t pstride, int kslab, GemmGrid gg) {
     constexpr int Bp = 16 * CT;
     const int lane = threadIdx.x & 63;
@@ -183,7 +184,7 @@ __global__ __launch_bounds__(256) void k_gemm32(const float* const* Qs, int64_t 
     if (!gemm_work(gg, bx, slab, r)) return;
     const float* Q = Qs[r];
     const float* X = Xall + r * xstride;
-    double* Part = Pall + r * pstride + (int64_t)slab * Mp * Bp;
+    float* Part = Pall + r * pstride + (int64_t)slab * Mp * Bp;
     const int64_t row0 = ((int64_t)bx * (blockDim.x >> 6) + wave) * (16 * RT);
     if (row0 >= M) return;
     const int64_t k0 = (int64_t)slab * kslab;
@@ -283,9 +284,11 @@ __global__ __launch_bounds__(256) void k_gemm32(const float* const* Qs, int64_t 
 #pragma unroll
         for (int c = 0; c < CT; ++c)
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
+            for (int j = 0; j < 4; j += 2) {
                 const int64_t row = row0 + 16 * t + 4 * lk + j;
-                if (row < M) Part[ilv2(row, 16 * c + lr, Bp)] = (double)acc[t][c][j];
+                float* o = Part + ilv2(row, 16 * c + lr, Bp);
+                if (row + 1 < M) *reinterpret_cast<float2*>(o) = make_float2(acc[t][c][j], acc[t][c][j + 1]);
+                else if (row < M) *o = acc[t][c][j];
             }
 }
 
@@ -480,7 +483,7 @@ __global__ __launch_bounds__(256) void k_gemm64s(const double* const* Qs, int64_
 
 template <int RT, int CT>
 __global__ __launch_bounds__(256) void k_gemm32s(const float* const* Qs, int64_t M, int64_t Mp, int64_t ldq,
-                                                 const float* Xall, int64_t xstride, double* Pall,
+                                                 const float* Xall, int64_t xstride, float* Pall,
                                                  int64_t pstride, int kslab, GemmGrid gg) {
     extern __shared__ lb_u4 stage_lds[];
     constexpr int Bp = 16 * CT;
@@ -492,7 +495,7 @@ __global__ __launch_bounds__(256) void k_gemm32s(const float* const* Qs, int64_t
     if (!gemm_work(gg, bx, slab, r)) return;
     const float* Q = Qs[r];
     const float* X = Xall + r * xstride;
-    double* Part = Pall + r * pstride + (int64_t)slab * Mp * Bp;
+    float* Part = Pall + r * pstride + (int64_t)slab * Mp * Bp;
     const int64_t row0 = ((int64_t)bx * (blockDim.x >> 6) + wave) * (16 * RT);
     if (row0 >= M) return;
     const int64_t k0 = (int64_t)slab * kslab;
@@ -623,9 +626,11 @@ __global__ __launch_bounds__(256) void k_gemm32s(const float* const* Qs, int64_t
 #pragma unroll
         for (int c = 0; c < CT; ++c)
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
+            for (int j = 0; j < 4; j += 2) {
                 const int64_t row = row0 + 16 * t + 4 * lk + j;
-                if (row < M) Part[ilv2(row, 16 * c + lr, Bp)] = (double)acc[t][c][j];
+                float* o = Part + ilv2(row, 16 * c + lr, Bp);
+                if (row + 1 < M) *reinterpret_cast<float2*>(o) = make_float2(acc[t][c][j], acc[t][c][j + 1]);
+                else if (row < M) *o = acc[t][c][j];
             }
 }
 
@@ -640,7 +645,7 @@ struct StageArgs {
     float* X32;      // may be null
     int64_t sstride; // per-system stride of V/Acc/X (doubles)
     int64_t s32stride;
-    const double* Part;
+    const void* Part;  // partial sums: double, or float in FP32
     int64_t pstride;
     int nslab;
     int64_t M, Mp;
@@ -648,37 +653,55 @@ struct StageArgs {
     double dt;
 };
 
-__global__ void k_stage(StageArgs a, int stage) {
-    const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;  // (row, b) in row-major
+// A thread takes two rows of one state: they are neighbours in every array but the
+// user's, so all of it moves in pairs, 16 bytes a lane in FP64 (one element a lane
+// left half of each line to another wave: 19.7 us at N = 99, 50 states, 17 slabs,
+// now 11.2; 10.9 at N = 100, 64 states, 5 slabs in FP64, now 8.8). T: type of the
+// partial sums.
+template <typename T>
+__global__ __launch_bounds__(256) void k_stage(StageArgs a, int stage) {
+    typedef T pair __attribute__((ext_vector_type(2)));
+    const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;  // (row pair, b) in row-major
     const int r = blockIdx.y;
-    if (e >= a.M * a.Bp) return;
-    const int64_t row = e / a.Bp;
+    const int64_t row = e / a.Bp * 2;
+    if (row >= a.M) return;
     const int b = (int)(e % a.Bp);
     const int64_t idx = ilv2(row, b, a.Bp);
-    const double* part = a.Part + r * a.pstride + idx;
-    double k = 0.0;
-    for (int s = 0; s < a.nslab; ++s) k += part[(int64_t)s * a.Mp * a.Bp];
-    k += a.Ks[r][row];
-    double* V = a.V + r * a.sstride;
-    double* Acc = a.Acc + r * a.sstride;
-    double* X = a.X + r * a.sstride;
-    const double h = a.dt;
-    double x;
-    if (stage == 1) {
-        Acc[idx] = k;
-        x = V[idx] + 0.5 * h * k;
-    } else if (stage == 2) {
-        Acc[idx] = Acc[idx] + 2.0 * k;
-        x = V[idx] + 0.5 * h * k;
-    } else if (stage == 3) {
-        Acc[idx] = Acc[idx] + 2.0 * k;
-        x = V[idx] + h * k;
-    } else {
-        x = V[idx] + h / 6.0 * (Acc[idx] + k);
-        V[idx] = x;
+    const bool two = row + 1 < a.M;
+    const T* part = (const T*)a.Part + r * a.pstride + idx;
+    lb_double2v k = {0.0, 0.0};
+#pragma unroll 4
+    for (int s = 0; s < a.nslab; ++s) {
+        const pair q = *reinterpret_cast<const pair*>(part + (int64_t)s * a.Mp * a.Bp);
+        k.x += (double)q.x;
+        k.y += (double)q.y;
     }
-    X[idx] = x;
-    if (a.X32) a.X32[r * a.s32stride + ilv4(row, b, a.Bp)] = (float)x;
+    k.x += a.Ks[r][row];
+    if (two) k.y += a.Ks[r][row + 1];
+    lb_double2v* V = reinterpret_cast<lb_double2v*>(a.V + r * a.sstride + idx);
+    lb_double2v* Acc = reinterpret_cast<lb_double2v*>(a.Acc + r * a.sstride + idx);
+    lb_double2v* X = reinterpret_cast<lb_double2v*>(a.X + r * a.sstride + idx);
+    const double h = a.dt;
+    const lb_double2v v = *V;
+    lb_double2v x;
+    if (stage == 1) {
+        *Acc = k;
+        x = v + 0.5 * h * k;
+    } else if (stage == 2) {
+        *Acc = *Acc + 2.0 * k;
+        x = v + 0.5 * h * k;
+    } else if (stage == 3) {
+        *Acc = *Acc + 2.0 * k;
+        x = v + h * k;
+    } else {
+        x = v + h / 6.0 * (*Acc + k);
+        if (!two) x.y = 0.0;
+        *V = x;
+    }
+    if (!two) x.y = 0.0;  // the padding row stays zero
+    *X = x;
+    if (a.X32)
+        *reinterpret_cast<float2*>(a.X32 + r * a.s32stride + ilv4(row, b, a.Bp)) = make_float2((float)x.x, (float)x.y);
 }
 
 // user layout (B, M) -> interleaved padded (Mp, Bp); padding rows/columns zero
@@ -881,7 +904,7 @@ __global__ void k_to_f32(const double* Q, float* Q32, int64_t n) {
 
 typedef void (*gemm64_fn)(const double* const*, int64_t, int64_t, int64_t, const double*, int64_t, double*,
                           int64_t, int, GemmGrid);
-typedef void (*gemm32_fn)(const float* const*, int64_t, int64_t, int64_t, const float*, int64_t, double*,
+typedef void (*gemm32_fn)(const float* const*, int64_t, int64_t, int64_t, const float*, int64_t, float*,
                           int64_t, int, GemmGrid);
 
 template <bool AL>
@@ -1266,7 +1289,7 @@ static int plan_gemm(const Plan& p, hipStream_t s, int stage, double dt) {
     } else {
         gemm32_fn fn = p.staged ? pick32s(RT, CT) : (p.aligned ? pick32<true>(RT, CT) : pick32<false>(RT, CT));
         hipLaunchKernelGGL(fn, ggrid, gblock, shm, s, (const float* const*)(p.d + p.R), p.M, p.Mp, p.ldq,
-                           (const float*)p.X32, p.s32stride, p.Part, p.pstride, p.tile.kslab, gg);
+                           (const float*)p.X32, p.s32stride, (float*)p.Part, p.pstride, p.tile.kslab, gg);
     }
     LB_CHECK_LAUNCH();
     return LB_OK;
@@ -1323,12 +1346,12 @@ static int plan_launch(const Plan& p, hipStream_t s, double dt, int64_t steps, c
         return LB_OK;
     }
     const StageArgs sa = stage_args(p, dt);
-    const dim3 sgrid(lb_blocks(p.M * p.Bp, 256), p.R);
+    const dim3 sgrid(lb_blocks((p.M + 1) / 2 * p.Bp, 256), p.R);
     for (int64_t st = 0; st < steps; ++st)
         for (int stage = 1; stage <= 4; ++stage) {
             rc = plan_gemm(p, s, stage, dt);
             if (rc) return rc;
-            hipLaunchKernelGGL(k_stage, sgrid, dim3(256), 0, s, sa, stage);
+            hipLaunchKernelGGL(p.precision == LB_FP64 ? k_stage<double> : k_stage<float>, sgrid, dim3(256), 0, s, sa, stage);
             LB_CHECK_LAUNCH();
         }
     hipLaunchKernelGGL(k_unpack, dim3(lb_blocks(p.M * p.B, 256), p.R), dim3(256), 0, s,
