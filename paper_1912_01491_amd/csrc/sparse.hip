@@ -45,6 +45,7 @@ namespace {
 
 constexpr double kR = 0.70710678118654752440;
 constexpr int kMaxRowEntries = 64;  // entries of L^+(F_s) held per pair row
+constexpr int kValueEntries = 24;   // up to which their values are held too
 
 struct Ell {
     int* idx;     // N x W
@@ -255,6 +256,8 @@ struct PairArgs {
     int64_t Pp;       // number of pairs
     const Ell* ells;  // set 0: columns of A = iH - G/2; 1 + 2p: rows of L0_p
     const double* rates;
+    const int* act;   // the nact jump operators with a nonzero rate and an entry, in order
+    int nact;
     // outputs
     int64_t* cnt;          // count phase: entries per row
     const int64_t* rowptr; // fill phase
@@ -262,26 +265,6 @@ struct PairArgs {
     double* val;
     double* K;
     int* overflow;
-};
-
-// A row's entries while it is formed: [entry][lane], the values in LDS together
-// with their sort keys (position << 6 | entry; position = pair * 2 + (a > c) for
-// the off-diagonal entry (a, c), 2 P + a for the diagonal, below 2^23 for
-// N <= 2048, so keys are unique and sorting keeps the order of equal positions).
-struct RowList {
-    double2* val;
-    uint32_t* key;
-    int n, bound;
-    int* overflow;
-    __device__ __forceinline__ void push(uint32_t pos, cd v) {
-        if (n >= bound) {
-            *overflow = 1;
-            return;
-        }
-        val[n * 64] = make_double2(v.re, v.im);
-        key[n * 64] = (pos << 6) | (uint32_t)n;
-        ++n;
-    }
 };
 
 // Sorts the first n of at most NB keys (stride 64 in LDS) by Batcher's odd-even
@@ -314,80 +297,117 @@ __device__ __forceinline__ uint32_t row_pos(int N, int64_t Pp, int a, int c) {
     return (uint32_t)(2 * lb_upair(N, a, c) + (a > c ? 1 : 0));
 }
 
-// One thread per row, one wavefront per block; dynamic LDS of 64 bound (16 + 4)
-// bytes. The same arithmetic in the count and the fill phase, so they agree on
-// which entries are exactly zero and not stored. (With the entries in a private
-// array, which lived in scratch memory, and an insertion sort there, N = 1000:
-// 1.09 ms in the count and 1.27 ms in the fill phase; now 70 and 118 us.)
-template <int NB>
+// One thread per row, one wavefront per block. The same arithmetic in the count and
+// the fill phase, so they agree on which entries are exactly zero and not stored.
+//
+// A row's entries while it is formed: [entry][lane] in LDS, a sort key (position
+// << 6 | entry; position = pair * 2 + (a > c) for the off-diagonal entry (a, c),
+// 2 P + a for the diagonal, below 2^23 for N <= 2048, so keys are unique and
+// sorting keeps the order of equal positions) and either its value (VALS, 20 bytes
+// an entry) or the term it comes from (6 bytes), its value being formed from the
+// lists when it is summed. A row of few entries is fastest with its values at hand;
+// one of many then leaves three wavefronts on a CU, too few to hide the lists'
+// latency. A whole preparation at N = 1000 with values / with terms: dimer (14
+// entries) 0.51 / 0.56 ms, rocked dimer (38) 1.42 / 1.06 ms.
+// Terms: kind | t1 << 3 | t2 << 7 | operator << 10, where an entry bound of 64
+// keeps t1 below 16 (4 lists of A), t1 and t2 below 6 (2 W^2) and operators below 32.
+template <int NB, bool VALS>
 __global__ __launch_bounds__(64) void k_pair_rows(PairArgs g, int fill) {
     extern __shared__ double2 rowmem[];
     const int64_t s = (int64_t)blockIdx.x * 64 + threadIdx.x;
     const int N = g.N;
     const int64_t Pp = g.Pp;
     const bool live = s < 2 * Pp;
-    RowList E;
-    E.val = rowmem + threadIdx.x;
-    E.key = reinterpret_cast<uint32_t*>(rowmem + 64 * g.bound) + threadIdx.x;
-    E.n = 0;
-    E.bound = g.bound;
-    E.overflow = g.overflow;
+    double2* vals = rowmem + threadIdx.x;
+    uint32_t* key = reinterpret_cast<uint32_t*>(rowmem + (VALS ? 64 * g.bound : 0)) + threadIdx.x;
+    uint16_t* terms = reinterpret_cast<uint16_t*>(key - threadIdx.x + 64 * g.bound) + threadIdx.x;
+    const int cls = s >= Pp ? 1 : 0;
+    int u = 0, v = 1;
     if (live) {
-        const int cls = s >= Pp ? 1 : 0;
-        int cc, u, v;
+        int cc;
         lb_decode(N, s - cls * Pp, cc, u, v);
-        const cd al = cls == 0 ? cmk(kR, 0) : cmk(0, -kR);  // (F_s)_uv
-        const cd be = cls == 0 ? cmk(kR, 0) : cmk(0, kR);   // (F_s)_vu
-        const Ell Ac = g.ells[0];
-        const int nu = Ac.cnt[u], nv = Ac.cnt[v];
+    }
+    const double fre = cls == 0 ? kR : 0.0, fim = cls == 0 ? 0.0 : -kR;  // al = (F_s)_uv; (F_s)_vu = be = conj(al)
+    const int* aidx = g.ells[0].idx;
+    const double* aval = g.ells[0].val;
+    const int aw = g.ells[0].W;
+    auto value = [&](int term) __attribute__((always_inline)) {
+        const int kind = term & 7, t1 = term >> 3 & 15;
+        const cd f = cmk(fre, kind & 1 ? -fim : fim);  // al for even kinds, be for odd ones
+        if (kind < 4) {
+            cd w = cload(aval, (int64_t)(kind == 1 || kind == 2 ? v : u) * aw + t1);
+            if (kind >= 2) w.im = -w.im;
+            return cmul(f, w);
+        }
+        const int t2 = term >> 7 & 7, p = g.act[term >> 10];
+        const Ell* e = g.ells + 1 + 2 * p;
+        const int64_t x = kind == 4 ? u : v, y = u + v - x;
+        const cd l1 = cload(e->val, x * e->W + t1), l2 = cload(e->val, y * e->W + t2);
+        return cscale(cmul(f, cmul(cconj(l1), l2)), g.rates[p]);
+    };
+    int n = 0;
+    auto push = [&](uint32_t pos, int term) __attribute__((always_inline)) {
+        if (n >= g.bound) {
+            *g.overflow = 1;
+            return;
+        }
+        if (VALS) {
+            const cd y = value(term);
+            vals[n * 64] = make_double2(y.re, y.im);
+        } else {
+            terms[n * 64] = (uint16_t)term;
+        }
+        key[n * 64] = (pos << 6) | (uint32_t)n;
+        ++n;
+    };
+    if (live) {
+        const int nu = g.ells[0].cnt[u], nv = g.ells[0].cnt[v];
+        const int *iu = aidx + (int64_t)u * aw, *iv = aidx + (int64_t)v * aw;
         // i H F_s - G F_s / 2 = A F_s: (a, v) += al A_au, (a, u) += be A_av
-        for (int t = 0; t < nu; ++t) E.push(row_pos(N, Pp, ell_idx(Ac, u, t), v), cmul(al, ell_val(Ac, u, t)));
-        for (int t = 0; t < nv; ++t) E.push(row_pos(N, Pp, ell_idx(Ac, v, t), u), cmul(be, ell_val(Ac, v, t)));
+        for (int t = 0; t < nu; ++t) push(row_pos(N, Pp, iu[t], v), 0 | t << 3);
+        for (int t = 0; t < nv; ++t) push(row_pos(N, Pp, iv[t], u), 1 | t << 3);
         // -i F_s H - F_s G / 2 = F_s A^+: (u, c) += al conj(A_cv), (v, c) += be conj(A_cu)
-        for (int t = 0; t < nv; ++t) E.push(row_pos(N, Pp, u, ell_idx(Ac, v, t)), cmul(al, cconj(ell_val(Ac, v, t))));
-        for (int t = 0; t < nu; ++t) E.push(row_pos(N, Pp, v, ell_idx(Ac, u, t)), cmul(be, cconj(ell_val(Ac, u, t))));
+        for (int t = 0; t < nv; ++t) push(row_pos(N, Pp, u, iv[t]), 2 | t << 3);
+        for (int t = 0; t < nu; ++t) push(row_pos(N, Pp, v, iu[t]), 3 | t << 3);
         // g_p L0^+ F_s L0: (a, c) += g al conj(L0_ua) L0_vc + g be conj(L0_va) L0_uc
-        for (int p = 0; p < g.P; ++p) {
-            const Ell Lr = g.ells[1 + 2 * p];
-            const double gp = g.rates[p];
-            if (gp == 0.0) continue;
-            const int lu = Lr.cnt[u], lv = Lr.cnt[v];
+        for (int p = 0; p < g.nact; ++p) {
+            const Ell* e = g.ells + 1 + 2 * g.act[p];
+            const int lu = e->cnt[u], lv = e->cnt[v];
+            const int *ju = e->idx + (int64_t)u * e->W, *jv = e->idx + (int64_t)v * e->W;
             for (int t1 = 0; t1 < lu; ++t1)
-                for (int t2 = 0; t2 < lv; ++t2)
-                    E.push(row_pos(N, Pp, ell_idx(Lr, u, t1), ell_idx(Lr, v, t2)),
-                           cscale(cmul(al, cmul(cconj(ell_val(Lr, u, t1)), ell_val(Lr, v, t2))), gp));
+                for (int t2 = 0; t2 < lv; ++t2) push(row_pos(N, Pp, ju[t1], jv[t2]), 4 | t1 << 3 | t2 << 7 | p << 10);
             for (int t1 = 0; t1 < lv; ++t1)
-                for (int t2 = 0; t2 < lu; ++t2)
-                    E.push(row_pos(N, Pp, ell_idx(Lr, v, t1), ell_idx(Lr, u, t2)),
-                           cscale(cmul(be, cmul(cconj(ell_val(Lr, v, t1)), ell_val(Lr, u, t2))), gp));
+                for (int t2 = 0; t2 < lu; ++t2) push(row_pos(N, Pp, jv[t1], ju[t2]), 5 | t1 << 3 | t2 << 7 | p << 10);
         }
     }
-    sort_keys<NB>(E.key, E.n);
-    const int n = E.n;
+    auto val_of = [&](uint32_t k) __attribute__((always_inline)) {
+        if (!VALS) return value(terms[(k & 63u) * 64]);
+        const double2 y = vals[(k & 63u) * 64];
+        return cmk(y.x, y.y);
+    };
+    sort_keys<NB>(key, n);
     const uint32_t diag0 = (uint32_t)(2 * Pp);
     // Off-diagonal entries come first, pair by pair: Y_pq (p < q) and Y_qp, each
     // the sum of its entries in the order they were formed. Tr(Y S_pq) =
     // r (Y_pq + Y_qp); Tr(Y J_pq) = i r (Y_pq - Y_qp). The S block of the row,
     // then the J block; the count phase takes both in one pass.
     constexpr uint32_t kEnd = 0xffffffffu;
-    auto key_at = [&](int i) { return i < n ? E.key[i * 64] : kEnd; };
-    auto val_of = [&](uint32_t k) {
-        const double2 v = E.val[(k & 63u) * 64];
-        return cmk(v.x, v.y);
-    };
+    auto key_at = [&](int i) { return i < n ? key[i * 64] : kEnd; };
     const uint32_t dkey = diag0 << 6;  // keys of diagonal entries start here
     int64_t o = fill && live ? g.rowptr[s] : 0;
     int nd0 = 0;  // first diagonal entry
     for (int part = 0; part < (fill ? 2 : 1); ++part) {
         int i = 0;
         uint32_t k = key_at(0), kn = key_at(1);
+        cd e = k < dkey ? val_of(k) : cmk(0, 0);
         while (k < dkey) {
             const uint32_t pr = k >> 7;
             cd y0 = cmk(0, 0), y1 = cmk(0, 0);
             do {
-                const cd e = val_of(k);
+                const cd en = kn < dkey ? val_of(kn) : cmk(0, 0);  // the next entry's on its way
                 if (k & 64u) y1 = cadd(y1, e);
                 else y0 = cadd(y0, e);
+                e = en;
                 k = kn;
                 ++i;
                 kn = key_at(i + 1);
@@ -409,7 +429,7 @@ __global__ __launch_bounds__(64) void k_pair_rows(PairArgs g, int fill) {
     // Diagonal entries (merged by position): Tr Y, and the D columns m from
     // max(1, first position) to the last position, or to N-1 when Tr(Y) != 0:
     // beyond the last position the value is Tr(Y)/sqrt(m(m+1)).
-    auto merged = [&](int& i) {  // sum of the entries at entry i's position; i moves past them
+    auto merged = [&](int& i) __attribute__((always_inline)) {  // sum of the entries at entry i's position; i moves past them
         const uint32_t ps = key_at(i) >> 6;
         cd y = val_of(key_at(i++));
         while (i < n && key_at(i) >> 6 == ps) y = cadd(y, val_of(key_at(i++)));
@@ -790,7 +810,7 @@ static int sparse_body(lb_ctx* c, int N, const lb_csr_c128* H, int P, const doub
     const size_t o_rates = take(sizeof(double) * (P + 1));
     const size_t o_l1 = take(sizeof(double) * N);
     const size_t o_cnt = take(sizeof(int) * (size_t)N * nsets);
-    const size_t o_ells = take(sizeof(Ell) * nsets);
+    const size_t o_ells = take(sizeof(Ell) * nsets + sizeof(int) * kMaxRowEntries);  // then the pair rows' operators
     const size_t o_rowcnt = take(sizeof(int64_t) * (M + 1));
     const size_t o_dcnt = take(sizeof(int64_t) * (M + 1));
     const size_t o_carry = take(sizeof(int64_t) * (M + 1));
@@ -818,9 +838,9 @@ static int sparse_body(lb_ctx* c, int N, const lb_csr_c128* H, int P, const doub
     int* wmax = ovf + 2;
     const size_t info_bytes = sizeof(int64_t) * 4 + sizeof(int) * (2 + nsets);
 
-    // pinned staging: [info read back | rates | ELL descriptors]
+    // pinned staging: [info read back | rates | ELL descriptors, operators of the pair rows]
     const size_t h_rates = lb_align(info_bytes, 64), h_ells = h_rates + lb_align(sizeof(double) * (P + 1), 64);
-    rc = lb_host_reserve(c, h_ells + sizeof(Ell) * nsets);
+    rc = lb_host_reserve(c, h_ells + sizeof(Ell) * nsets + sizeof(int) * kMaxRowEntries);
     if (rc) return rc;
     LB_HIP(hipStreamSynchronize(s));  // an earlier copy on this stream may still read the staging buffer
     char* host = (char*)c->host;
@@ -882,7 +902,11 @@ static int sparse_body(lb_ctx* c, int N, const lb_csr_c128* H, int P, const doub
         *want = o2 + (o2 >> 2);
         return 1;
     }
-    LB_HIP(hipMemcpyAsync(dells, hl, sizeof(Ell) * nsets, hipMemcpyHostToDevice, s));
+    int nact = 0;  // at most kMaxRowEntries / 2, as each adds at least 2 to the bound
+    int* hact = (int*)(hl + nsets);
+    for (int p = 0; p < P; ++p)
+        if (rates[p] != 0.0 && hw[1 + 2 * p] > 0) hact[nact++] = p;
+    LB_HIP(hipMemcpyAsync(dells, hl, sizeof(Ell) * nsets + sizeof(int) * nact, hipMemcpyHostToDevice, s));
     hipLaunchKernelGGL(k_ell_fill, egrid, dim3(256), 0, s, N, (const double*)A, (const double*)Ld, (const Ell*)dells);
     LB_CHECK_LAUNCH();
     hipLaunchKernelGGL(k_l1diag, dim3(lb_blocks(N, 64)), dim3(64), 0, s, N, P, (const double*)drates,
@@ -911,17 +935,21 @@ static int sparse_body(lb_ctx* c, int N, const lb_csr_c128* H, int P, const doub
     pa.Pp = Pp;
     pa.ells = dells;
     pa.rates = drates;
+    pa.act = (const int*)(dells + nsets);
+    pa.nact = nact;
     pa.cnt = rowcnt;
     pa.rowptr = nullptr;
     pa.col = nullptr;
     pa.val = nullptr;
     pa.K = nullptr;
     pa.overflow = ovf;
-    void (*pair_rows)(PairArgs, int) = bound <= 16   ? k_pair_rows<16>
-                                         : bound <= 24 ? k_pair_rows<24>
-                                         : bound <= 40 ? k_pair_rows<40>
-                                                       : k_pair_rows<64>;
-    const size_t pair_lds = (size_t)64 * pa.bound * (sizeof(double2) + sizeof(uint32_t));
+    const bool vals = bound <= kValueEntries;
+    void (*pair_rows)(PairArgs, int) = bound <= 16   ? k_pair_rows<16, true>
+                                         : bound <= 24 ? k_pair_rows<24, true>
+                                         : bound <= 40 ? k_pair_rows<40, false>
+                                                       : k_pair_rows<64, false>;
+    const size_t pair_lds =
+        (size_t)64 * pa.bound * (sizeof(uint32_t) + (vals ? sizeof(double2) : sizeof(uint16_t)));
     rc = lb_aux_stream(c);
     if (rc) return rc;
     AuxWork aux(c);
