@@ -1,7 +1,8 @@
 // Exclusive scan of int64 counts on the device: per-tile sums, one block over
 // the tiles, then the offsets of each tile. It replaces scans on the host,
 // whose two PCIe copies and serial loop took 1.3 ms for 10^6 counts; the three
-// launches here take 15 us.
+// launches here take 15 us. Up to kScanOne counts one workgroup walks all of them
+// (10^4: 10 us), which is less than three launches one after the other.
 #pragma once
 
 #include "lb_internal.h"
@@ -9,11 +10,13 @@
 namespace {
 
 constexpr int kScanTile = 2048;  // counts per block (8 per thread)
+constexpr int64_t kScanOne = 32768;
 
-// A block's sum over its 256 threads' values in thread order; *before is the
+// A block's sum over the values of its W wavefronts in thread order; *before is the
 // sum over earlier threads. Every thread must call it.
-__device__ __forceinline__ int64_t block_scan256(int64_t v, int64_t* before) {
-    __shared__ int64_t wsum[4];
+template <int W>
+__device__ __forceinline__ int64_t block_scan(int64_t v, int64_t* before) {
+    __shared__ int64_t wsum[W];
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     int64_t inc = v;
     for (int o = 1; o < 64; o <<= 1) {
@@ -24,8 +27,8 @@ __device__ __forceinline__ int64_t block_scan256(int64_t v, int64_t* before) {
     if (lane == 63) wsum[w] = inc;
     __syncthreads();
     int64_t base = 0, tot = 0;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
+#pragma unroll 4
+    for (int i = 0; i < W; ++i) {
         if (i < w) base += wsum[i];
         tot += wsum[i];
     }
@@ -41,8 +44,8 @@ __global__ __launch_bounds__(256) void k_scan_tiles(int64_t n, const int64_t* sr
             s += src[i];
             z += src[i] != 0;
         }
-    s = block_scan256(s, &before);
-    z = block_scan256(z, &before);
+    s = block_scan<4>(s, &before);
+    z = block_scan<4>(z, &before);
     if (threadIdx.x == 0) {
         tsum[blockIdx.x] = s;
         tnz[blockIdx.x] = z;
@@ -57,8 +60,8 @@ __global__ __launch_bounds__(256) void k_scan_mid(int64_t nt, int64_t* tsum, int
         const int64_t i = i0 + threadIdx.x;
         const int64_t s = i < nt ? tsum[i] : 0, z = i < nt ? tnz[i] : 0;
         int64_t bs, bz;
-        const int64_t ts = block_scan256(s, &bs);
-        const int64_t tz = block_scan256(z, &bz);
+        const int64_t ts = block_scan<4>(s, &bs);
+        const int64_t tz = block_scan<4>(z, &bz);
         if (i < nt) {
             tsum[i] = rs + bs;
             tnz[i] = rz + bz;
@@ -72,12 +75,13 @@ __global__ __launch_bounds__(256) void k_scan_mid(int64_t nt, int64_t* tsum, int
     }
 }
 
-// Offsets dst[0..n] (dst[n] the total; dst may be src; both 16-byte aligned) and, when list is not
-// null, the positions of the nonzero counts in increasing order.
-__global__ __launch_bounds__(256) void k_scan_fin(int64_t n, const int64_t* src, const int64_t* tsum,
-                                                  const int64_t* tnz, int64_t* dst, int64_t* list) {
-    const int64_t i0 = (int64_t)blockIdx.x * kScanTile + 8 * threadIdx.x;
-    int64_t v[8], s = 0, z = 0, bs, bz = 0;
+// Offsets of 8 counts per thread from start on, after bs counted and bz nonzero
+// ones; both move on by the block's.
+template <int W>
+__device__ __forceinline__ void scan_eight(int64_t start, int64_t n, const int64_t* src, int64_t* dst, int64_t* list,
+                                           int64_t& bs, int64_t& bz) {
+    const int64_t i0 = start + 8 * threadIdx.x;
+    int64_t v[8], s = 0, z = 0, os, oz;
     if (i0 + 8 <= n) {
 #pragma unroll
         for (int j = 0; j < 8; j += 2) {
@@ -94,17 +98,20 @@ __global__ __launch_bounds__(256) void k_scan_fin(int64_t n, const int64_t* src,
         s += v[j];
         z += v[j] != 0;
     }
-    block_scan256(s, &bs);
-    if (list) block_scan256(z, &bz);
-    bs += tsum[blockIdx.x];
-    bz += tnz[blockIdx.x];
+    // both in one pass: a block has at most 2^13 nonzero counts, and its sum stays below 2^50
+    constexpr int64_t low = ((int64_t)1 << 50) - 1;
+    s = block_scan<W>(s | z << 50, &os);
+    oz = bz + (os >> 50);
+    os = bs + (os & low);
+    bs += s & low;
+    bz += s >> 50;
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
-        if (list && v[j] != 0) list[bz++] = i0 + j;
+        if (list && v[j] != 0) list[oz++] = i0 + j;
         const int64_t c = v[j];
-        v[j] = bs;
-        bs += c;
-        if (i0 + j == n - 1) dst[n] = bs;
+        v[j] = os;
+        os += c;
+        if (i0 + j == n - 1) dst[n] = os;
     }
     if (i0 + 8 <= n) {
 #pragma unroll
@@ -116,12 +123,36 @@ __global__ __launch_bounds__(256) void k_scan_fin(int64_t n, const int64_t* src,
     }
 }
 
+// Offsets dst[0..n] (dst[n] the total; dst may be src; both 16-byte aligned) and, when list is not
+// null, the positions of the nonzero counts in increasing order.
+__global__ __launch_bounds__(256) void k_scan_fin(int64_t n, const int64_t* src, const int64_t* tsum,
+                                                  const int64_t* tnz, int64_t* dst, int64_t* list) {
+    int64_t bs = tsum[blockIdx.x], bz = tnz[blockIdx.x];
+    scan_eight<4>((int64_t)blockIdx.x * kScanTile, n, src, dst, list, bs, bz);
+}
+
+// The whole scan by one workgroup.
+__global__ __launch_bounds__(1024) void k_scan_one(int64_t n, const int64_t* src, int64_t* dst, int64_t* list,
+                                                   int64_t* tot) {
+    int64_t bs = 0, bz = 0;
+    for (int64_t i = 0; i < n; i += 8 * 1024) scan_eight<16>(i, n, src, dst, list, bs, bz);
+    if (threadIdx.x == 0) {
+        tot[0] = bs;
+        tot[1] = bz;
+    }
+}
+
 // int64 values of device scratch the scan of n counts needs.
 static inline size_t scan_scratch(int64_t n) { return 2 * (size_t)((n + kScanTile - 1) / kScanTile); }
 
 // Enqueues the scan of n >= 1 counts; tot[0] = their sum, tot[1] = how many are nonzero (device).
 static int scan_counts(hipStream_t s, int64_t n, const int64_t* src, int64_t* dst, int64_t* list, int64_t* scratch,
                        int64_t* tot) {
+    if (n <= kScanOne) {
+        hipLaunchKernelGGL(k_scan_one, dim3(1), dim3(1024), 0, s, n, src, dst, list, tot);
+        LB_CHECK_LAUNCH();
+        return LB_OK;
+    }
     const unsigned nt = lb_blocks(n, kScanTile);
     int64_t *tsum = scratch, *tnz = scratch + nt;
     hipLaunchKernelGGL(k_scan_tiles, dim3(nt), dim3(256), 0, s, n, src, tsum, tnz);

@@ -30,8 +30,9 @@
 // of a millisecond; what the phases cost is the latency of many small steps, so
 // every loop over N or M runs across lanes and the scans stay on the device.
 // N = 1000 dimer: 14.9 ms before, 0.97 ms as two calls (a count, and a fill that
-// has to count again), 0.58 ms as one, 0.51 ms with the pair rows' counts beside the
-// diagonals' lists and the two fills beside each other on a second stream.
+// has to count again), 0.58 ms as one, 0.50 ms with the pair rows' counts beside the
+// diagonals' lists and the two fills beside each other on a second stream. Below
+// N = 400 launches are all of it: 0.24 ms at N = 100 with 30 of them, 0.19 ms with 22.
 // Rows are written with sorted column indices (S block, J block, D block);
 // entries whose value is exactly zero are not stored.
 #include "lb_internal.h"
@@ -64,8 +65,15 @@ __device__ __forceinline__ int ell_idx(const Ell& e, int i, int t) { return e.id
 // One wavefront per row. Entries go in parallel when the row's columns are
 // strictly increasing; otherwise (repeated columns add up) one lane adds them
 // in their order. Columns outside 0..N-1 are ignored.
-__global__ __launch_bounds__(64) void k_densify(int N, const int64_t* rowptr, const int64_t* col, const double* val,
-                                                double* D) {
+struct DenseJobs {
+    lb_csr_c128 m[8];
+    double* D[8];
+};
+
+__global__ __launch_bounds__(64) void k_densify(int N, DenseJobs jobs) {
+    const int64_t *rowptr = jobs.m[blockIdx.y].rowptr, *col = jobs.m[blockIdx.y].col;
+    const double* val = jobs.m[blockIdx.y].val;
+    double* D = jobs.D[blockIdx.y];
     const int r = blockIdx.x, lane = threadIdx.x;
     double* row = D + 2 * (int64_t)r * N;
     for (int c = lane; c < N; c += 64) cstore(row, c, cmk(0, 0));
@@ -228,23 +236,6 @@ __global__ __launch_bounds__(256) void k_ell_fill(int N, const double* A, const 
         }
         n += __popcll(m);
     }
-}
-
-// diag(L(1))_x = 2 Re Z_xx + sum_p g_p sum_b |L0_p,xb|^2, with Z = A^+ (Re Z_xx = Re A_xx)
-__global__ void k_l1diag(int N, int P, const double* rates, const double* A, const Ell* Lrow, double* out) {
-    const int x = blockIdx.x * blockDim.x + threadIdx.x;
-    if (x >= N) return;
-    double s = 2.0 * cload(A, (int64_t)x * N + x).re;
-    for (int p = 0; p < P; ++p) {
-        const Ell Lr = Lrow[2 * p];
-        double q = 0;
-        for (int t = 0; t < Lr.cnt[x]; ++t) {
-            const cd v = ell_val(Lr, x, t);
-            q += v.re * v.re + v.im * v.im;
-        }
-        s += rates[p] * q;
-    }
-    out[x] = s;
 }
 
 // ---------------------------------------------------------------------------
@@ -620,12 +611,31 @@ __device__ __forceinline__ void diag_dcol(const DiagArgs& g, int mm, int lane, i
     if (!fill && lane == 0) g.cnt[nidx] = n;
 }
 
+// diag(L(1))_x = 2 Re Z_xx + sum_p g_p sum_b |L0_p,xb|^2, with Z = A^+ (Re Z_xx = Re A_xx)
+__device__ __forceinline__ void l1diag(int N, int P, const double* rates, const double* A, const Ell* Lrow, double* out,
+                                       int x) {
+    if (x >= N) return;
+    double s = 2.0 * cload(A, (int64_t)x * N + x).re;
+    for (int p = 0; p < P; ++p) {
+        const Ell Lr = Lrow[2 * p];
+        double q = 0;
+        for (int t = 0; t < Lr.cnt[x]; ++t) {
+            const cd v = ell_val(Lr, x, t);
+            q += v.re * v.re + v.im * v.im;
+        }
+        s += rates[p] * q;
+    }
+    out[x] = s;
+}
+
 // The N - 1 columns of diagonal generators, four to a block, then those of the
-// pairs, 256 to a block: two independent chains of latency side by side (one
+// pairs, 256 to a block, then (to count) diag(L(1)): two independent chains of latency side by side (one
 // after the other 43 us at N = 1000).
-__global__ __launch_bounds__(256) void k_diag(DiagArgs g, unsigned nd, int fill, int* ovf) {
-    if (blockIdx.x < nd) diag_dcol(g, (int)(blockIdx.x * 4 + (threadIdx.x >> 6)) + 1, threadIdx.x & 63, fill);
-    else diag_pair(g, (int64_t)(blockIdx.x - nd) * 256 + threadIdx.x, fill, ovf);
+__global__ __launch_bounds__(256) void k_diag(DiagArgs g, unsigned nd, unsigned np, int fill, double* l1, int* ovf) {
+    const unsigned b = blockIdx.x;
+    if (b < nd) diag_dcol(g, (int)(b * 4 + (threadIdx.x >> 6)) + 1, threadIdx.x & 63, fill);
+    else if (b < nd + np) diag_pair(g, (int64_t)(b - nd) * 256 + threadIdx.x, fill, ovf);
+    else l1diag(g.N, g.P, g.rates, g.A, g.ells + 1, l1, (int)((b - nd - np) * 256 + threadIdx.x));
 }
 
 // D rows: Q[D^m][n] = sum_x w_m(x) diag_n(x) = (pre_n(m) - m diag_n(m)) / sqrt(m(m+1)),
@@ -807,7 +817,6 @@ static int sparse_body(lb_ctx* c, int N, const lb_csr_c128* H, int P, const doub
     const size_t o_l = take(sizeof(double) * 2 * NN * (P > 0 ? P : 1));
     const size_t o_a = take(sizeof(double) * 2 * NN);
     const size_t o_c = take(sizeof(double) * 2 * (P + 1));
-    const size_t o_rates = take(sizeof(double) * (P + 1));
     const size_t o_l1 = take(sizeof(double) * N);
     const size_t o_cnt = take(sizeof(int) * (size_t)N * nsets);
     const size_t o_ells = take(sizeof(Ell) * nsets + sizeof(int) * kMaxRowEntries);  // then the pair rows' operators
@@ -816,7 +825,8 @@ static int sparse_body(lb_ctx* c, int N, const lb_csr_c128* H, int P, const doub
     const size_t o_carry = take(sizeof(int64_t) * (M + 1));
     const size_t o_scan = take(sizeof(int64_t) * scan_scratch(M));
     // read back: scan totals (diagonal entries, carrying columns; stored entries, -), overflow flags, ELL widths
-    const size_t o_info = take(sizeof(int64_t) * 4 + sizeof(int) * (2 + nsets));
+    const size_t info_bytes = sizeof(int64_t) * 4 + sizeof(int) * (2 + nsets), h_rates = lb_align(info_bytes, 64);
+    const size_t o_info = take(h_rates + sizeof(double) * (P + 1));  // then the rates
     const size_t fixed = off;
     int rc = lb_ws_reserve(c, fixed);
     if (rc) return rc;
@@ -825,7 +835,7 @@ static int sparse_body(lb_ctx* c, int N, const lb_csr_c128* H, int P, const doub
     double* Ld = (double*)(ws + o_l);
     double* A = (double*)(ws + o_a);
     double* cvec = (double*)(ws + o_c);
-    double* drates = (double*)(ws + o_rates);
+    double* drates = (double*)(ws + o_info + h_rates);
     double* l1 = (double*)(ws + o_l1);
     int* cnts = (int*)(ws + o_cnt);
     Ell* dells = (Ell*)(ws + o_ells);
@@ -836,10 +846,9 @@ static int sparse_body(lb_ctx* c, int N, const lb_csr_c128* H, int P, const doub
     int64_t* tot = (int64_t*)(ws + o_info);
     int* ovf = (int*)(tot + 4);
     int* wmax = ovf + 2;
-    const size_t info_bytes = sizeof(int64_t) * 4 + sizeof(int) * (2 + nsets);
 
     // pinned staging: [info read back | rates | ELL descriptors, operators of the pair rows]
-    const size_t h_rates = lb_align(info_bytes, 64), h_ells = h_rates + lb_align(sizeof(double) * (P + 1), 64);
+    const size_t h_ells = h_rates + lb_align(sizeof(double) * (P + 1), 64);
     rc = lb_host_reserve(c, h_ells + sizeof(Ell) * nsets + sizeof(int) * kMaxRowEntries);
     if (rc) return rc;
     LB_HIP(hipStreamSynchronize(s));  // an earlier copy on this stream may still read the staging buffer
@@ -847,15 +856,19 @@ static int sparse_body(lb_ctx* c, int N, const lb_csr_c128* H, int P, const doub
     const int64_t* htot = (const int64_t*)host;
     const int* hovf = (const int*)(htot + 4);
     const int* hw = hovf + 2;
+    memset(host, 0, info_bytes);
     for (int p = 0; p < P; ++p) ((double*)(host + h_rates))[p] = rates[p];
-    if (P > 0) LB_HIP(hipMemcpyAsync(drates, host + h_rates, sizeof(double) * P, hipMemcpyHostToDevice, s));
-    LB_HIP(hipMemsetAsync(tot, 0, info_bytes, s));
+    LB_HIP(hipMemcpyAsync(tot, host, h_rates + sizeof(double) * P, hipMemcpyHostToDevice, s));
 
     // dense set-up
-    hipLaunchKernelGGL(k_densify, dim3(N), dim3(64), 0, s, N, H->rowptr, H->col, H->val, Hd);
-    LB_CHECK_LAUNCH();
-    for (int p = 0; p < P; ++p) {
-        hipLaunchKernelGGL(k_densify, dim3(N), dim3(64), 0, s, N, L[p].rowptr, L[p].col, L[p].val, Ld + 2 * NN * p);
+    for (int p0 = -1; p0 < P; p0 += 8) {
+        DenseJobs jobs = {};
+        const int n = std::min(8, P - p0);
+        for (int i = 0; i < n; ++i) {
+            jobs.m[i] = p0 + i < 0 ? *H : L[p0 + i];
+            jobs.D[i] = p0 + i < 0 ? Hd : Ld + 2 * NN * (p0 + i);
+        }
+        hipLaunchKernelGGL(k_densify, dim3(N, n), dim3(64), 0, s, N, jobs);
         LB_CHECK_LAUNCH();
     }
     if (P > 0) {
@@ -909,10 +922,6 @@ static int sparse_body(lb_ctx* c, int N, const lb_csr_c128* H, int P, const doub
     LB_HIP(hipMemcpyAsync(dells, hl, sizeof(Ell) * nsets + sizeof(int) * nact, hipMemcpyHostToDevice, s));
     hipLaunchKernelGGL(k_ell_fill, egrid, dim3(256), 0, s, N, (const double*)A, (const double*)Ld, (const Ell*)dells);
     LB_CHECK_LAUNCH();
-    hipLaunchKernelGGL(k_l1diag, dim3(lb_blocks(N, 64)), dim3(64), 0, s, N, P, (const double*)drates,
-                       (const double*)A, (const Ell*)(dells + 1), l1);
-    LB_CHECK_LAUNCH();
-
     // carrying lists: diag(L(F_n)) for every column n
     DiagArgs da;
     da.N = N;
@@ -958,8 +967,8 @@ static int sparse_body(lb_ctx* c, int N, const lb_csr_c128* H, int P, const doub
     hipLaunchKernelGGL(pair_rows, dim3(lb_blocks(2 * Pp, 64)), dim3(64), pair_lds, c->aux, pa, 0);
     LB_CHECK_LAUNCH();
 
-    const unsigned nd = lb_blocks(N - 1, 4), ndiag = nd + lb_blocks(2 * Pp, 256);
-    hipLaunchKernelGGL(k_diag, dim3(ndiag), dim3(256), 0, s, da, nd, 0, ovf + 1);
+    const unsigned nd = lb_blocks(N - 1, 4), np = lb_blocks(2 * Pp, 256);
+    hipLaunchKernelGGL(k_diag, dim3(nd + np + lb_blocks(N, 256)), dim3(256), 0, s, da, nd, np, 0, l1, ovf + 1);
     LB_CHECK_LAUNCH();
     rc = scan_counts(s, M, dcnt, dcnt, carry, scratch, tot);
     if (rc) return rc;
@@ -981,7 +990,7 @@ static int sparse_body(lb_ctx* c, int N, const lb_csr_c128* H, int P, const doub
     }
     da.pos = (int*)(ws + o_pos);
     da.val = (double*)(ws + o_dval);
-    hipLaunchKernelGGL(k_diag, dim3(ndiag), dim3(256), 0, s, da, nd, 1, ovf + 1);
+    hipLaunchKernelGGL(k_diag, dim3(nd + np), dim3(256), 0, s, da, nd, np, 1, l1, ovf + 1);
     LB_CHECK_LAUNCH();
     {
         // every diagonal generator's column carries (its list starts at position 0), after those of the pairs
