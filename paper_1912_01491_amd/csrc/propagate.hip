@@ -15,6 +15,8 @@
 //     (v_mfma_f64_16x16x4f64, v_mfma_f32_16x16x4f32) writing per-slab
 //     partial sums, followed by k_stage which reduces the slabs in a fixed
 //     order (deterministic, no atomics) and applies the RK4 combination.
+//     FP64 up to M = 2704 (2048 for more than 32 states): k_block64 -- the whole
+//     stage in one launch, a workgroup per 16 rows.
 //   * M <= 256 and B*M <= 4096: rk4_small.h -- one workgroup per state runs
 //     all steps with Q in registers.
 // State layout inside the library: states are padded to Bp in {16, 32, 64}
@@ -33,6 +35,7 @@
 #include <math.h>
 
 #include <algorithm>
+#include <type_traits>
 #include <cstring>
 #include <stdio.h>
 #include <stdlib.h>
@@ -653,6 +656,30 @@ struct StageArgs {
     double dt;
 };
 
+// The stage combination of two rows of a state: k = (Q x + K); returns the next
+// stage's x. Without a second row (two false) that element stays zero.
+__device__ __forceinline__ lb_double2v stage_pair(int stage, double h, lb_double2v k, bool two, lb_double2v* V,
+                                                  lb_double2v* Acc) {
+    const lb_double2v v = *V;
+    lb_double2v x;
+    if (stage == 1) {
+        *Acc = k;
+        x = v + 0.5 * h * k;
+    } else if (stage == 2) {
+        *Acc = *Acc + 2.0 * k;
+        x = v + 0.5 * h * k;
+    } else if (stage == 3) {
+        *Acc = *Acc + 2.0 * k;
+        x = v + h * k;
+    } else {
+        x = v + h / 6.0 * (*Acc + k);
+        if (!two) x.y = 0.0;
+        *V = x;
+    }
+    if (!two) x.y = 0.0;
+    return x;
+}
+
 // A thread takes two rows of one state: they are neighbours in every array but the
 // user's, so all of it moves in pairs, 16 bytes a lane in FP64 (one element a lane
 // left half of each line to another wave: 19.7 us at N = 99, 50 states, 17 slabs,
@@ -681,27 +708,108 @@ __global__ __launch_bounds__(256) void k_stage(StageArgs a, int stage) {
     lb_double2v* V = reinterpret_cast<lb_double2v*>(a.V + r * a.sstride + idx);
     lb_double2v* Acc = reinterpret_cast<lb_double2v*>(a.Acc + r * a.sstride + idx);
     lb_double2v* X = reinterpret_cast<lb_double2v*>(a.X + r * a.sstride + idx);
-    const double h = a.dt;
-    const lb_double2v v = *V;
-    lb_double2v x;
-    if (stage == 1) {
-        *Acc = k;
-        x = v + 0.5 * h * k;
-    } else if (stage == 2) {
-        *Acc = *Acc + 2.0 * k;
-        x = v + 0.5 * h * k;
-    } else if (stage == 3) {
-        *Acc = *Acc + 2.0 * k;
-        x = v + h * k;
-    } else {
-        x = v + h / 6.0 * (*Acc + k);
-        if (!two) x.y = 0.0;
-        *V = x;
-    }
-    if (!two) x.y = 0.0;  // the padding row stays zero
+    const lb_double2v x = stage_pair(stage, a.dt, k, two, V, Acc);
     *X = x;
     if (a.X32)
         *reinterpret_cast<float2*>(a.X32 + r * a.s32stride + ilv4(row, b, a.Bp)) = make_float2((float)x.x, (float)x.y);
+}
+
+// ---------------------------------------------------------------------------
+// A whole stage of a small system in one launch (FP64, 2 to 64 states): a workgroup
+// owns 16 rows, its eight waves an eighth of the columns each (lane mapping as in
+// k_gemm64), their sums meet in LDS in the order of the waves and the stage
+// combination follows at once. x is read from one buffer and written to another,
+// since other workgroups may still be reading. What a stage costs at this size is
+// launches and latency, and this is one launch instead of two, without partial sums
+// in memory. The columns' split depends on M alone, so a system's bits do not depend
+// on what shares the launch.
+// ---------------------------------------------------------------------------
+constexpr int kBlockWaves = 8;
+
+struct BlockArgs {
+    const double* const* Qs;
+    const double* const* Ks;
+    int64_t M, ldq;
+    double *V, *Acc;
+    int64_t sstride;
+    const double* Xin;
+    double* Xout;
+    int64_t in_stride, out_stride;
+    double h;
+};
+
+template <int CT, bool ALIGNED>
+__global__ __launch_bounds__(64 * kBlockWaves) void k_block64(BlockArgs a, int stage) {
+    constexpr int Bp = 16 * CT;
+    __shared__ double red[kBlockWaves][CT * 256];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int lr = lane & 15, lk = lane >> 4;
+    const int r = blockIdx.y;
+    const int64_t M = a.M, row0 = (int64_t)blockIdx.x * 16;
+    const double* X = a.Xin + r * a.in_stride + 2 * lr;
+    const double* q = a.Qs[r] + (row0 + lr < M ? row0 + lr : M - 1) * a.ldq;
+    const int64_t kw = (M + 8 * kBlockWaves - 1) / (8 * kBlockWaves) * 8;
+    const int64_t k0 = wave * kw, k1 = k0 + kw < M ? k0 + kw : M;
+    lb_double4 acc[CT];
+#pragma unroll
+    for (int c = 0; c < CT; ++c) acc[c] = lb_double4{0, 0, 0, 0};
+    // U steps of 8 columns, all loads first
+    auto steps = [&](auto U, int64_t kc) __attribute__((always_inline)) {
+        constexpr int n = decltype(U)::value;
+        double2 qa[n], xa[n][CT];
+#pragma unroll
+        for (int u = 0; u < n; ++u) {
+            const double* p = q + kc + 8 * u + 2 * lk;
+            qa[u] = ALIGNED ? *reinterpret_cast<const double2*>(p) : make_double2(p[0], p[1]);
+#pragma unroll
+            for (int c = 0; c < CT; ++c)
+                xa[u][c] = *reinterpret_cast<const double2*>(X + (((kc + 8 * u) >> 1) + lk) * (2 * Bp) + 32 * c);
+        }
+#pragma unroll
+        for (int u = 0; u < n; ++u)
+#pragma unroll
+            for (int c = 0; c < CT; ++c) {
+                acc[c] = __builtin_amdgcn_mfma_f64_16x16x4f64(qa[u].x, xa[u][c].x, acc[c], 0, 0, 0);
+                acc[c] = __builtin_amdgcn_mfma_f64_16x16x4f64(qa[u].y, xa[u][c].y, acc[c], 0, 0, 0);
+            }
+    };
+    int64_t kc = k0;
+    for (; kc + 32 <= k1; kc += 32) steps(std::integral_constant<int, 4>(), kc);
+    for (; kc + 8 <= k1; kc += 8) steps(std::integral_constant<int, 1>(), kc);
+    if (kc < k1) {  // fewer than 8 columns, at the end of the row: nothing beyond M is read
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+            const int64_t k = kc + 2 * lk + e;
+            const bool ok = k < k1;
+            const double qv = ok ? q[k] : 0.0;
+#pragma unroll
+            for (int c = 0; c < CT; ++c)
+                acc[c] = __builtin_amdgcn_mfma_f64_16x16x4f64(
+                    qv, ok ? X[(k >> 1) * (2 * Bp) + (k & 1) + 32 * c] : 0.0, acc[c], 0, 0, 0);
+        }
+    }
+#pragma unroll
+    for (int c = 0; c < CT; ++c)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) red[wave][256 * c + 64 * j + lane] = acc[c][j];  // (row 4j + l/16, column l%16)
+    __syncthreads();
+    const int b = threadIdx.x % Bp, rp = threadIdx.x / Bp;
+    const int64_t row = row0 + 2 * rp;
+    if (rp >= 8 || row >= M) return;
+    const bool two = row + 1 < M;
+    const int i = (b >> 4) * 256 + 32 * rp + (b & 15);
+    lb_double2v k = {red[0][i], red[0][i + 16]};
+#pragma unroll
+    for (int w = 1; w < kBlockWaves; ++w) {
+        k.x += red[w][i];
+        k.y += red[w][i + 16];
+    }
+    k.x += a.Ks[r][row];
+    if (two) k.y += a.Ks[r][row + 1];
+    const int64_t idx = ilv2(row, b, Bp);
+    *reinterpret_cast<lb_double2v*>(a.Xout + r * a.out_stride + idx) =
+        stage_pair(stage, a.h, k, two, reinterpret_cast<lb_double2v*>(a.V + r * a.sstride + idx),
+                   reinterpret_cast<lb_double2v*>(a.Acc + r * a.sstride + idx));
 }
 
 // user layout (B, M) -> interleaved padded (Mp, Bp); padding rows/columns zero
@@ -1002,6 +1110,8 @@ static int64_t long_slabs(int64_t M, int Bp) {
 //   N = 20   16 rows   25 / 9.4       N = 80   32 rows   81 / 58
 //   N = 30   16 rows   22 / 11        N = 100  64 rows  162 / 132
 //   N = 60   32 rows   36 / 27        N = 128  64 rows  409 / 333
+// (k_block64 takes the smallest of these sizes where no tile is asked for; a server's
+// mixed batches and stage timings still run them as tiles).
 // Hence tiles of 16 rows below M = 2500, of 32 below 8200, of 64 beyond (32 for
 // 64 states in FP64, which fits two waves of that size on a SIMD), and as many
 // slabs as keep row tiles x slabs within 1024, or within 2048 where that fills
@@ -1085,6 +1195,11 @@ static lb_tile choose_tile(lb_ctx* c, int64_t M, int Bp, int precision, int R) {
     return lb_default_tile(M, Bp, precision, R);
 }
 
+// Whether choose_tile's answer was set or tuned (after it: the cache file is loaded then).
+static bool has_tile(lb_ctx* c, int64_t M, int Bp, int precision) {
+    return c->tuned.find(std::make_tuple(M, Bp, precision)) != c->tuned.end();
+}
+
 int lb_impl_q_to_f32(lb_ctx* c, int64_t M, const double* Q, int64_t ldq, float* Q32) {
     const int64_t n = M * ldq;
     hipLaunchKernelGGL(k_to_f32, dim3(lb_blocks(n, 256)), dim3(256), 0, c->stream, Q, Q32, n);
@@ -1102,6 +1217,17 @@ namespace {
 // per stage (N = 37: 78 us resident against 85; one step 55 us).
 constexpr int64_t kResidentSteps = 2;
 
+// FP64 blocks up to this size run a stage as one launch (k_block64) unless a tile was
+// set or tuned for them. A workgroup per 16 rows fills the chip in whole rounds: up to
+// 128 row tiles two systems fit one round and up to 169 three of them fit two; beyond,
+// two or three systems lose more than one gains (64 states, which keep a CU busier,
+// from 128 on). In us a stage, GEMM and combination / one launch:
+//   16 states:  N = 17  9.8 / 6.2    N = 30  12.3 / 9.1    N = 45  18.0 / 14.6
+//   64 states:  N = 17  12.1 / 8.1   N = 30  17.5 / 14.8   N = 45  29.4 / 26.4
+//   N = 51, 32 states, 1, 2, 3 systems:  25.5 / 23.6  40.0 / 37.4  59.1 / 40.1
+//   N = 49, 64 states, 2 systems 53 / 56; N = 58, 32 states, 3 systems 78 / 90
+static int64_t whole_limit(int Bp) { return Bp == 64 ? 2048 : 2704; }
+
 enum PathKind { PATH_SMALL, PATH_GEMV, PATH_MFMA };
 
 struct Plan {
@@ -1115,14 +1241,16 @@ struct Plan {
     size_t o_ptr, o_v, o_acc, o_x, o_x32, o_part, o_w, bytes;
     Rk4Small small;
     bool aligned;
+    bool whole;   // a stage is one launch of k_block64
     bool staged;  // every Q and every row of Q 128-byte aligned: LDS-staged GEMM, streaming GEMV loads
     const void** d;
     double *V, *Acc, *X, *Part, *W;
     float* X32;
 };
 
+// own_tile: the tile was set or tuned for this size, and is used.
 static int plan_make(Plan& p, int R, int64_t M, int64_t ldq, int B, int precision, const lb_tile& tile,
-                     bool allow_small) {
+                     bool allow_small, bool own_tile) {
     p = Plan();
     p.R = R;
     p.M = M;
@@ -1159,6 +1287,7 @@ static int plan_make(Plan& p, int R, int64_t M, int64_t ldq, int B, int precisio
         p.o_x = take(sizeof(double) * p.sstride * R);
         if (precision == LB_FP32) p.o_x32 = take(sizeof(float) * p.s32stride * R);
         p.o_part = take(sizeof(double) * p.pstride * R);
+        p.whole = allow_small && !own_tile && precision == LB_FP64 && M <= whole_limit(p.Bp);
         const int RT = tile.rows / 16, CT = p.Bp / 16;
         if (tile.rows % 16 || tile.kslab % 16 || tile.kslab <= 0 || tile.waves < 1 || tile.waves > 4 ||
             (precision == LB_FP64 ? (p.aligned ? pick64<true>(RT, CT) : pick64<false>(RT, CT)) == nullptr
@@ -1309,6 +1438,13 @@ static int plan_init_state(const Plan& p, hipStream_t s) {
     return LB_OK;
 }
 
+static int plan_unpack(const Plan& p, hipStream_t s) {
+    hipLaunchKernelGGL(k_unpack, dim3(lb_blocks(p.M * p.B, 256), p.R), dim3(256), 0, s,
+                       (double* const*)(p.d + 4 * p.R), p.M, p.B, p.Bp, (const double*)p.V, p.sstride);
+    LB_CHECK_LAUNCH();
+    return LB_OK;
+}
+
 // Enqueues the whole integration (kernels only: no synchronization, no copies),
 // so it can be recorded into a graph.
 static int plan_launch(const Plan& p, hipStream_t s, double dt, int64_t steps, const Rk4Resident& res) {
@@ -1345,6 +1481,33 @@ static int plan_launch(const Plan& p, hipStream_t s, double dt, int64_t steps, c
             }
         return LB_OK;
     }
+    if (p.whole) {
+        // x alternates between its buffer and that of the partial sums, which are not needed
+        typedef void (*block_fn)(BlockArgs, int);
+        const int CT = p.Bp / 16;
+        const block_fn fn = p.aligned ? (CT == 1 ? k_block64<1, true> : CT == 2 ? k_block64<2, true> : k_block64<4, true>)
+                                      : (CT == 1 ? k_block64<1, false> : CT == 2 ? k_block64<2, false> : k_block64<4, false>);
+        BlockArgs a;
+        a.Qs = (const double* const*)p.d;
+        a.Ks = (const double* const*)(p.d + 2 * p.R);
+        a.M = p.M;
+        a.ldq = p.ldq;
+        a.V = p.V;
+        a.Acc = p.Acc;
+        a.sstride = p.sstride;
+        a.h = dt;
+        for (int64_t st = 0; st < steps; ++st)
+            for (int stage = 1; stage <= 4; ++stage) {
+                const bool odd = stage & 1;
+                a.Xin = odd ? p.X : p.Part;
+                a.Xout = odd ? p.Part : p.X;
+                a.in_stride = odd ? p.sstride : p.pstride;
+                a.out_stride = odd ? p.pstride : p.sstride;
+                hipLaunchKernelGGL(fn, dim3((unsigned)(p.Mp / 16), p.R), dim3(64 * kBlockWaves), 0, s, a, stage);
+                LB_CHECK_LAUNCH();
+            }
+        return plan_unpack(p, s);
+    }
     const StageArgs sa = stage_args(p, dt);
     const dim3 sgrid(lb_blocks((p.M + 1) / 2 * p.Bp, 256), p.R);
     for (int64_t st = 0; st < steps; ++st)
@@ -1354,10 +1517,7 @@ static int plan_launch(const Plan& p, hipStream_t s, double dt, int64_t steps, c
             hipLaunchKernelGGL(p.precision == LB_FP64 ? k_stage<double> : k_stage<float>, sgrid, dim3(256), 0, s, sa, stage);
             LB_CHECK_LAUNCH();
         }
-    hipLaunchKernelGGL(k_unpack, dim3(lb_blocks(p.M * p.B, 256), p.R), dim3(256), 0, s,
-                       (double* const*)(p.d + 4 * p.R), p.M, p.B, p.Bp, (const double*)p.V, p.sstride);
-    LB_CHECK_LAUNCH();
-    return LB_OK;
+    return plan_unpack(p, s);
 }
 
 // Average duration (ms) of the dominant stage kernel over `iters` launches,
@@ -1391,7 +1551,8 @@ static int plan_time(lb_ctx* c, const Plan& p, int iters, double* ms) {
 static int plan_for(lb_ctx* c, Plan& p, int R, int64_t M, const lb_prop_sys* sys, int64_t ldq, int B, int precision,
                     const lb_tile* force_tile, bool allow_small) {
     const lb_tile tile = force_tile ? *force_tile : choose_tile(c, M, bpad(B), precision, R);
-    int rc = plan_make(p, R, M, ldq, B, precision, tile, allow_small && force_tile == nullptr);
+    int rc = plan_make(p, R, M, ldq, B, precision, tile, allow_small && force_tile == nullptr,
+                       has_tile(c, M, bpad(B), precision));
     if (rc) return rc;
     rc = lb_ws_reserve(c, p.bytes);
     if (rc) return rc;
@@ -1487,12 +1648,14 @@ int lb_impl_propagate_noalloc(lb_ctx* c, int64_t M, const lb_prop_sys* sys, int6
     if (!base) return lb_fail(LB_ERR_DEVICE, "the static scratch of device %d is not set up", c->device);
     Plan p;
     const int Bp = bpad(B);
-    int rc = plan_make(p, 1, M, ldq, B, precision, choose_tile(c, M, Bp, precision, 1), true);
+    const lb_tile tile = choose_tile(c, M, Bp, precision, 1);
+    const bool own = has_tile(c, M, Bp, precision);
+    int rc = plan_make(p, 1, M, ldq, B, precision, tile, true, own);
     if (rc) return rc;
     size_t need = p.bytes;
-    if (p.kind == PATH_MFMA && c->tuned.find(std::make_tuple(M, Bp, precision)) == c->tuned.end()) {
+    if (p.kind == PATH_MFMA && !own) {
         Plan lim;
-        rc = plan_make(lim, 1, M, ldq, B, precision, limit_tile(M, Bp), true);
+        rc = plan_make(lim, 1, M, ldq, B, precision, limit_tile(M, Bp), true, own);
         if (rc) return rc;
         need = std::max(need, lim.bytes);
     }
@@ -1543,7 +1706,7 @@ int lb_impl_propagate_graph(lb_ctx* c, int64_t M, const lb_prop_sys* sys, int64_
         }
         lb_graph_entry* g = new lb_graph_entry();
         const lb_tile tile = choose_tile(c, M, bpad(B), precision, 1);
-        int rc = plan_make(g->plan, 1, M, ldq, B, precision, tile, true);
+        int rc = plan_make(g->plan, 1, M, ldq, B, precision, tile, true, has_tile(c, M, bpad(B), precision));
         if (rc) {
             delete g;
             return rc;
