@@ -531,11 +531,11 @@ def config_c2(args):
     lb.lindblad_propagate_csr(ctx, rp, col, val, K, V, dt, 10)
     V = V0.clone()
     t_prop, _ = _timed(lambda: lb.lindblad_propagate_csr(ctx, rp, col, val, K, V, dt, S))
-    # algorithmic bytes per RK4 step: four passes over the stored entries (8 B value + 4 B column index,
-    # the kernel's format; its slice padding is not counted) and the CSR row pointers, plus the M-vectors
-    # touched once each: per step x in (4),
-    # K (4), v read (4) and written (1), accumulator read (3) and written (3), stage output (4)
-    bytes_step = 4 * (nnz * (8 + 4) + (M + 1) * 8) + 23 * M * 8
+    # algorithmic bytes per RK4 step: four passes over the stored values (8 B; the slices keep most columns
+    # once per 64 entries, and neither the others nor the slices' padding are counted), plus the M-vectors
+    # touched once each: per step x in (4, v itself in the first stage), K (4), v read (3) and written (1),
+    # accumulator read (3) and written (3), stage output (3)
+    bytes_step = 4 * nnz * 8 + 21 * M * 8
     gbs = S * bytes_step / t_prop / 1e9
     rho = lb.lb_reconstruct(ctx, V, N)[0].cpu().numpy()
     tr = abs(np.trace(rho) - 1)
@@ -613,9 +613,9 @@ def config_c2p(args):
     lb.lindblad_propagate_csr_drive(ctx, Q0, Q1, K, V, dt, 20, 0.0, E, A, T)
     V = V0.clone()
     t_prop, _ = _timed(lambda: lb.lindblad_propagate_csr_drive(ctx, Q0, Q1, K, V, dt, S, 0.0, E, A, T))
-    # algorithmic bytes per RK4 step: four passes over both matrices (8 B value + 4 B column per stored
-    # entry, row pointers) and the M-vectors touched once each (as for the static sparse path)
-    bytes_step = 4 * ((nnz0 + nnz1) * (8 + 4) + 2 * (M + 1) * 8) + 23 * M * 8
+    # algorithmic bytes per RK4 step: four passes over the stored values of both matrices and the M-vectors
+    # touched once each (as for the static sparse path)
+    bytes_step = 4 * (nnz0 + nnz1) * 8 + 21 * M * 8
     gbs = S * bytes_step / t_prop / 1e9
     rho = lb.lb_reconstruct(ctx, V, N)[0].cpu().numpy()
     # oracle parity on sampled rows of both matrices
