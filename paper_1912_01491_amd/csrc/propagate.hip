@@ -1375,9 +1375,11 @@ static StageArgs stage_args(const Plan& p, double dt) {
 // One launch of the stage GEMM (MFMA path) or the stage GEMV (stage 1).
 static int plan_gemm(const Plan& p, hipStream_t s, int stage, double dt) {
     if (p.kind == PATH_GEMV) {
-        // rows per wave: as many as keep at least ~8192 waves in the launch
+        // rows per wave: as many as keep at least ~8192 waves in the launch, and two of
+        // the long rows from M = 9000 on, where x is a second stream per wave (one row
+        // and two, in us a stage: N = 90 88 / 92, N = 97 118 / 110, N = 128 338 / 323)
         const int64_t rows_total = p.M * p.R;
-        const int RW = rows_total >= 8 * 8192 ? 8 : rows_total >= 4 * 8192 ? 4 : rows_total >= 2 * 8192 ? 2 : 1;
+        const int RW = rows_total >= 8 * 8192 ? 8 : rows_total >= 4 * 8192 ? 4 : rows_total >= 2 * 8192 || p.M >= 9000 ? 2 : 1;
         const unsigned gx = lb_blocks((p.M + RW - 1) / RW, 4);
         // The nontemporal hint pays once the systems' Q no longer fit the last-level
         // cache (256 MB), where a stage evicts what the next one reads first. One
