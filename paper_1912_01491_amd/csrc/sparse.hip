@@ -30,9 +30,10 @@
 // of a millisecond; what the phases cost is the latency of many small steps, so
 // every loop over N or M runs across lanes and the scans stay on the device.
 // N = 1000 dimer: 14.9 ms before, 0.97 ms as two calls (a count, and a fill that
-// has to count again), 0.58 ms as one, 0.50 ms with the pair rows' counts beside the
+// has to count again), 0.58 ms as one, 0.49 ms with the pair rows' counts beside the
 // diagonals' lists and the two fills beside each other on a second stream. Below
-// N = 400 launches are all of it: 0.24 ms at N = 100 with 30 of them, 0.19 ms with 22.
+// N = 400 launches and read-backs are all of it: 0.24 ms at N = 100 with 30 launches and three
+// read-backs, 0.16 ms with 22 and two.
 // Rows are written with sorted column indices (S block, J block, D block);
 // entries whose value is exactly zero are not stored.
 #include "lb_internal.h"
@@ -46,6 +47,7 @@ namespace {
 
 constexpr double kR = 0.70710678118654752440;
 constexpr int kMaxRowEntries = 64;  // entries of L^+(F_s) held per pair row
+constexpr int64_t kListEntries = 10 << 20;  // of the diagonals' lists, reserved unseen (28 bytes each)
 constexpr int kValueEntries = 24;   // up to which their values are held too
 
 struct Ell {
@@ -643,7 +645,7 @@ __global__ __launch_bounds__(256) void k_diag(DiagArgs g, unsigned nd, unsigned 
 struct DRowArgs {
     int N;
     int64_t Pp, M;
-    int64_t ncarry;
+    const int64_t* carrying;  // how many columns carry
     const int64_t* carry;   // carrying column indices, increasing
     const int64_t* off;     // per column offsets into pos/val (M+1)
     const int* pos;
@@ -662,10 +664,12 @@ struct DRowArgs {
 // diagonal generators (up to N entries, the last ncarry - npair of the carrying
 // ones) a wavefront: it loads 64 entries at once, the next 64 ahead, and passes
 // the running sum along the lanes.
-__global__ __launch_bounds__(64) void k_diag_prefix(int64_t npair, int64_t ncarry, unsigned pair_blocks,
+__global__ __launch_bounds__(64) void k_diag_prefix(int N, const int64_t* carrying, unsigned pair_blocks,
                                                     const int64_t* carry, const int64_t* off, const double* val,
                                                     double* pref) {
     const int lane = threadIdx.x;
+    // every diagonal generator's column carries (its list starts at position 0), after those of the pairs
+    const int64_t ncarry = *carrying, npair = ncarry - (N - 1);
     if (blockIdx.x < pair_blocks) {
         const int64_t t = (int64_t)blockIdx.x * 64 + lane;
         if (t >= npair) return;
@@ -735,8 +739,9 @@ __global__ __launch_bounds__(64 * kDrowWaves) void k_drows_sparse(DRowArgs g, in
         for (int x = threadIdx.x; x <= m; x += 64 * kDrowWaves) l1[x] = g.l1diag[x];
     const int64_t row = 2 * g.Pp + m - 1;
     const double nrm = 1.0 / sqrt((double)m * (m + 1));
-    const int64_t per = ((g.ncarry + kDrowWaves - 1) / kDrowWaves + 63) / 64 * 64;
-    const int64_t t0 = w * per, t1 = t0 + per < g.ncarry ? t0 + per : g.ncarry;
+    const int64_t ncarry = *g.carrying;
+    const int64_t per = ((ncarry + kDrowWaves - 1) / kDrowWaves + 63) / 64 * 64;
+    const int64_t t0 = w * per, t1 = t0 + per < ncarry ? t0 + per : ncarry;
     int64_t n = 0, c = 0;
     double q = 0.0;
     for (int64_t t = t0; t < t1; t += 64) n += __popcll(__ballot(drow_value(g, t + lane, t1, m, nrm, c, q)));
@@ -972,9 +977,19 @@ static int sparse_body(lb_ctx* c, int N, const lb_csr_c128* H, int P, const doub
     LB_CHECK_LAUNCH();
     rc = scan_counts(s, M, dcnt, dcnt, carry, scratch, tot);
     if (rc) return rc;
-    LB_HIP(hipMemcpyAsync(host, tot, info_bytes, hipMemcpyDeviceToHost, s));
-    LB_HIP(hipStreamSynchronize(s));
-    const int64_t dtotal = htot[0], ncarry = htot[1];
+    // The lists hold at most this many entries: a pair's column its two positions and
+    // those where the operators' columns meet, a diagonal generator's column N. Where
+    // that much is affordable the host does not wait for the exact number (35 us).
+    int64_t wide = 2;
+    for (int p = 0; p < P; ++p) wide += rates[p] != 0.0 ? hw[2 + 2 * p] : 0;
+    int64_t dtotal = 2 * Pp * std::min<int64_t>(wide, kMaxRowEntries) + (int64_t)(N - 1) * N;
+    unsigned pb = lb_blocks(2 * Pp, 64);
+    if (dtotal > kListEntries) {
+        LB_HIP(hipMemcpyAsync(host, tot, info_bytes, hipMemcpyDeviceToHost, s));
+        LB_HIP(hipStreamSynchronize(s));
+        dtotal = htot[0];
+        pb = lb_blocks(htot[1] - (N - 1), 64);
+    }
     size_t o3 = before_lists;
     auto take3 = [&](size_t bytes) {
         size_t o = o3;
@@ -992,20 +1007,14 @@ static int sparse_body(lb_ctx* c, int N, const lb_csr_c128* H, int P, const doub
     da.val = (double*)(ws + o_dval);
     hipLaunchKernelGGL(k_diag, dim3(nd + np), dim3(256), 0, s, da, nd, np, 1, l1, ovf + 1);
     LB_CHECK_LAUNCH();
-    {
-        // every diagonal generator's column carries (its list starts at position 0), after those of the pairs
-        const int64_t npair = ncarry - (N - 1);
-        const unsigned pb = lb_blocks(npair, 64);
-        hipLaunchKernelGGL(k_diag_prefix, dim3(pb + (unsigned)(N - 1)), dim3(64), 0, s, npair, ncarry, pb,
-                           (const int64_t*)carry, (const int64_t*)dcnt, (const double*)da.val,
-                           (double*)(ws + o_pref));
-        LB_CHECK_LAUNCH();
-    }
+    hipLaunchKernelGGL(k_diag_prefix, dim3(pb + (unsigned)(N - 1)), dim3(64), 0, s, N, (const int64_t*)(tot + 1), pb,
+                       (const int64_t*)carry, (const int64_t*)dcnt, (const double*)da.val, (double*)(ws + o_pref));
+    LB_CHECK_LAUNCH();
     DRowArgs dr;
     dr.N = N;
     dr.Pp = Pp;
     dr.M = M;
-    dr.ncarry = ncarry;
+    dr.carrying = tot + 1;
     dr.carry = carry;
     dr.off = dcnt;
     dr.pos = da.pos;
