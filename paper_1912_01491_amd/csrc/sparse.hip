@@ -802,10 +802,11 @@ struct AuxWork {
     }
 };
 
+// exact: read the length of the diagonals' lists back in any case.
 // Returns LB_OK, a negative status, or 1 when the workspace must grow to *want
 // bytes first (growing reallocates it, so the caller restarts from the top).
 static int sparse_body(lb_ctx* c, int N, const lb_csr_c128* H, int P, const double* rates, const lb_csr_c128* L,
-                       lb_sparse_alloc alloc, void* user, int64_t* nnz, size_t* want) {
+                       lb_sparse_alloc alloc, void* user, int64_t* nnz, bool exact, size_t* want) {
     hipStream_t s = c->stream;
     const int64_t M = (int64_t)N * N - 1;
     const int64_t Pp = lb_npairs(N);
@@ -984,7 +985,7 @@ static int sparse_body(lb_ctx* c, int N, const lb_csr_c128* H, int P, const doub
     for (int p = 0; p < P; ++p) wide += rates[p] != 0.0 ? hw[2 + 2 * p] : 0;
     int64_t dtotal = 2 * Pp * std::min<int64_t>(wide, kMaxRowEntries) + (int64_t)(N - 1) * N;
     unsigned pb = lb_blocks(2 * Pp, 64);
-    if (dtotal > kListEntries) {
+    if (exact || dtotal > kListEntries) {
         LB_HIP(hipMemcpyAsync(host, tot, info_bytes, hipMemcpyDeviceToHost, s));
         LB_HIP(hipStreamSynchronize(s));
         dtotal = htot[0];
@@ -1057,12 +1058,15 @@ static int sparse_body(lb_ctx* c, int N, const lb_csr_c128* H, int P, const doub
 int lb_impl_sparse(lb_ctx* c, int N, const lb_csr_c128* H, int P, const double* rates, const lb_csr_c128* L,
                    lb_sparse_alloc alloc, void* user, int64_t* nnz) {
     size_t want = 0;
-    for (int attempt = 0; attempt < 4; ++attempt) {
+    bool exact = false;  // the diagonals' lists at their own size: where their bound's does not fit
+    for (int attempt = 0; attempt < 8; ++attempt) {
         if (want) {
             int rc = lb_ws_reserve(c, want);
-            if (rc) return rc;
+            want = 0;
+            if (rc == LB_ERR_OOM && !exact) exact = true;
+            else if (rc) return rc;
         }
-        int rc = sparse_body(c, N, H, P, rates, L, alloc, user, nnz, &want);
+        int rc = sparse_body(c, N, H, P, rates, L, alloc, user, nnz, exact, &want);
         if (rc != 1) return rc;
     }
     return lb_fail(LB_ERR_OOM, "sparse workspace sizing did not converge");
