@@ -30,7 +30,7 @@
 // of a millisecond; what the phases cost is the latency of many small steps, so
 // every loop over N or M runs across lanes and the scans stay on the device.
 // N = 1000 dimer: 14.9 ms before, 0.97 ms as two calls (a count, and a fill that
-// has to count again), 0.58 ms as one, 0.49 ms with the pair rows' counts beside the
+// has to count again), 0.58 ms as one, 0.47 ms with the pair rows' counts beside the
 // diagonals' lists and the two fills beside each other on a second stream. Below
 // N = 400 launches and read-backs are all of it: 0.24 ms at N = 100 with 30 launches and three
 // read-backs, 0.16 ms with 22 and two.
@@ -253,6 +253,7 @@ struct PairArgs {
     int nact;
     // outputs
     int64_t* cnt;          // count phase: entries per row
+    int* ns;               // entries in the S block, from the count to the fill
     const int64_t* rowptr; // fill phase
     int64_t* col;
     double* val;
@@ -382,43 +383,46 @@ __global__ __launch_bounds__(64) void k_pair_rows(PairArgs g, int fill) {
     const uint32_t diag0 = (uint32_t)(2 * Pp);
     // Off-diagonal entries come first, pair by pair: Y_pq (p < q) and Y_qp, each
     // the sum of its entries in the order they were formed. Tr(Y S_pq) =
-    // r (Y_pq + Y_qp); Tr(Y J_pq) = i r (Y_pq - Y_qp). The S block of the row,
-    // then the J block; the count phase takes both in one pass.
+    // r (Y_pq + Y_qp); Tr(Y J_pq) = i r (Y_pq - Y_qp). The S block of the row
+    // is followed by the J block; the count's number of S entries lets the fill write
+    // both in one pass over the pairs.
     constexpr uint32_t kEnd = 0xffffffffu;
     auto key_at = [&](int i) { return i < n ? key[i * 64] : kEnd; };
     const uint32_t dkey = diag0 << 6;  // keys of diagonal entries start here
-    int64_t o = fill && live ? g.rowptr[s] : 0;
+    int64_t o = fill && live ? g.rowptr[s] : 0, oj = fill && live ? o + g.ns[s] : 0;
     int nd0 = 0;  // first diagonal entry
-    for (int part = 0; part < (fill ? 2 : 1); ++part) {
-        int i = 0;
-        uint32_t k = key_at(0), kn = key_at(1);
-        cd e = k < dkey ? val_of(k) : cmk(0, 0);
-        while (k < dkey) {
-            const uint32_t pr = k >> 7;
-            cd y0 = cmk(0, 0), y1 = cmk(0, 0);
-            do {
-                const cd en = kn < dkey ? val_of(kn) : cmk(0, 0);  // the next entry's on its way
-                if (k & 64u) y1 = cadd(y1, e);
-                else y0 = cadd(y0, e);
-                e = en;
-                k = kn;
-                ++i;
-                kn = key_at(i + 1);
-            } while ((k >> 7) == pr && k < dkey);
-            const double qs = kR * (y0.re + y1.re), qj = -kR * (y0.im - y1.im);
-            if (!fill) {
-                o += (qs != 0.0) + (qj != 0.0);
-            } else {
-                const double q = part == 0 ? qs : qj;
-                if (q != 0.0) {
-                    g.col[o] = part * Pp + pr;
-                    g.val[o] = q;
-                    ++o;
-                }
+    uint32_t k = key_at(0), kn = key_at(1);
+    cd e = k < dkey ? val_of(k) : cmk(0, 0);
+    while (k < dkey) {
+        const uint32_t pr = k >> 7;
+        cd y0 = cmk(0, 0), y1 = cmk(0, 0);
+        do {
+            const cd en = kn < dkey ? val_of(kn) : cmk(0, 0);  // the next entry's on its way
+            if (k & 64u) y1 = cadd(y1, e);
+            else y0 = cadd(y0, e);
+            e = en;
+            k = kn;
+            ++nd0;
+            kn = key_at(nd0 + 1);
+        } while ((k >> 7) == pr && k < dkey);
+        const double qs = kR * (y0.re + y1.re), qj = -kR * (y0.im - y1.im);
+        if (qs != 0.0) {
+            if (fill) {
+                g.col[o] = pr;
+                g.val[o] = qs;
             }
+            ++o;
         }
-        nd0 = i;
+        if (qj != 0.0) {
+            if (fill) {
+                g.col[oj] = Pp + pr;
+                g.val[oj] = qj;
+            }
+            ++oj;
+        }
     }
+    if (!fill && live) g.ns[s] = (int)o;
+    o = fill ? oj : o + oj;
     // Diagonal entries (merged by position): Tr Y, and the D columns m from
     // max(1, first position) to the last position, or to N-1 when Tr(Y) != 0:
     // beyond the last position the value is Tr(Y)/sqrt(m(m+1)).
@@ -828,6 +832,7 @@ static int sparse_body(lb_ctx* c, int N, const lb_csr_c128* H, int P, const doub
     const size_t o_ells = take(sizeof(Ell) * nsets + sizeof(int) * kMaxRowEntries);  // then the pair rows' operators
     const size_t o_rowcnt = take(sizeof(int64_t) * (M + 1));
     const size_t o_dcnt = take(sizeof(int64_t) * (M + 1));
+    const size_t o_ns = take(sizeof(int) * 2 * (size_t)Pp);
     const size_t o_carry = take(sizeof(int64_t) * (M + 1));
     const size_t o_scan = take(sizeof(int64_t) * scan_scratch(M));
     // read back: scan totals (diagonal entries, carrying columns; stored entries, -), overflow flags, ELL widths
@@ -953,6 +958,7 @@ static int sparse_body(lb_ctx* c, int N, const lb_csr_c128* H, int P, const doub
     pa.act = (const int*)(dells + nsets);
     pa.nact = nact;
     pa.cnt = rowcnt;
+    pa.ns = (int*)(ws + o_ns);
     pa.rowptr = nullptr;
     pa.col = nullptr;
     pa.val = nullptr;
