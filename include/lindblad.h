@@ -503,7 +503,9 @@ int lb_read_bandwidth(lb_ctx* ctx, size_t bytes, double* gbs);
 /* Times the candidate GEMM tile shapes for (M, B, precision) on the context
  * stream and keeps the fastest for later propagate calls in this process
  * (and in the cache file named by the LB_TUNE_CACHE environment variable,
- * if set). Q/Q32 and K as for lindblad_propagate; V is scratch (B*M). */
+ * if set). Q/Q32 and K as for lindblad_propagate; V is scratch (B*M).
+ * FP64 blocks of up to 2704 rows (2048 for more than 32 states) run a stage as
+ * one launch whatever tile is the fastest, unless lindblad_set_tile asks for one. */
 int lindblad_autotune(lb_ctx* ctx, int64_t M, const double* Q, const float* Q32, int64_t ldq,
                       const double* K, double* V, int B, int precision);
 

@@ -662,6 +662,7 @@ int lindblad_set_tile(lb_ctx* c, int64_t M, int B, int precision, int rows, int 
         return lb_fail(LB_ERR_INVALID_ARG, "tile rows=%d kslab=%d waves=%d out of range", rows, kslab, waves);
     const int Bp = B <= 16 ? 16 : (B <= 32 ? 32 : 64);
     c->tuned[std::make_tuple(M, Bp, precision)] = lb_tile{rows, kslab, waves};
+    c->measured.erase(std::make_tuple(M, Bp, precision));
     return LB_OK;
 }
 

@@ -6,6 +6,7 @@
 #include <stdint.h>
 
 #include <map>
+#include <set>
 #include <string>
 #include <tuple>
 #include <vector>
@@ -70,6 +71,7 @@ struct lb_ctx {
     size_t host_bytes = 0;
     // tuned tile shapes: key (M, Bp, precision)
     std::map<std::tuple<int64_t, int, int>, lb_tile> tuned;
+    std::set<std::tuple<int64_t, int, int>> measured;  // of these, the fastest of several, not asked for
     bool cache_loaded = false;
     // auxiliary stream for work that overlaps the context stream's (dense
     // preparation), joined back with events; created on first use

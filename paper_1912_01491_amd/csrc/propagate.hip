@@ -1172,8 +1172,10 @@ static void load_tune_cache(lb_ctx* c) {
     if (!f) return;
     long long M;
     int Bp, prec, rows, ks, waves;
-    while (fscanf(f, "%lld %d %d %d %d %d", &M, &Bp, &prec, &rows, &ks, &waves) == 6)
+    while (fscanf(f, "%lld %d %d %d %d %d", &M, &Bp, &prec, &rows, &ks, &waves) == 6) {
         c->tuned[std::make_tuple((int64_t)M, Bp, prec)] = lb_tile{rows, ks, waves};
+        c->measured.insert(std::make_tuple((int64_t)M, Bp, prec));
+    }
     fclose(f);
 }
 
@@ -1195,9 +1197,13 @@ static lb_tile choose_tile(lb_ctx* c, int64_t M, int Bp, int precision, int R) {
     return lb_default_tile(M, Bp, precision, R);
 }
 
-// Whether choose_tile's answer was set or tuned (after it: the cache file is loaded then).
+// Whether choose_tile's answer was set or tuned (after it: the cache file is loaded then),
+// and whether it was set: the fastest of several tiles gives way to a stage in one launch.
 static bool has_tile(lb_ctx* c, int64_t M, int Bp, int precision) {
-    return c->tuned.find(std::make_tuple(M, Bp, precision)) != c->tuned.end();
+    return c->tuned.count(std::make_tuple(M, Bp, precision)) != 0;
+}
+static bool asked_tile(lb_ctx* c, int64_t M, int Bp, int precision) {
+    return has_tile(c, M, Bp, precision) && !c->measured.count(std::make_tuple(M, Bp, precision));
 }
 
 int lb_impl_q_to_f32(lb_ctx* c, int64_t M, const double* Q, int64_t ldq, float* Q32) {
@@ -1218,7 +1224,7 @@ namespace {
 constexpr int64_t kResidentSteps = 2;
 
 // FP64 blocks up to this size run a stage as one launch (k_block64) unless a tile was
-// set or tuned for them. A workgroup per 16 rows fills the chip in whole rounds: up to
+// set for them. A workgroup per 16 rows fills the chip in whole rounds: up to
 // 128 row tiles two systems fit one round and up to 169 three of them fit two; beyond,
 // two or three systems lose more than one gains (64 states, which keep a CU busier,
 // from 128 on). In us a stage, GEMM and combination / one launch:
@@ -1248,7 +1254,7 @@ struct Plan {
     float* X32;
 };
 
-// own_tile: the tile was set or tuned for this size, and is used.
+// own_tile: the tile was asked for, and is used.
 static int plan_make(Plan& p, int R, int64_t M, int64_t ldq, int B, int precision, const lb_tile& tile,
                      bool allow_small, bool own_tile) {
     p = Plan();
@@ -1554,7 +1560,7 @@ static int plan_for(lb_ctx* c, Plan& p, int R, int64_t M, const lb_prop_sys* sys
                     const lb_tile* force_tile, bool allow_small) {
     const lb_tile tile = force_tile ? *force_tile : choose_tile(c, M, bpad(B), precision, R);
     int rc = plan_make(p, R, M, ldq, B, precision, tile, allow_small && force_tile == nullptr,
-                       has_tile(c, M, bpad(B), precision));
+                       asked_tile(c, M, bpad(B), precision));
     if (rc) return rc;
     rc = lb_ws_reserve(c, p.bytes);
     if (rc) return rc;
@@ -1652,7 +1658,7 @@ int lb_impl_propagate_noalloc(lb_ctx* c, int64_t M, const lb_prop_sys* sys, int6
     const int Bp = bpad(B);
     const lb_tile tile = choose_tile(c, M, Bp, precision, 1);
     const bool own = has_tile(c, M, Bp, precision);
-    int rc = plan_make(p, 1, M, ldq, B, precision, tile, true, own);
+    int rc = plan_make(p, 1, M, ldq, B, precision, tile, true, asked_tile(c, M, Bp, precision));
     if (rc) return rc;
     size_t need = p.bytes;
     if (p.kind == PATH_MFMA && !own) {
@@ -1708,7 +1714,7 @@ int lb_impl_propagate_graph(lb_ctx* c, int64_t M, const lb_prop_sys* sys, int64_
         }
         lb_graph_entry* g = new lb_graph_entry();
         const lb_tile tile = choose_tile(c, M, bpad(B), precision, 1);
-        int rc = plan_make(g->plan, 1, M, ldq, B, precision, tile, true, has_tile(c, M, bpad(B), precision));
+        int rc = plan_make(g->plan, 1, M, ldq, B, precision, tile, true, asked_tile(c, M, bpad(B), precision));
         if (rc) {
             delete g;
             return rc;
@@ -1765,7 +1771,8 @@ int lb_impl_autotune(lb_ctx* c, int64_t M, const lb_prop_sys* sys, int64_t ldq, 
     std::vector<int> waves_c = {1, 2, 4};
     std::vector<int> target_c = {1, 1250, 2500, 5000, 10000};  // 1: one slab per row block
     lb_tile best = lb_default_tile(M, Bp, precision, 1);
-    double best_ms = 1e30;
+    double best_ms = 1e30, ms0 = 0;
+    if (!lb_impl_time_stage(c, 1, M, sys, ldq, B, precision, 3, &ms0, &best)) best_ms = ms0;
     for (int rows : rows_c)
         for (int waves : waves_c)
             for (int target : target_c) {
@@ -1787,6 +1794,7 @@ int lb_impl_autotune(lb_ctx* c, int64_t M, const lb_prop_sys* sys, int64_t ldq, 
                 }
             }
     c->tuned[std::make_tuple(M, Bp, precision)] = best;
+    c->measured.insert(std::make_tuple(M, Bp, precision));
     if (const char* path = getenv("LB_TUNE_CACHE")) {
         FILE* f = fopen(path, "a");
         if (f) {
