@@ -209,9 +209,14 @@ int lindblad_prepare_sparse(lb_ctx* ctx, int N, const lb_csr_c128* H, int P, con
  * of leading dimension ldq. precision LB_FP64 uses Q directly; LB_FP32
  * requires Q32 (device float, same ldq) from lindblad_q_to_f32 and ignores
  * Q. Bit-for-bit deterministic for fixed inputs and launch configuration.
- * One FP64 state of 256 < M <= 4096 runs as one cooperative launch that takes the
- * whole GPU for the call (HIP runs one such launch at a time; a launch per stage,
- * with the same bits, where it is not available or the stream is being captured).
+ * One FP64 state of 256 < M <= 4096 is integrated with Q held on the chip, by a
+ * workgroup per 16 rows that all have to be there at once. Where other streams' or
+ * processes' kernels keep some of them off for longer than 2 ms (40 us a step, if
+ * that is less), they leave and the call is carried out without, in 1 to 2 times the
+ * time of a launch per stage: same result, bit for bit, and V is not written before
+ * (lindblad_set_resident_wait). Calls of M > 2048 take the whole GPU and run one
+ * after the other; smaller ones run side by side. A stream that is being captured
+ * records a launch per stage, with the same bits.
  * When Q (or Q32) starts on a 128-byte boundary and its rows are 128-byte
  * multiples (ldq a multiple of 16 in FP64, 32 in FP32), the stage GEMM stages
  * Q through LDS with full-line streaming loads; otherwise it loads the matrix
@@ -523,6 +528,13 @@ int lindblad_time_stage(lb_ctx* ctx, int R, int64_t M, const double* const* Q, c
  * kernel are rejected at propagate time), k-slab length (multiple of 16) and
  * waves per workgroup (1..4). */
 int lindblad_set_tile(lb_ctx* ctx, int64_t M, int B, int precision, int rows, int kslab, int waves);
+
+/* How long the one-state integration of 256 < M <= 4096 (lindblad_propagate) waits
+ * with Q on the chip before it is carried out without: start_ms (2) for all of its
+ * workgroups to be on the chip, never longer than 40 us a step, and stage_ms (2000)
+ * for any one of them afterwards. 0 gives up at the first wait; start_ms < 0 takes a
+ * launch per stage from the outset. The result is the same bit for bit. Host only. */
+int lindblad_set_resident_wait(lb_ctx* ctx, double start_ms, double stage_ms);
 
 /* Describes the tile shape propagate will use for (M, B, precision):
  * rows per wave, k-slab length, waves per workgroup, and whether it came

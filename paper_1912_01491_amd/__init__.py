@@ -26,7 +26,7 @@ __all__ = [
     "lindblad_propagate_batched",
     "lindblad_propagate_graph", "lindblad_graph_clear", "lindblad_propagate_csr", "lindblad_prepare_sparse",
     "lindblad_propagate_csr_drive", "lb_eigh", "Secular", "read_bandwidth", "gemm_f64", "gemm_c128", "lb_hessenberg", "lindblad_spectrum",
-    "lindblad_spectrum_histogram", "save_system", "load_system", "load_system_info", "lindblad_steady_state", "lindblad_steady_state_csr", "lindblad_autotune", "lindblad_tile_info", "lindblad_set_tile", "lindblad_time_stage", "Server",
+    "lindblad_spectrum_histogram", "save_system", "load_system", "load_system_info", "lindblad_steady_state", "lindblad_steady_state_csr", "lindblad_autotune", "lindblad_tile_info", "lindblad_set_tile", "lindblad_set_resident_wait", "lindblad_time_stage", "Server",
     "FP64", "FP32", "CHECK_HERMITIAN",
 ]
 
@@ -134,6 +134,7 @@ def signatures():
         "lindblad_autotune": [V, I64, V, V, I64, V, V, I, I],
         "lindblad_tile_info": [V, I64, I, I, V, V, V, V],
         "lindblad_set_tile": [V, I64, I, I, I, I, I],
+        "lindblad_set_resident_wait": [V, D, D],
         "lindblad_time_stage": [V, I, I64, V, V, I64, V, V, I, I, I, V],
         "lindblad_server_create": [I, ctypes.c_size_t, I, I, I, ctypes.POINTER(ctypes.c_void_p)],
         "lindblad_server_submit": [V, V, V],
@@ -762,6 +763,12 @@ def lindblad_graph_clear(ctx: Context) -> int:
     n = ctypes.c_int()
     _check(load().lindblad_graph_clear(ctx.handle, ctypes.byref(n)))
     return n.value
+
+
+def lindblad_set_resident_wait(ctx: Context, start_ms: float, stage_ms: float = 2000.0):
+    """How long the one-state integration of 256 < M <= 4096 waits for the chip before it is carried out
+    without holding Q there (start_ms < 0: never holds it). Same result, bit for bit."""
+    _check(load().lindblad_set_resident_wait(ctx.handle, float(start_ms), float(stage_ms)))
 
 
 def lindblad_set_tile(ctx: Context, M: int, B: int, rows: int, kslab: int, waves: int, precision: int = FP64):

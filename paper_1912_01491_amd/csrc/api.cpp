@@ -666,6 +666,15 @@ int lindblad_set_tile(lb_ctx* c, int64_t M, int B, int precision, int rows, int 
     return LB_OK;
 }
 
+int lindblad_set_resident_wait(lb_ctx* c, double start_ms, double stage_ms) {
+    if (!c) return lb_fail(LB_ERR_INVALID_ARG, "null context");
+    if (!(start_ms <= 1e9) || !(stage_ms >= 0 && stage_ms <= 1e9))
+        return lb_fail(LB_ERR_INVALID_ARG, "waits of %g and %g ms out of range", start_ms, stage_ms);
+    c->resident_start = start_ms < 0 ? -1 : (int64_t)(start_ms * 1e5);
+    c->resident_run = (int64_t)(stage_ms * 1e5);
+    return LB_OK;
+}
+
 int lindblad_tile_info(lb_ctx* c, int64_t M, int B, int precision, int* rows, int* kslab, int* waves, int* tuned) {
     if (!c) return lb_fail(LB_ERR_INVALID_ARG, "null context");
     const int Bp = B <= 16 ? 16 : (B <= 32 ? 32 : 64);

@@ -73,6 +73,9 @@ struct lb_ctx {
     std::map<std::tuple<int64_t, int, int>, lb_tile> tuned;
     std::set<std::tuple<int64_t, int, int>> measured;  // of these, the fastest of several, not asked for
     bool cache_loaded = false;
+    // how long a resident run waits for its workgroups to be on the chip (negative: none is
+    // tried) and for one of them, in ticks of the 100 MHz clock: 2 ms and 2 s
+    int64_t resident_start = 200 * 1000, resident_run = 200 * 1000 * 1000;
     // auxiliary stream for work that overlaps the context stream's (dense
     // preparation), joined back with events; created on first use
     hipStream_t aux = nullptr;

@@ -9,8 +9,8 @@
 // Dense paths (per stage):
 //   * B = 1: k_gemv -- one wavefront per group of rows, lanes along the row,
 //     cross-lane reduction, stage combine fused into the same kernel; for one
-//     system of 256 < M <= 4096, rk4_resident.h -- one cooperative launch runs
-//     all steps with Q on the chip.
+//     system of 256 < M <= 4096, rk4_resident.h -- one launch runs all steps
+//     with Q on the chip.
 //   * B >= 2: k_gemm64 / k_gemm32 -- split-K GEMM on the matrix cores
 //     (v_mfma_f64_16x16x4f64, v_mfma_f32_16x16x4f32) writing per-slab
 //     partial sums, followed by k_stage which reduces the slabs in a fixed
@@ -1219,9 +1219,15 @@ int lb_impl_q_to_f32(lb_ctx* c, int64_t M, const double* Q, int64_t ldq, float* 
 
 namespace {
 
-// The cooperative launch and the load of Q cost about 45 us: two steps of a launch
-// per stage (N = 37: 78 us resident against 85; one step 55 us).
+// The load of Q, the arrivals and the two launches around them: a whole call of two
+// steps, a launch per stage / resident, in us: N = 17 75 / 49, N = 37 71 / 61, N = 64
+// 207 / 113.
 constexpr int64_t kResidentSteps = 2;
+// The wait for the chip is no longer than about what a launch per stage takes more in the
+// run's steps: 40 us each.
+constexpr int64_t kResidentStepTicks = 4000;
+
+constexpr int kMaxDevices = 64;
 
 // FP64 blocks up to this size run a stage as one launch (k_block64) unless a tile was
 // set for them. A workgroup per 16 rows fills the chip in whole rounds: up to
@@ -1277,7 +1283,7 @@ static int plan_make(Plan& p, int R, int64_t M, int64_t ldq, int B, int precisio
         p.kind = PATH_GEMV;
         p.aligned = ldq % 2 == 0;
         p.wstride = 3 * (int64_t)lb_align(M, 32);
-        p.o_w = take(sizeof(double) * p.wstride * R);
+        p.o_w = take(sizeof(double) * p.wstride * R + (R == 1 && rk4_resident_range(M) ? rk4_resident_bytes(M) : 0));
     } else {
         p.kind = PATH_MFMA;
         p.Bp = bpad(B);
@@ -1453,25 +1459,45 @@ static int plan_unpack(const Plan& p, hipStream_t s) {
     return LB_OK;
 }
 
+// The resident run and what follows it. Two that need more than half of the chip
+// each could both be on it in part and wait in vain until one gives way, so those of
+// a device are enqueued one behind the other, whatever their streams.
+struct WideOrder {
+    std::mutex mu;
+    hipEvent_t last = nullptr;
+};
+WideOrder g_wide[kMaxDevices];
+
+static int resident_launch(const Plan& p, hipStream_t s, double dt, int64_t steps, const Rk4Resident& res) {
+    const int64_t stride = rk4_resident_stride(p.M), n = 3 * stride;
+    double* out = p.W + n;
+    ResidentCtl* ctl = (ResidentCtl*)(out + stride);
+    const double* const* q = (const double* const*)p.d;
+    const double* const* k = (const double* const*)(p.d + 2 * p.R);
+    double* const* v = (double* const*)(p.d + 3 * p.R);
+    WideOrder& wide = g_wide[res.device];
+    std::unique_lock<std::mutex> lk(wide.mu, std::defer_lock);
+    if (res.wide) {
+        lk.lock();
+        LB_HIP(hipStreamWaitEvent(s, wide.last, 0));
+    }
+    hipLaunchKernelGGL(k_resident_init, dim3(lb_blocks(n, 256)), dim3(256), 0, s, p.W, n, ctl);
+    LB_CHECK_LAUNCH();
+    hipLaunchKernelGGL(res.fn, dim3(res.grid), dim3(256), 0, s, q, k, v, (int)p.M, p.ldq, p.W, stride, dt, steps, out,
+                       ctl, res.start, res.run);
+    LB_CHECK_LAUNCH();
+    if (res.wide) LB_HIP(hipEventRecord(wide.last, s));
+    hipLaunchKernelGGL(p.aligned ? k_resident_end<true> : k_resident_end<false>, dim3(res.grid), dim3(1024), 0, s, q, k,
+                       v, (int)p.M, p.ldq, p.W, stride, dt, steps, (const double*)out, ctl);
+    LB_CHECK_LAUNCH();
+    return LB_OK;
+}
+
 // Enqueues the whole integration (kernels only: no synchronization, no copies),
 // so it can be recorded into a graph.
 static int plan_launch(const Plan& p, hipStream_t s, double dt, int64_t steps, const Rk4Resident& res) {
     if (steps == 0) return LB_OK;
-    if (res.fn) {
-        const int64_t n = 3 * (int64_t)lb_align(p.M, 32);
-        hipLaunchKernelGGL(k_resident_init, dim3(lb_blocks(n, 256)), dim3(256), 0, s, p.W, n);
-        LB_CHECK_LAUNCH();
-        const double* const* q = (const double* const*)p.d;
-        const double* const* k = (const double* const*)(p.d + 2 * p.R);
-        double* const* v = (double* const*)(p.d + 3 * p.R);
-        int M = (int)p.M, spins = 1 << 20;
-        int64_t ldq = p.ldq, stride = lb_align(p.M, 32);
-        double* w = p.W;
-        void* args[] = {&q, &k, &v, &M, &ldq, &w, &stride, &dt, &steps, &spins};
-        if (hipLaunchCooperativeKernel((const void*)res.fn, dim3(res.grid), dim3(256), args, 0, s) == hipSuccess)
-            return LB_OK;
-        (void)hipGetLastError();  // not launched: a launch per stage, with the same bits
-    }
+    if (res.fn) return resident_launch(p, s, dt, steps, res);
     if (p.kind == PATH_SMALL) {
         hipLaunchKernelGGL(p.small.fn, dim3(p.R, p.B), dim3(p.small.threads), 0, s, (const double* const*)p.d,
                            (const double* const*)(p.d + 2 * p.R), (double* const*)(p.d + 3 * p.R), (int)p.M, p.ldq,
@@ -1568,16 +1594,21 @@ static int plan_for(lb_ctx* c, Plan& p, int R, int64_t M, const lb_prop_sys* sys
 }
 
 // The resident kernel for this plan, or none: one system, one state, enough steps
-// to pay for the cooperative launch and the load of Q, and a stream that is not
-// being captured. It sums a row as k_gemv does: the same bits either way.
+// to pay for the load of Q and two more launches, a stream that is not being captured,
+// and not switched off for the context. It sums a row as k_gemv does: the same bits either way.
 static Rk4Resident plan_resident(lb_ctx* c, const Plan& p, int64_t steps) {
     Rk4Resident r;
-    if (p.kind != PATH_GEMV || p.R != 1 || steps < kResidentSteps) return r;
+    if (p.kind != PATH_GEMV || p.R != 1 || steps < kResidentSteps || c->resident_start < 0) return r;
     r = rk4_resident_pick(p.M);
     if (!r.fn) return r;
+    r.device = c->device;
+    r.start = std::min(c->resident_start, steps < (1 << 20) ? steps * kResidentStepTicks : c->resident_start);
+    r.run = c->resident_run;
+    const unsigned cus = (unsigned)rk4_compute_units(c->device);
+    r.wide = 2 * r.grid > cus;
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(c->stream, &cap) != hipSuccess) (void)hipGetLastError();
-    if (cap != hipStreamCaptureStatusNone || !rk4_resident_fits(c->device, r.grid)) r.fn = nullptr;
+    if (cap != hipStreamCaptureStatusNone || r.grid > cus) r.fn = nullptr;
     return r;
 }
 
@@ -1616,7 +1647,6 @@ static __device__ __align__(256) double scratch[kScratchBytes / sizeof(double)];
 
 namespace {
 
-constexpr int kMaxDevices = 64;
 std::mutex g_scratch_mu;
 void* g_scratch[kMaxDevices];  // device address of `scratch` on each GPU
 
@@ -1632,7 +1662,8 @@ __global__ void k_set_ptrs(const void** d, const void* q, const void* q32, const
 
 }  // namespace
 
-// Looks up the array's device address once per device; `device` must be current.
+// Looks up the array's device address once per device, and makes the event that orders the wide
+// resident runs there, so that no later call has to; `device` must be current.
 int lb_scratch_init(int device) {
     if (device < 0 || device >= kMaxDevices) return lb_fail(LB_ERR_UNSUPPORTED, "device %d beyond %d", device, kMaxDevices);
     std::lock_guard<std::mutex> lk(g_scratch_mu);
@@ -1641,6 +1672,7 @@ int lb_scratch_init(int device) {
     const hipError_t e = hipGetSymbolAddress(&ptr, HIP_SYMBOL(scratch));
     if (e != hipSuccess || !ptr)
         return lb_fail(LB_ERR_DEVICE, "hipGetSymbolAddress(scratch) on device %d: %s", device, hipGetErrorString(e));
+    LB_HIP(hipEventCreateWithFlags(&g_wide[device].last, hipEventDisableTiming));
     g_scratch[device] = ptr;
     return LB_OK;
 }

@@ -1,14 +1,26 @@
 // RK4 of one dense system and one state with Q resident on the chip (256 < M <=
-// 4096): a cooperative launch of one workgroup per compute unit holds Q in
-// registers and LDS for all steps and exchanges only the stage vector.
+// 4096): a launch of one workgroup per 16 rows holds Q in registers and LDS for all
+// steps and exchanges only the stage vector.
 //
-// One launch per stage reads Q again from the last-level cache: 22.9 us for the
+// One launch per stage reads Q again from the last-level cache: 22.1 us for the
 // 134 MB of N = 64, of which 19 are the read, and 4 to 6 us for systems of a few
 // MB, most of it the launch. Resident, a stage is the exchange of M doubles
 // through memory (a write and a poll, about 2 us) and M multiply-adds per row: us
-// a stage, before and now, N = 20: 4.2 / 2.1, N = 37: 5.7 / 2.9, N = 50: 11.3 / 4.2,
-// N = 64: 22.3 / 5.9. Registers and LDS hold 4096 x 4096 doubles (134 MB of 168);
+// a stage of 100 steps, launches and resident, N = 20: 4.4 / 2.0, N = 37: 5.1 / 2.8,
+// N = 50: 11.1 / 4.2, N = 64: 22.1 / 5.9. As a cooperative launch, which HIP runs one
+// at a time, N = 37 took 3.0, and 8 threads with N = 17 each 18.1 between them,
+// now 4.4. Registers and LDS hold 4096 x 4096 doubles (134 MB of 168);
 // larger systems stream.
+//
+// The workgroups wait for each other, so all of them have to be on the chip at
+// once. Other streams and processes may hold a part of it for any time, and no
+// launch keeps them off, so the workgroups first count themselves in: the last one
+// to arrive decides that they go; one that has waited for `start` decides that they
+// leave, whichever comes first. From then on each wait is for a workgroup that
+// runs. A wait beyond `run` all the same (a process put aside) ends the attempt.
+// V is written by the kernel behind it, k_resident_end: with the attempt's result
+// where no wave left, else by integrating from the untouched V in a form that is
+// right with any number of workgroups on the chip.
 #pragma once
 
 #include "lb_internal.h"
@@ -50,9 +62,33 @@ __device__ __forceinline__ double wave_sum_dpp(double v) {
     return dpp_add<0xb1>(v);  // quad_perm:[1,0,3,2]
 }
 
-__global__ void k_resident_init(double* W, int64_t n) {
+// What the workgroups of a run share besides the vectors, cleared by k_resident_init.
+struct ResidentCtl {
+    unsigned decision;  // 0: open, else one of the two below
+    unsigned arrived;   // workgroups that have started
+    unsigned long long ticket, done;  // k_resident_end: pieces of work taken, and finished
+};
+constexpr unsigned kGo = 1, kLeave = 2;
+
+template <typename T>
+__device__ __forceinline__ T agent_load(const T* p) {
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+template <typename T>
+__device__ __forceinline__ T agent_add(T* p, T v) {
+    return __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// Settles an open decision; one that is settled stays.
+__device__ __forceinline__ void decide(ResidentCtl* c, unsigned d) {
+    unsigned open = 0;
+    __hip_atomic_compare_exchange_strong(&c->decision, &open, d, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                         __HIP_MEMORY_SCOPE_AGENT);
+}
+
+__global__ void k_resident_init(double* W, int64_t n, ResidentCtl* ctl) {
     const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (e < n) reinterpret_cast<uint64_t*>(W)[e] = kPending;
+    if (e == 0) *ctl = ResidentCtl{};
 }
 
 // Four rows per wave, RL of them in LDS; U column steps of 128 (M <= 128 U). Lane
@@ -60,21 +96,31 @@ __global__ void k_resident_init(double* W, int64_t n) {
 // then the lanes are added by xor-shuffles: the order, and the bits, of k_gemv.
 // The stage vector is polled once per workgroup and passed on through LDS (each
 // wave polling all of it for itself, without barriers, was 1.6 times slower).
-// Every wait ends: a wave whose exchange is not complete after `spins` polls
-// (seconds; the cooperative launch has all of them resident, so none waits for
-// one that cannot run) leaves NaN in its rows of V.
+// start, run: ticks of the constant 100 MHz clock. A wave that leaves has settled the
+// decision to that, or found it so, and a decision that still is to go when the
+// kernel has ended means that every wave came to its end. The other waves of its
+// workgroup (a barrier does not wait for one that has ended) and the other workgroups
+// may go on with a stage vector that lacks its part, up to their next wait for one of
+// its rows: nothing they write is used then.
 constexpr int kResRows = 4;
 
 template <int RL, int U>
 __global__ __launch_bounds__(256, 1) void k_rk4_resident(const double* const* Qs, const double* const* Ks,
                                                          double* const* Vs, int M, int64_t ldq, double* W,
-                                                         int64_t wstride, double h, int64_t steps, int spins) {
+                                                         int64_t wstride, double h, int64_t steps, double* out,
+                                                         ResidentCtl* ctl, int64_t start, int64_t run) {
     constexpr int R = kResRows, RR = R - RL, XB = RL ? 1 : 2;
     static_assert(U % 2 == 0, "whole rounds of 256 threads");
     __shared__ double xs[XB][128 * U];
     __shared__ double ql[RL ? 4 * RL : 1][RL ? 128 * U : 2];
+    const int64_t since = wall_clock64();
+    // arrives before it loads Q, waits after
+    if (threadIdx.x == 0) {
+        if (start == 0) decide(ctl, kLeave);
+        if (agent_add(&ctl->arrived, 1u) + 1 == gridDim.x) decide(ctl, kGo);
+    }
     const double* Q = Qs[0];
-    double* V = Vs[0];
+    const double* V = Vs[0];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int row0 = ((int)blockIdx.x * 4 + wave) * R;
     lb_double2v q[RR][U];
@@ -96,8 +142,11 @@ __global__ __launch_bounds__(256, 1) void k_rk4_resident(const double* const* Qs
     double v = mine ? V[mrow] : 0.0, acc = 0.0;
     for (int c = threadIdx.x; c < 128 * U; c += 256)
         for (int b = 0; b < XB; ++b) xs[b][c] = b == 0 && c < M ? V[c] : 0.0;
+    unsigned d;
+    while ((d = agent_load(&ctl->decision)) == 0)
+        if (lane == 0 && wall_clock64() - since >= start) decide(ctl, kLeave);
+    if (d != kGo) return;
     __syncthreads();
-    // every wave has read V before any row of it is written (the end is an exchange away, or steps are none)
     // elements per thread of an exchange, and at a time (16 at once spill next to four rows of 32 steps)
     constexpr int NE = U / 2, NG = NE <= 8 ? NE : NE % 8 == 0 ? 8 : NE % 7 == 0 ? 7 : NE % 6 == 0 ? 6 : 5;
     static_assert(NE % NG == 0, "whole groups");
@@ -147,10 +196,15 @@ __global__ __launch_bounds__(256, 1) void k_rk4_resident(const double* const* Qs
                 }
 #pragma unroll
                 for (int i = 0; i < NG; ++i) all &= got[i] != kPending;
-                for (int n = 0; !all; ++n) {
-                    if (n > spins) {
-                        if (mine) V[mrow] = __builtin_nan("");
-                        return;
+                int64_t from = 0;
+                for (unsigned n = 1; !all; ++n) {
+                    if (run == 0 || n % 256 == 0) {
+                        const int64_t now = wall_clock64();
+                        if (from == 0) from = now;
+                        if (now - from >= run || agent_load(&ctl->decision) != kGo) {
+                            __hip_atomic_store(&ctl->decision, kLeave, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                            break;
+                        }
                     }
                     all = true;
 #pragma unroll
@@ -159,6 +213,7 @@ __global__ __launch_bounds__(256, 1) void k_rk4_resident(const double* const* Qs
                         all &= got[i] != kPending;
                     }
                 }
+                if (__any(!all)) return;
 #pragma unroll
                 for (int i = 0; i < NG; ++i) xw[threadIdx.x + 256 * (i0 + i)] = __builtin_bit_cast(double, got[i]);
             }
@@ -167,23 +222,104 @@ __global__ __launch_bounds__(256, 1) void k_rk4_resident(const double* const* Qs
             ++j;
         }
     }
-    if (mine) V[mrow] = v;
+    if (mine) out[mrow] = v;
+}
+
+__device__ __forceinline__ unsigned long long first_lane(unsigned long long v) {
+    const unsigned lo = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)v);
+    return (unsigned long long)(unsigned)__builtin_amdgcn_readfirstlane((int)(v >> 32)) << 32 | lo;
+}
+
+// Behind the attempt: its result into V, or, where it was left, the integration from
+// the start. The pieces (stage by stage, 16 rows each, a row per wave) are handed out
+// in order, and a workgroup waits only for pieces handed out before its own, which
+// running workgroups hold: it ends with any number of them on the chip. V, the
+// accumulators and the stage vectors pass between workgroups as above. A row's sum is
+// k_gemv's (wave_rowdots), so the bits are the same on every way. On a free chip, in
+// us a stage, a launch per stage / this: N = 17 4.1 / 4.2, N = 37 5.0 / 9.0, N = 50
+// 11.0 / 16.8, N = 64 22 / 31 (pieces of 32 and 64 rows: 34 and 39 at N = 64): the two
+// counters, 8 to 10 us for the 256 workgroups of N = 64, and x read by each of them.
+template <bool ALIGNED>
+__global__ __launch_bounds__(1024) void k_resident_end(const double* const* Qs, const double* const* Ks,
+                                                       double* const* Vs, int M, int64_t ldq, double* W,
+                                                       int64_t wstride, double h, int64_t steps, const double* out,
+                                                       ResidentCtl* ctl) {
+    __shared__ __align__(16) double xs[4096];
+    __shared__ unsigned long long piece;
+    double* V = Vs[0];
+    if (ctl->decision == kGo) {
+        const int e = (int)(blockIdx.x * blockDim.x + threadIdx.x);
+        if (e < M) V[e] = out[e];
+        return;
+    }
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const unsigned long long tiles = (unsigned)(M + 15) / 16, total = 4 * (unsigned long long)steps * tiles;
+    double *Acc = W, *Xa = W + wstride, *Xb = W + 2 * wstride;
+    unsigned long long next = 0, mine = 0;
+    if (threadIdx.x == 0) next = agent_add(&ctl->ticket, 1ull);
+    // One thread's work per round in one place and every branch around a barrier on wave-uniform
+    // values: with the first thread's additions at the round's end as well, the compiler let its
+    // wave's other lanes run on into the next round's barriers without it.
+    for (;; mine = 1) {
+        if (wave == 0) {
+            if (lane == 0) {
+                agent_add(&ctl->done, mine);
+                piece = next;
+            }
+            const unsigned long long t = first_lane(next);
+            if (t < total)
+                while (agent_load(&ctl->done) < t / tiles * tiles) __builtin_amdgcn_s_sleep(1);
+            if (lane == 0) next = agent_add(&ctl->ticket, 1ull);  // on its way during this piece
+        }
+        __syncthreads();
+        const unsigned long long t = first_lane(piece);
+        if (t >= total) return;
+        const int stage = (int)(t / tiles % 4) + 1;
+        const double* x = stage == 1 ? V : stage == 3 ? Xb : Xa;
+        double* xn = stage == 4 ? V : stage == 2 ? Xb : Xa;
+        for (int e = threadIdx.x; e < M; e += 1024) xs[e] = __builtin_bit_cast(double, xchg_load(x + e));
+        __syncthreads();
+        const int row = (int)(t % tiles) * 16 + wave;
+        if (row < M) {
+            const double* q = Qs[0] + (int64_t)row * ldq;
+            double k;
+            wave_rowdots<1, ALIGNED, false>(&q, xs, M, lane, &k);
+            if (lane == 0) {
+                double v = __builtin_bit_cast(double, xchg_load(V + row));
+                double acc = stage > 1 ? __builtin_bit_cast(double, xchg_load(Acc + row)) : 0.0;
+                const double n = rk4_next(stage, h, k + Ks[0][row], v, acc);
+                xchg_store(xn + row, __builtin_bit_cast(uint64_t, n));
+                if (stage < 4) xchg_store(Acc + row, __builtin_bit_cast(uint64_t, acc));
+            }
+        }
+        __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0): these rows are out before the piece counts as done
+        __syncthreads();
+    }
 }
 
 typedef void (*rk4_resident_fn)(const double* const*, const double* const*, double* const*, int, int64_t, double*,
-                                int64_t, double, int64_t, int);
+                                int64_t, double, int64_t, double*, ResidentCtl*, int64_t, int64_t);
 
 struct Rk4Resident {
     rk4_resident_fn fn = nullptr;
     unsigned grid = 0;
+    bool wide = false;  // takes more than half of the chip
+    int64_t start = 0, run = 0;
+    int device = 0;
 };
+
+// Doubles of one of the run's vectors, and the bytes it needs behind k_gemv's three: its
+// result and the shared words.
+static int64_t rk4_resident_stride(int64_t M) { return (int64_t)lb_align(M, 32); }
+static size_t rk4_resident_bytes(int64_t M) { return sizeof(double) * rk4_resident_stride(M) + sizeof(ResidentCtl); }
+static bool rk4_resident_range(int64_t M) { return M > 256 && M <= 4096; }
 
 // Kernel and grid for one system and one state, or none. Four rows per wave, so
 // that a workgroup's 16 rows are one line of the exchange (with 1, 2 and 3 rows
 // per wave N = 32 took 4.4, 3.0 and 2.9 us a stage; with 4, 2.5).
 static Rk4Resident rk4_resident_pick(int64_t M) {
     Rk4Resident r;
-    if (M <= 256 || M > 4096) return r;
+    if (!rk4_resident_range(M)) return r;
     r.grid = (unsigned)((M + 4 * kResRows - 1) / (4 * kResRows));
     r.fn = M <= 512    ? k_rk4_resident<0, 4>
            : M <= 768  ? k_rk4_resident<0, 6>
@@ -197,15 +333,11 @@ static Rk4Resident rk4_resident_pick(int64_t M) {
     return r;
 }
 
-// Whether a cooperative launch of `grid` workgroups, one per compute unit, fits the current device.
-static bool rk4_resident_fits(int device, unsigned grid) {
-    int coop = 0, cus = 0;
-    if (hipDeviceGetAttribute(&coop, hipDeviceAttributeCooperativeLaunch, device) != hipSuccess ||
-        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess) {
-        (void)hipGetLastError();
-        return false;
-    }
-    return coop && grid <= (unsigned)cus;
+static int rk4_compute_units(int device) {
+    int cus = 0;
+    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device) == hipSuccess) return cus;
+    (void)hipGetLastError();
+    return 0;
 }
 
 }  // namespace

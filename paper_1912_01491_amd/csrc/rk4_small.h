@@ -17,20 +17,22 @@
 namespace {
 
 // The stage combination on registers: k = (Q x + K)_i; returns the next stage's x_i.
+// The fused multiply-adds are written out: what the compiler makes of sums and
+// products depends on whether it knows the stage, and the bits with it.
 __device__ __forceinline__ double rk4_next(int stage, double h, double k, double& v, double& acc) {
     if (stage == 1) {
         acc = k;
-        return v + 0.5 * h * k;
+        return fma(0.5 * h, k, v);
     }
     if (stage == 2) {
-        acc = acc + 2.0 * k;
-        return v + 0.5 * h * k;
+        acc = fma(2.0, k, acc);
+        return fma(0.5 * h, k, v);
     }
     if (stage == 3) {
-        acc = acc + 2.0 * k;
-        return v + h * k;
+        acc = fma(2.0, k, acc);
+        return fma(h, k, v);
     }
-    v = v + h / 6.0 * (acc + k);
+    v = fma(h / 6.0, acc + k, v);
     return v;
 }
 
