@@ -716,13 +716,14 @@ __global__ __launch_bounds__(256) void k_stage(StageArgs a, int stage) {
 
 // ---------------------------------------------------------------------------
 // A whole stage of a small system in one launch (FP64, 2 to 64 states): a workgroup
-// owns 16 rows, its eight waves an eighth of the columns each (lane mapping as in
+// owns RT tiles of 16 rows, its eight waves an eighth of the columns each (lane mapping as in
 // k_gemm64), their sums meet in LDS in the order of the waves and the stage
 // combination follows at once. x is read from one buffer and written to another,
 // since other workgroups may still be reading. What a stage costs at this size is
 // launches and latency, and this is one launch instead of two, without partial sums
 // in memory. The columns' split depends on M alone, so a system's bits do not depend
-// on what shares the launch.
+// on what shares the launch, nor on RT: two tiles read x once for 32 rows where there
+// are workgroups enough (block_rows).
 // ---------------------------------------------------------------------------
 constexpr int kBlockWaves = 8;
 
@@ -738,40 +739,52 @@ struct BlockArgs {
     double h;
 };
 
-template <int CT, bool ALIGNED>
-__global__ __launch_bounds__(64 * kBlockWaves) void k_block64(BlockArgs a, int stage) {
+template <int CT, int RT, bool ALIGNED>
+__global__ __launch_bounds__(64 * kBlockWaves, RT == 1 ? 2 : 4) void k_block64(BlockArgs a, int stage) {
     constexpr int Bp = 16 * CT;
     __shared__ double red[kBlockWaves][CT * 256];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int lr = lane & 15, lk = lane >> 4;
     const int r = blockIdx.y;
-    const int64_t M = a.M, row0 = (int64_t)blockIdx.x * 16;
+    const int64_t M = a.M, row0 = (int64_t)blockIdx.x * (16 * RT);
     const double* X = a.Xin + r * a.in_stride + 2 * lr;
-    const double* q = a.Qs[r] + (row0 + lr < M ? row0 + lr : M - 1) * a.ldq;
+    const double* q[RT];
+#pragma unroll
+    for (int t = 0; t < RT; ++t) {
+        const int64_t row = row0 + 16 * t + lr;
+        q[t] = a.Qs[r] + (row < M ? row : M - 1) * a.ldq;
+    }
     const int64_t kw = (M + 8 * kBlockWaves - 1) / (8 * kBlockWaves) * 8;
     const int64_t k0 = wave * kw, k1 = k0 + kw < M ? k0 + kw : M;
-    lb_double4 acc[CT];
+    lb_double4 acc[RT][CT];
 #pragma unroll
-    for (int c = 0; c < CT; ++c) acc[c] = lb_double4{0, 0, 0, 0};
+    for (int t = 0; t < RT; ++t)
+#pragma unroll
+        for (int c = 0; c < CT; ++c) acc[t][c] = lb_double4{0, 0, 0, 0};
     // U steps of 8 columns, all loads first
     auto steps = [&](auto U, int64_t kc) __attribute__((always_inline)) {
         constexpr int n = decltype(U)::value;
-        double2 qa[n], xa[n][CT];
+        lb_double2v qa[n][RT], xa[n][CT];
 #pragma unroll
         for (int u = 0; u < n; ++u) {
-            const double* p = q + kc + 8 * u + 2 * lk;
-            qa[u] = ALIGNED ? *reinterpret_cast<const double2*>(p) : make_double2(p[0], p[1]);
+#pragma unroll
+            for (int t = 0; t < RT; ++t) {
+                const double* p = q[t] + kc + 8 * u + 2 * lk;
+                qa[u][t] = ALIGNED ? *reinterpret_cast<const lb_double2v*>(p) : lb_double2v{p[0], p[1]};
+            }
 #pragma unroll
             for (int c = 0; c < CT; ++c)
-                xa[u][c] = *reinterpret_cast<const double2*>(X + (((kc + 8 * u) >> 1) + lk) * (2 * Bp) + 32 * c);
+                xa[u][c] = *reinterpret_cast<const lb_double2v*>(X + (((kc + 8 * u) >> 1) + lk) * (2 * Bp) + 32 * c);
         }
 #pragma unroll
         for (int u = 0; u < n; ++u)
 #pragma unroll
-            for (int c = 0; c < CT; ++c) {
-                acc[c] = __builtin_amdgcn_mfma_f64_16x16x4f64(qa[u].x, xa[u][c].x, acc[c], 0, 0, 0);
-                acc[c] = __builtin_amdgcn_mfma_f64_16x16x4f64(qa[u].y, xa[u][c].y, acc[c], 0, 0, 0);
-            }
+            for (int t = 0; t < RT; ++t)
+#pragma unroll
+                for (int c = 0; c < CT; ++c) {
+                    acc[t][c] = __builtin_amdgcn_mfma_f64_16x16x4f64(qa[u][t].x, xa[u][c].x, acc[t][c], 0, 0, 0);
+                    acc[t][c] = __builtin_amdgcn_mfma_f64_16x16x4f64(qa[u][t].y, xa[u][c].y, acc[t][c], 0, 0, 0);
+                }
     };
     int64_t kc = k0;
     for (; kc + 32 <= k1; kc += 32) steps(std::integral_constant<int, 4>(), kc);
@@ -781,35 +794,45 @@ __global__ __launch_bounds__(64 * kBlockWaves) void k_block64(BlockArgs a, int s
         for (int e = 0; e < 2; ++e) {
             const int64_t k = kc + 2 * lk + e;
             const bool ok = k < k1;
-            const double qv = ok ? q[k] : 0.0;
+            double xv[CT];
 #pragma unroll
-            for (int c = 0; c < CT; ++c)
-                acc[c] = __builtin_amdgcn_mfma_f64_16x16x4f64(
-                    qv, ok ? X[(k >> 1) * (2 * Bp) + (k & 1) + 32 * c] : 0.0, acc[c], 0, 0, 0);
+            for (int c = 0; c < CT; ++c) xv[c] = ok ? X[(k >> 1) * (2 * Bp) + (k & 1) + 32 * c] : 0.0;
+#pragma unroll
+            for (int t = 0; t < RT; ++t) {
+                const double qv = ok ? q[t][k] : 0.0;
+#pragma unroll
+                for (int c = 0; c < CT; ++c)
+                    acc[t][c] = __builtin_amdgcn_mfma_f64_16x16x4f64(qv, xv[c], acc[t][c], 0, 0, 0);
+            }
         }
     }
-#pragma unroll
-    for (int c = 0; c < CT; ++c)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) red[wave][256 * c + 64 * j + lane] = acc[c][j];  // (row 4j + l/16, column l%16)
-    __syncthreads();
     const int b = threadIdx.x % Bp, rp = threadIdx.x / Bp;
-    const int64_t row = row0 + 2 * rp;
-    if (rp >= 8 || row >= M) return;
-    const bool two = row + 1 < M;
     const int i = (b >> 4) * 256 + 32 * rp + (b & 15);
-    lb_double2v k = {red[0][i], red[0][i + 16]};
 #pragma unroll
-    for (int w = 1; w < kBlockWaves; ++w) {
-        k.x += red[w][i];
-        k.y += red[w][i + 16];
+    for (int t = 0; t < RT; ++t) {
+        if (t > 0) __syncthreads();  // the last tile's sums are still being read
+#pragma unroll
+        for (int c = 0; c < CT; ++c)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) red[wave][256 * c + 64 * j + lane] = acc[t][c][j];  // (row 4j + l/16, column l%16)
+        __syncthreads();
+        const int64_t row = row0 + 16 * t + 2 * rp;
+        if (rp < 8 && row < M) {
+            const bool two = row + 1 < M;
+            lb_double2v k = {red[0][i], red[0][i + 16]};
+#pragma unroll
+            for (int w = 1; w < kBlockWaves; ++w) {
+                k.x += red[w][i];
+                k.y += red[w][i + 16];
+            }
+            k.x += a.Ks[r][row];
+            if (two) k.y += a.Ks[r][row + 1];
+            const int64_t idx = ilv2(row, b, Bp);
+            *reinterpret_cast<lb_double2v*>(a.Xout + r * a.out_stride + idx) =
+                stage_pair(stage, a.h, k, two, reinterpret_cast<lb_double2v*>(a.V + r * a.sstride + idx),
+                           reinterpret_cast<lb_double2v*>(a.Acc + r * a.sstride + idx));
+        }
     }
-    k.x += a.Ks[r][row];
-    if (two) k.y += a.Ks[r][row + 1];
-    const int64_t idx = ilv2(row, b, Bp);
-    *reinterpret_cast<lb_double2v*>(a.Xout + r * a.out_stride + idx) =
-        stage_pair(stage, a.h, k, two, reinterpret_cast<lb_double2v*>(a.V + r * a.sstride + idx),
-                   reinterpret_cast<lb_double2v*>(a.Acc + r * a.sstride + idx));
 }
 
 // user layout (B, M) -> interleaved padded (Mp, Bp); padding rows/columns zero
@@ -1102,6 +1125,17 @@ static int64_t long_slabs(int64_t M, int Bp) {
     return std::max<int64_t>(1, std::min((target + rowwaves - 1) / rowwaves, maxslab));
 }
 
+// FP64 blocks up to this size run a stage as one launch (k_block64) unless a tile was
+// set for them. A workgroup per 16 rows fills the chip in whole rounds: up to 128 row
+// tiles two systems fit one round and up to 169 three of them fit two; beyond, two or
+// three systems lose more than one gains (64 states, which keep a CU busier, from 128
+// on). In us a stage, GEMM and combination / one launch:
+//   16 states:  N = 17  9.8 / 6.2    N = 30  12.3 / 9.1    N = 45  18.0 / 14.6
+//   64 states:  N = 17  12.1 / 8.1   N = 30  17.5 / 14.8   N = 45  29.4 / 26.4
+//   N = 51, 32 states, 1, 2, 3 systems:  25.5 / 23.6  40.0 / 37.4  59.1 / 40.1
+//   N = 49, 64 states, 2 systems 53 / 56; N = 58, 32 states, 3 systems 78 / 90
+static int64_t whole_limit(int Bp) { return Bp == 64 ? 2048 : 2704; }
+
 // Default tile from sweeps on MI355X (LDS-staged kernels). A stage of one system
 // is fastest with one wave per SIMD (1024, just under rather than just over) and
 // as few slabs as that takes: more waves mean more partial sums, more rows in
@@ -1112,12 +1146,17 @@ static int64_t long_slabs(int64_t M, int Bp) {
 //   N = 60   32 rows   36 / 27        N = 128  64 rows  409 / 333
 // (k_block64 takes the smallest of these sizes where no tile is asked for; a server's
 // mixed batches and stage timings still run them as tiles).
-// Hence tiles of 16 rows below M = 2500, of 32 below 8200, of 64 beyond (32 for
-// 64 states in FP64, which fits two waves of that size on a SIMD), and as many
+// Hence tiles of 16 rows below M = 3000 (FP32: 2500), of 32 below 8200, of 64 beyond
+// (32 for 64 states in FP64, which fits two waves of that size on a SIMD), and as many
 // slabs as keep row tiles x slabs within 1024, or within 2048 where that fills
 // the last round better. From M = 32768 on the waves of one system fill the chip
 // several times over and the stage runs at the read stream's rate: about 2500
 // waves there (N = 200, two systems: 3857 us a stage; with 1875 waves 3932).
+// Several systems of M = 2000 to 3000 have waves enough with tiles of 32 rows, one to a
+// workgroup (16 states, N = 53, R = 4: 62 us with the long slabs' 64 rows, 60 with 16,
+// 54 with 32); 64 states then need the long rule's slabs, up to six of them (N = 51,
+// R = 1, 2, 3: 43, 51, 75 us with the long rule's tile, 35, 58, 83 with five slabs of 16
+// rows, 31, 48, 74 now), and 32 states have no better tile there than the long rule's.
 // FP32 keeps the long rule's slabs at every size: a slab is summed in FP32, so its
 // length is the sum's accuracy (N = 99, 50 states: with 6 slabs instead of 17 the
 // stage is 1.3 times as fast and the error 1.7 times as large).
@@ -1128,7 +1167,6 @@ static int64_t long_slabs(int64_t M, int Bp) {
 lb_tile lb_default_tile(int64_t M, int Bp, int precision, int R) {
     lb_tile t;
     const int CT = Bp / 16;
-    (void)R;
     t.rows = M < (precision == LB_FP32 ? 2500 : 3000) ? 16 : M < 8200 ? 32 : 64;
     t.waves = 4;
     int64_t nslab;
@@ -1143,6 +1181,10 @@ lb_tile lb_default_tile(int64_t M, int Bp, int precision, int R) {
         const int64_t tiles = (M + t.rows - 1) / t.rows, groups = (tiles + 3) / 4;
         if (t.rows == 16) {
             nslab = std::min<int64_t>(5, (M + 63) / 64);
+            if (M > whole_limit(Bp)) {
+                if (CT == 4) nslab = std::min(long_slabs(M, Bp), std::max<int64_t>(5, 1024 / tiles));
+                if (CT == 2) nslab = long_slabs(M, Bp);
+            }
         } else {
             const int64_t n1 = std::max<int64_t>(1, 1024 / tiles), n2 = std::max<int64_t>(1, 2048 / tiles);
             // two rounds, with twice the partial sums, where they are filled 15 % better than one
@@ -1155,6 +1197,10 @@ lb_tile lb_default_tile(int64_t M, int Bp, int precision, int R) {
         const int64_t lim = (((int64_t)LB_NOALLOC_SCRATCH_BYTES - 4096) / (4 * (M + 16) * Bp) - 7) / 2;
         nslab = std::min(nslab, std::max(lim, long_slabs(M, Bp)));
         if (CT == 4 && t.rows == 64) t.rows = 32;
+        if (t.rows == 16 && M > 2000 && (R > 1 || (CT == 2 && M > whole_limit(Bp)))) {
+            t.rows = 32;
+            t.waves = 1;
+        }
     }
     int64_t ks = (M + nslab - 1) / nslab;
     ks = (ks + 31) / 32 * 32;
@@ -1228,17 +1274,6 @@ constexpr int64_t kResidentSteps = 2;
 constexpr int64_t kResidentStepTicks = 4000;
 
 constexpr int kMaxDevices = 64;
-
-// FP64 blocks up to this size run a stage as one launch (k_block64) unless a tile was
-// set for them. A workgroup per 16 rows fills the chip in whole rounds: up to
-// 128 row tiles two systems fit one round and up to 169 three of them fit two; beyond,
-// two or three systems lose more than one gains (64 states, which keep a CU busier,
-// from 128 on). In us a stage, GEMM and combination / one launch:
-//   16 states:  N = 17  9.8 / 6.2    N = 30  12.3 / 9.1    N = 45  18.0 / 14.6
-//   64 states:  N = 17  12.1 / 8.1   N = 30  17.5 / 14.8   N = 45  29.4 / 26.4
-//   N = 51, 32 states, 1, 2, 3 systems:  25.5 / 23.6  40.0 / 37.4  59.1 / 40.1
-//   N = 49, 64 states, 2 systems 53 / 56; N = 58, 32 states, 3 systems 78 / 90
-static int64_t whole_limit(int Bp) { return Bp == 64 ? 2048 : 2704; }
 
 enum PathKind { PATH_SMALL, PATH_GEMV, PATH_MFMA };
 
@@ -1459,6 +1494,29 @@ static int plan_unpack(const Plan& p, hipStream_t s) {
     return LB_OK;
 }
 
+// Rows of a workgroup of k_block64. Of many systems two tiles are faster. With 64
+// states x is four times Q's traffic and the eight waves of one tile keep a CU to
+// themselves: from three rounds of such workgroups on. With fewer, where the systems' Q
+// no longer fit the last-level cache (256 MB). In us a stage, tile GEMM of 64 (32)
+// rows / one tile / two:
+//   64 states:  N = 30, R = 12  73 / 46 / 47   R = 16  80 / 60 / 50   R = 64  193 / 261 / 205
+//               N = 37, R = 8   78 / 57 / 60   R = 16  111 / 128 / 98  R = 128  739 / 972 / 718
+//   16 states:  N = 37, R = 16  64 / 58 / 59   R = 64  238 / 259 / 235
+//               N = 52, R = 4   60 / 46 / 55   R = 6   88 / 90 / 82    R = 8  117 / 131 / 119
+//   32 states:  N = 40, R = 12  84 / 66 / 74   R = 64  391 / 407 / 375
+// (seven to ten systems of N = 40 to 48 remain, which fill the last round badly either
+// way: N = 48, R = 8, 16 states 82 / 92 / 92.)
+static int block_rows(const Plan& p) {
+    if (p.Bp == 64) return (int64_t)p.R * (p.Mp / 16) > 768 ? 32 : 16;
+    return (size_t)p.R * p.M * p.ldq * sizeof(double) > ((size_t)256 << 20) ? 32 : 16;
+}
+typedef void (*block_fn)(BlockArgs, int);
+template <bool AL>
+static block_fn pick_block(int CT, int rows) {
+    if (rows == 32) return CT == 1 ? k_block64<1, 2, AL> : CT == 2 ? k_block64<2, 2, AL> : k_block64<4, 2, AL>;
+    return CT == 1 ? k_block64<1, 1, AL> : CT == 2 ? k_block64<2, 1, AL> : k_block64<4, 1, AL>;
+}
+
 // The resident run and what follows it. Two that need more than half of the chip
 // each could both be on it in part and wait in vain until one gives way, so those of
 // a device are enqueued one behind the other, whatever their streams.
@@ -1517,10 +1575,9 @@ static int plan_launch(const Plan& p, hipStream_t s, double dt, int64_t steps, c
     }
     if (p.whole) {
         // x alternates between its buffer and that of the partial sums, which are not needed
-        typedef void (*block_fn)(BlockArgs, int);
         const int CT = p.Bp / 16;
-        const block_fn fn = p.aligned ? (CT == 1 ? k_block64<1, true> : CT == 2 ? k_block64<2, true> : k_block64<4, true>)
-                                      : (CT == 1 ? k_block64<1, false> : CT == 2 ? k_block64<2, false> : k_block64<4, false>);
+        const int rows = block_rows(p);
+        const block_fn fn = p.aligned ? pick_block<true>(CT, rows) : pick_block<false>(CT, rows);
         BlockArgs a;
         a.Qs = (const double* const*)p.d;
         a.Ks = (const double* const*)(p.d + 2 * p.R);
@@ -1537,7 +1594,7 @@ static int plan_launch(const Plan& p, hipStream_t s, double dt, int64_t steps, c
                 a.Xout = odd ? p.Part : p.X;
                 a.in_stride = odd ? p.sstride : p.pstride;
                 a.out_stride = odd ? p.pstride : p.sstride;
-                hipLaunchKernelGGL(fn, dim3((unsigned)(p.Mp / 16), p.R), dim3(64 * kBlockWaves), 0, s, a, stage);
+                hipLaunchKernelGGL(fn, dim3(lb_blocks(p.M, rows), p.R), dim3(64 * kBlockWaves), 0, s, a, stage);
                 LB_CHECK_LAUNCH();
             }
         return plan_unpack(p, s);

@@ -231,9 +231,9 @@ static int run_batch(lb_server* s, int slot, std::vector<Ticket*>& batch) {
             if (!rc && r.precision == LB_FP32) rc = lb_impl_q_to_f32(c, M, (double*)Q, ldq, (float*)Q32);
             sys[g] = lb_prop_sys{(const double*)Q, (const float*)Q32, (const double*)K, X[g]};
         }
-        // the 16-state matrix-core path with its default tile whatever the
-        // batch holds, so that every state column is summed in the same order
-        const lb_tile tile = lb_default_tile(M, 16, r0.precision, 1);
+        // the 16-state matrix-core path whatever the batch holds: the default tile's slabs do
+        // not depend on the number of systems, so every state column is summed in the same order
+        const lb_tile tile = lb_default_tile(M, 16, r0.precision, G);
         if (!rc) rc = lb_impl_propagate(c, G, M, sys.data(), ldq, Brun, r0.dt, r0.steps, r0.precision,
                                         solo ? nullptr : &tile);
     } else {
