@@ -6,6 +6,7 @@
 #pragma once
 
 #include "lb_internal.h"
+#include "scan_pack.h"
 
 namespace {
 
@@ -98,13 +99,13 @@ __device__ __forceinline__ void scan_eight(int64_t start, int64_t n, const int64
         s += v[j];
         z += v[j] != 0;
     }
-    // both in one pass: a block has at most 2^13 nonzero counts, and its sum stays below 2^50
-    constexpr int64_t low = ((int64_t)1 << 50) - 1;
-    s = block_scan<W>(s | z << 50, &os);
-    oz = bz + (os >> 50);
-    os = bs + (os & low);
-    bs += s & low;
-    bz += s >> 50;
+    // both in one pass
+    static_assert(8 * 64 * W <= kScanPackCounts, "counts of a workgroup");
+    s = block_scan<W>(scan_pack(s, z), &os);
+    oz = bz + scan_packed_nonzero(os);
+    os = bs + scan_packed_sum(os);
+    bs += scan_packed_sum(s);
+    bz += scan_packed_nonzero(s);
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
         if (list && v[j] != 0) list[oz++] = i0 + j;
