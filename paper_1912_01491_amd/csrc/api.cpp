@@ -661,6 +661,7 @@ int lindblad_set_tile(lb_ctx* c, int64_t M, int B, int precision, int rows, int 
     if (rows < 16 || rows % 16 || rows > 128 || kslab < 16 || kslab % 16 || waves < 1 || waves > 4)
         return lb_fail(LB_ERR_INVALID_ARG, "tile rows=%d kslab=%d waves=%d out of range", rows, kslab, waves);
     const int Bp = B <= 16 ? 16 : (B <= 32 ? 32 : 64);
+    lb_load_tune_cache(c);
     c->tuned[std::make_tuple(M, Bp, precision)] = lb_tile{rows, kslab, waves};
     c->measured.erase(std::make_tuple(M, Bp, precision));
     return LB_OK;
@@ -678,6 +679,7 @@ int lindblad_set_resident_wait(lb_ctx* c, double start_ms, double stage_ms) {
 int lindblad_tile_info(lb_ctx* c, int64_t M, int B, int precision, int* rows, int* kslab, int* waves, int* tuned) {
     if (!c) return lb_fail(LB_ERR_INVALID_ARG, "null context");
     const int Bp = B <= 16 ? 16 : (B <= 32 ? 32 : 64);
+    lb_load_tune_cache(c);
     auto it = c->tuned.find(std::make_tuple(M, Bp, precision));
     lb_tile t = it != c->tuned.end() ? it->second : lb_default_tile(M, Bp, precision, 1);
     if (rows) *rows = t.rows;

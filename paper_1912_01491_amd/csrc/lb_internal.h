@@ -266,3 +266,4 @@ int lb_impl_secular_apply(lb_ctx* c, const lb_secular* pre, const double* r, dou
 void lb_impl_secular_destroy(lb_secular* pre);
 int64_t lb_secular_size(const lb_secular* pre);  // M of the system it was built for
 lb_tile lb_default_tile(int64_t M, int Bp, int precision, int R);
+void lb_load_tune_cache(lb_ctx* c);

@@ -1208,8 +1208,10 @@ lb_tile lb_default_tile(int64_t M, int Bp, int precision, int R) {
     return t;
 }
 
-// Tile-cache file (LB_TUNE_CACHE): one line "M Bp precision rows kslab waves".
-static void load_tune_cache(lb_ctx* c) {
+// Tile-cache file (LB_TUNE_CACHE): one line "M Bp precision rows kslab waves". Read once
+// per context, before the first tile is set, tuned, asked for or used, so that it never
+// takes the place of one that was set.
+void lb_load_tune_cache(lb_ctx* c) {
     if (c->cache_loaded) return;
     c->cache_loaded = true;
     const char* path = getenv("LB_TUNE_CACHE");
@@ -1237,7 +1239,7 @@ static lb_tile limit_tile(int64_t M, int Bp) {
 }
 
 static lb_tile choose_tile(lb_ctx* c, int64_t M, int Bp, int precision, int R) {
-    load_tune_cache(c);
+    lb_load_tune_cache(c);
     auto it = c->tuned.find(std::make_tuple(M, Bp, precision));
     if (it != c->tuned.end()) return it->second;
     return lb_default_tile(M, Bp, precision, R);
@@ -1882,6 +1884,7 @@ int lb_impl_autotune(lb_ctx* c, int64_t M, const lb_prop_sys* sys, int64_t ldq, 
                     best = t;
                 }
             }
+    lb_load_tune_cache(c);
     c->tuned[std::make_tuple(M, Bp, precision)] = best;
     c->measured.insert(std::make_tuple(M, Bp, precision));
     if (const char* path = getenv("LB_TUNE_CACHE")) {
