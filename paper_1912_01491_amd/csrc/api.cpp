@@ -247,6 +247,11 @@ int lindblad_prepare(lb_ctx* c, int N, const double* H, const double* gamma, dou
     if (ldq < M) return lb_fail(LB_ERR_INVALID_ARG, "ldq=%lld < M=%lld", (long long)ldq, (long long)M);
     if (((uintptr_t)gamma) % 16 || ((uintptr_t)H) % 16)
         return lb_fail(LB_ERR_INVALID_ARG, "H and gamma must be 16-byte aligned complex arrays");
+    // a recorded preparation would keep a workspace that later calls replace; refused before
+    // anything below synchronizes or frees, so the capture stays valid
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(c->stream, &cap) != hipSuccess) (void)hipGetLastError();
+    if (cap != hipStreamCaptureStatusNone) return lb_fail(LB_ERR_DEVICE, "lindblad_prepare cannot be captured");
     if (flags & LB_CHECK_HERMITIAN) {
         double dev = 0, mx = 0;
         int rc = lb_impl_hermitian_check(c, N, H, &dev, &mx);

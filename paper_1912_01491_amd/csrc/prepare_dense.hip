@@ -1109,14 +1109,10 @@ int lb_impl_prepare_dense(lb_ctx* c, int N, const double* H, const double* gamma
     const size_t o_t = take(sizeof(double) * (size_t)NN);
     const size_t o_gp = take(sizeof(double) * 2 * 4 * (size_t)nch * NN);  // GpA, TpA, GpC, TpC
     const size_t o_order = take(sizeof(int2) * (size_t)norder + 8);
+    hipStream_t s = c->stream;
     int rc = lb_ws_reserve(c, off);
     if (rc) return rc;
     char* ws = (char*)c->ws;
-    hipStream_t s = c->stream;
-    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(s, &cap) != hipSuccess) (void)hipGetLastError();
-    if (cap != hipStreamCaptureStatusNone)  // a recorded preparation would keep a workspace that later calls replace
-        return lb_fail(LB_ERR_DEVICE, "lindblad_prepare cannot be captured");
     if (!fused) {
         rc = lb_aux_stream(c);
         if (rc) return rc;
