@@ -1297,7 +1297,8 @@ struct Plan {
     float* X32;
 };
 
-// own_tile: the tile was asked for, and is used.
+// allow_small: a whole run in one launch where M is small; own_tile: the tile was asked
+// for, and is used.
 static int plan_make(Plan& p, int R, int64_t M, int64_t ldq, int B, int precision, const lb_tile& tile,
                      bool allow_small, bool own_tile) {
     p = Plan();
@@ -1336,7 +1337,7 @@ static int plan_make(Plan& p, int R, int64_t M, int64_t ldq, int B, int precisio
         p.o_x = take(sizeof(double) * p.sstride * R);
         if (precision == LB_FP32) p.o_x32 = take(sizeof(float) * p.s32stride * R);
         p.o_part = take(sizeof(double) * p.pstride * R);
-        p.whole = allow_small && !own_tile && precision == LB_FP64 && M <= whole_limit(p.Bp);
+        p.whole = !own_tile && precision == LB_FP64 && M <= whole_limit(p.Bp);
         const int RT = tile.rows / 16, CT = p.Bp / 16;
         if (tile.rows % 16 || tile.kslab % 16 || tile.kslab <= 0 || tile.waves < 1 || tile.waves > 4 ||
             (precision == LB_FP64 ? (p.aligned ? pick64<true>(RT, CT) : pick64<false>(RT, CT)) == nullptr
@@ -1519,16 +1520,42 @@ static block_fn pick_block(int CT, int rows) {
     return CT == 1 ? k_block64<1, 1, AL> : CT == 2 ? k_block64<2, 1, AL> : k_block64<4, 1, AL>;
 }
 
-// The resident run and what follows it. Two that need more than half of the chip
-// each could both be on it in part and wait in vain until one gives way, so those of
-// a device are enqueued one behind the other, whatever their streams.
+// One stage in one launch; x alternates between its buffer and that of the partial
+// sums, which are not needed.
+static int plan_block(const Plan& p, hipStream_t s, int stage, double dt) {
+    const int CT = p.Bp / 16, rows = block_rows(p);
+    const block_fn fn = p.aligned ? pick_block<true>(CT, rows) : pick_block<false>(CT, rows);
+    const bool odd = stage & 1;
+    BlockArgs a;
+    a.Qs = (const double* const*)p.d;
+    a.Ks = (const double* const*)(p.d + 2 * p.R);
+    a.M = p.M;
+    a.ldq = p.ldq;
+    a.V = p.V;
+    a.Acc = p.Acc;
+    a.sstride = p.sstride;
+    a.Xin = odd ? p.X : p.Part;
+    a.Xout = odd ? p.Part : p.X;
+    a.in_stride = odd ? p.sstride : p.pstride;
+    a.out_stride = odd ? p.pstride : p.sstride;
+    a.h = dt;
+    hipLaunchKernelGGL(fn, dim3(lb_blocks(p.M, rows), p.R), dim3(64 * kBlockWaves), 0, s, a, stage);
+    LB_CHECK_LAUNCH();
+    return LB_OK;
+}
+
+// The resident run and what follows it (finish: without it V stays as it is). Two that
+// need more than half of the chip each could both be on it in part and wait in vain
+// until one gives way, so those of a device are enqueued one behind the other, whatever
+// their streams.
 struct WideOrder {
     std::mutex mu;
     hipEvent_t last = nullptr;
 };
 WideOrder g_wide[kMaxDevices];
 
-static int resident_launch(const Plan& p, hipStream_t s, double dt, int64_t steps, const Rk4Resident& res) {
+static int resident_launch(const Plan& p, hipStream_t s, double dt, int64_t steps, const Rk4Resident& res,
+                           bool finish) {
     const int64_t stride = rk4_resident_stride(p.M), n = 3 * stride;
     double* out = p.W + n;
     ResidentCtl* ctl = (ResidentCtl*)(out + stride);
@@ -1547,6 +1574,7 @@ static int resident_launch(const Plan& p, hipStream_t s, double dt, int64_t step
                        ctl, res.start, res.run);
     LB_CHECK_LAUNCH();
     if (res.wide) LB_HIP(hipEventRecord(wide.last, s));
+    if (!finish) return LB_OK;
     hipLaunchKernelGGL(p.aligned ? k_resident_end<true> : k_resident_end<false>, dim3(res.grid), dim3(1024), 0, s, q, k,
                        v, (int)p.M, p.ldq, p.W, stride, dt, steps, (const double*)out, ctl);
     LB_CHECK_LAUNCH();
@@ -1557,7 +1585,7 @@ static int resident_launch(const Plan& p, hipStream_t s, double dt, int64_t step
 // so it can be recorded into a graph.
 static int plan_launch(const Plan& p, hipStream_t s, double dt, int64_t steps, const Rk4Resident& res) {
     if (steps == 0) return LB_OK;
-    if (res.fn) return resident_launch(p, s, dt, steps, res);
+    if (res.fn) return resident_launch(p, s, dt, steps, res, true);
     if (p.kind == PATH_SMALL) {
         hipLaunchKernelGGL(p.small.fn, dim3(p.R, p.B), dim3(p.small.threads), 0, s, (const double* const*)p.d,
                            (const double* const*)(p.d + 2 * p.R), (double* const*)(p.d + 3 * p.R), (int)p.M, p.ldq,
@@ -1576,28 +1604,10 @@ static int plan_launch(const Plan& p, hipStream_t s, double dt, int64_t steps, c
         return LB_OK;
     }
     if (p.whole) {
-        // x alternates between its buffer and that of the partial sums, which are not needed
-        const int CT = p.Bp / 16;
-        const int rows = block_rows(p);
-        const block_fn fn = p.aligned ? pick_block<true>(CT, rows) : pick_block<false>(CT, rows);
-        BlockArgs a;
-        a.Qs = (const double* const*)p.d;
-        a.Ks = (const double* const*)(p.d + 2 * p.R);
-        a.M = p.M;
-        a.ldq = p.ldq;
-        a.V = p.V;
-        a.Acc = p.Acc;
-        a.sstride = p.sstride;
-        a.h = dt;
         for (int64_t st = 0; st < steps; ++st)
             for (int stage = 1; stage <= 4; ++stage) {
-                const bool odd = stage & 1;
-                a.Xin = odd ? p.X : p.Part;
-                a.Xout = odd ? p.Part : p.X;
-                a.in_stride = odd ? p.sstride : p.pstride;
-                a.out_stride = odd ? p.pstride : p.sstride;
-                hipLaunchKernelGGL(fn, dim3(lb_blocks(p.M, rows), p.R), dim3(64 * kBlockWaves), 0, s, a, stage);
-                LB_CHECK_LAUNCH();
+                rc = plan_block(p, s, stage, dt);
+                if (rc) return rc;
             }
         return plan_unpack(p, s);
     }
@@ -1613,31 +1623,36 @@ static int plan_launch(const Plan& p, hipStream_t s, double dt, int64_t steps, c
     return plan_unpack(p, s);
 }
 
-// Average duration (ms) of the dominant stage kernel over `iters` launches,
-// measured with HIP events on the context stream. The states are packed
+// Average duration (ms) of a stage over `iters` launches of the kernel that is most or
+// all of it, measured with HIP events on the context stream; with Q on the chip, of the
+// stages by which a run of iters steps more is longer. The states are packed
 // first; the kernel reads them but the timing loop does not advance them.
-static int plan_time(lb_ctx* c, const Plan& p, int iters, double* ms) {
+static int plan_time(lb_ctx* c, const Plan& p, int iters, const Rk4Resident& res, double* ms) {
     hipStream_t s = c->stream;
     int rc = plan_init_state(p, s);
     if (rc) return rc;
-    rc = plan_gemm(p, s, 1, 0.0);  // warm-up launch
+    auto launch = [&](int i) {
+        return p.kind == PATH_GEMV ? plan_gemm(p, s, 1 + (i & 1), 0.0)
+               : p.whole           ? plan_block(p, s, 1, 0.0)
+                                   : plan_gemm(p, s, 1, 0.0);
+    };
+    rc = res.fn ? resident_launch(p, s, 0.0, 2, res, false) : launch(0);  // warm-up
     if (rc) return rc;
-    hipEvent_t e0, e1;
-    LB_HIP(hipEventCreate(&e0));
-    LB_HIP(hipEventCreate(&e1));
-    LB_HIP(hipEventRecord(e0, s));
-    for (int i = 0; i < iters; ++i) {
-        rc = plan_gemm(p, s, p.kind == PATH_GEMV ? 1 + (i & 1) : 1, 0.0);
-        if (rc) break;
-    }
-    LB_HIP(hipEventRecord(e1, s));
-    LB_HIP(hipEventSynchronize(e1));
-    float t = 0;
-    LB_HIP(hipEventElapsedTime(&t, e0, e1));
-    (void)hipEventDestroy(e0);
-    (void)hipEventDestroy(e1);
+    hipEvent_t e[3];
+    for (hipEvent_t& ev : e) LB_HIP(hipEventCreate(&ev));
+    LB_HIP(hipEventRecord(e[0], s));
+    if (res.fn) rc = resident_launch(p, s, 0.0, 2, res, false);
+    LB_HIP(hipEventRecord(e[1], s));
+    if (res.fn && !rc) rc = resident_launch(p, s, 0.0, 2 + (int64_t)iters, res, false);
+    for (int i = 0; !res.fn && i < iters && !rc; ++i) rc = launch(i);
+    LB_HIP(hipEventRecord(e[2], s));
+    LB_HIP(hipEventSynchronize(e[2]));
+    float t0 = 0, t1 = 0;
+    LB_HIP(hipEventElapsedTime(&t0, e[0], e[1]));
+    LB_HIP(hipEventElapsedTime(&t1, e[1], e[2]));
+    for (hipEvent_t ev : e) (void)hipEventDestroy(ev);
     if (rc) return rc;
-    *ms = (double)t / iters;
+    *ms = res.fn ? ((double)t1 - t0) / (4.0 * iters) : (double)t1 / iters;
     return LB_OK;
 }
 
@@ -1645,7 +1660,7 @@ static int plan_for(lb_ctx* c, Plan& p, int R, int64_t M, const lb_prop_sys* sys
                     const lb_tile* force_tile, bool allow_small) {
     const lb_tile tile = force_tile ? *force_tile : choose_tile(c, M, bpad(B), precision, R);
     int rc = plan_make(p, R, M, ldq, B, precision, tile, allow_small && force_tile == nullptr,
-                       asked_tile(c, M, bpad(B), precision));
+                       force_tile != nullptr || asked_tile(c, M, bpad(B), precision));
     if (rc) return rc;
     rc = lb_ws_reserve(c, p.bytes);
     if (rc) return rc;
@@ -1688,7 +1703,7 @@ int lb_impl_time_stage(lb_ctx* c, int R, int64_t M, const lb_prop_sys* sys, int6
     Plan p;
     int rc = plan_for(c, p, R, M, sys, ldq, B, precision, force_tile, false);
     if (rc) return rc;
-    return plan_time(c, p, iters, ms);
+    return plan_time(c, p, iters, plan_resident(c, p, 2 + (int64_t)iters), ms);
 }
 
 // ---------------------------------------------------------------------------
