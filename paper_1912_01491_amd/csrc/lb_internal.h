@@ -12,6 +12,7 @@
 #include <vector>
 
 #include "../../include/lindblad.h"
+#include "tile_rule.h"
 
 // ---------------------------------------------------------------------------
 // Errors
@@ -39,12 +40,6 @@ int lb_fail(int code, const char* fmt, ...);
 // ---------------------------------------------------------------------------
 // Context
 // ---------------------------------------------------------------------------
-
-struct lb_tile {
-    int rows;   // rows per wave (multiple of 16)
-    int kslab;  // columns per split-K slab (multiple of 16)
-    int waves;  // waves per workgroup
-};
 
 struct lb_graph_key {
     int64_t M, ldq;
@@ -265,5 +260,4 @@ int lb_impl_secular_create(lb_ctx* c, int N, const lb_csr_c128* H, int P, const 
 int lb_impl_secular_apply(lb_ctx* c, const lb_secular* pre, const double* r, double* z);
 void lb_impl_secular_destroy(lb_secular* pre);
 int64_t lb_secular_size(const lb_secular* pre);  // M of the system it was built for
-lb_tile lb_default_tile(int64_t M, int Bp, int precision, int R);
 void lb_load_tune_cache(lb_ctx* c);
