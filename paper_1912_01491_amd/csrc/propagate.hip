@@ -1166,6 +1166,9 @@ namespace {
 // steps, a launch per stage / resident, in us: N = 17 75 / 49, N = 37 71 / 61, N = 64
 // 207 / 113.
 constexpr int64_t kResidentSteps = 2;
+// Steps of a piece of a long run: 30 to 100 ms, of which the load of Q and the launches
+// are less than a thousandth.
+constexpr int64_t kResidentPiece = 4096;
 // The wait for the chip is no longer than about what a launch per stage takes more in the
 // run's steps: 40 us each.
 constexpr int64_t kResidentStepTicks = 4000;
@@ -1449,14 +1452,14 @@ struct WideOrder {
 };
 WideOrder g_wide[kMaxDevices];
 
-static int resident_launch(const Plan& p, hipStream_t s, double dt, int64_t steps, const Rk4Resident& res,
-                           bool finish) {
+static int resident_piece(const Plan& p, hipStream_t s, double dt, int64_t steps, const Rk4Resident& res, bool finish) {
     const int64_t stride = rk4_resident_stride(p.M), n = 3 * stride;
     double* out = p.W + n;
     ResidentCtl* ctl = (ResidentCtl*)(out + stride);
     const double* const* q = (const double* const*)p.d;
     const double* const* k = (const double* const*)(p.d + 2 * p.R);
     double* const* v = (double* const*)(p.d + 3 * p.R);
+    const int64_t start = std::min(res.start, steps * kResidentStepTicks);
     WideOrder& wide = g_wide[res.device];
     std::unique_lock<std::mutex> lk(wide.mu, std::defer_lock);
     if (res.wide) {
@@ -1466,7 +1469,7 @@ static int resident_launch(const Plan& p, hipStream_t s, double dt, int64_t step
     hipLaunchKernelGGL(k_resident_init, dim3(lb_blocks(n, 256)), dim3(256), 0, s, p.W, n, ctl);
     LB_CHECK_LAUNCH();
     hipLaunchKernelGGL(res.fn, dim3(res.grid), dim3(256), 0, s, q, k, v, (int)p.M, p.ldq, p.W, stride, dt, steps, out,
-                       ctl, res.start, res.run);
+                       ctl, start, res.run);
     LB_CHECK_LAUNCH();
     if (res.wide) LB_HIP(hipEventRecord(wide.last, s));
     if (!finish) return LB_OK;
@@ -1476,11 +1479,23 @@ static int resident_launch(const Plan& p, hipStream_t s, double dt, int64_t step
     return LB_OK;
 }
 
+// A long run in pieces, so that a chip that is not free when it starts costs it one of
+// them and not the whole run, and another that has to wait for the chip gets a turn.
+static int resident_launch(const Plan& p, hipStream_t s, double dt, int64_t steps, const Rk4Resident& res) {
+    while (steps > 0) {
+        const int64_t pieces = (steps + kResidentPiece - 1) / kResidentPiece, n = (steps + pieces - 1) / pieces;
+        const int rc = resident_piece(p, s, dt, n, res, true);
+        if (rc) return rc;
+        steps -= n;
+    }
+    return LB_OK;
+}
+
 // Enqueues the whole integration (kernels only: no synchronization, no copies),
 // so it can be recorded into a graph.
 static int plan_launch(const Plan& p, hipStream_t s, double dt, int64_t steps, const Rk4Resident& res) {
     if (steps == 0) return LB_OK;
-    if (res.fn) return resident_launch(p, s, dt, steps, res, true);
+    if (res.fn) return resident_launch(p, s, dt, steps, res);
     if (p.kind == PATH_SMALL) {
         hipLaunchKernelGGL(p.small.fn, dim3(p.R, p.B), dim3(p.small.threads), 0, s, (const double* const*)p.d,
                            (const double* const*)(p.d + 2 * p.R), (double* const*)(p.d + 3 * p.R), (int)p.M, p.ldq,
@@ -1531,14 +1546,14 @@ static int plan_time(lb_ctx* c, const Plan& p, int iters, const Rk4Resident& res
                : p.whole           ? plan_block(p, s, 1, 0.0)
                                    : plan_gemm(p, s, 1, 0.0);
     };
-    rc = res.fn ? resident_launch(p, s, 0.0, 2, res, false) : launch(0);  // warm-up
+    rc = res.fn ? resident_piece(p, s, 0.0, 2, res, false) : launch(0);  // warm-up
     if (rc) return rc;
     hipEvent_t e[3];
     for (hipEvent_t& ev : e) LB_HIP(hipEventCreate(&ev));
     LB_HIP(hipEventRecord(e[0], s));
-    if (res.fn) rc = resident_launch(p, s, 0.0, 2, res, false);
+    if (res.fn) rc = resident_piece(p, s, 0.0, 2, res, false);
     LB_HIP(hipEventRecord(e[1], s));
-    if (res.fn && !rc) rc = resident_launch(p, s, 0.0, 2 + (int64_t)iters, res, false);
+    if (res.fn && !rc) rc = resident_piece(p, s, 0.0, 2 + (int64_t)iters, res, false);
     for (int i = 0; !res.fn && i < iters && !rc; ++i) rc = launch(i);
     LB_HIP(hipEventRecord(e[2], s));
     LB_HIP(hipEventSynchronize(e[2]));
@@ -1571,7 +1586,7 @@ static Rk4Resident plan_resident(lb_ctx* c, const Plan& p, int64_t steps) {
     r = rk4_resident_pick(p.M);
     if (!r.fn) return r;
     r.device = c->device;
-    r.start = std::min(c->resident_start, steps < (1 << 20) ? steps * kResidentStepTicks : c->resident_start);
+    r.start = c->resident_start;
     r.run = c->resident_run;
     const unsigned cus = (unsigned)rk4_compute_units(c->device);
     r.wide = 2 * r.grid > cus;

@@ -84,6 +84,21 @@ def test_chip_held_by_another_stream(lb):
     assert all(torch.equal(g, want) for g in got)
 
 
+@pytest.mark.parametrize("steps", [4096, 4097, 8195])
+def test_long_runs_in_pieces(lb, steps):
+    """One piece, two and three: on the chip, left at once, and a launch per stage."""
+    Q, K, V = _system(300, 300, 8)
+    out = []
+    print("[gpu] resident %d steps" % steps, flush=True)
+    with lb.Context(0) as ctx:
+        for start in (2.0, 0.0, -1.0):
+            lb.lindblad_set_resident_wait(ctx, start)
+            out.append(lb.lindblad_propagate(ctx, Q, K, V.clone(), 1e-3, steps))
+            ctx.sync()
+    assert torch.isfinite(out[0]).all()
+    assert torch.equal(out[0], out[1]) and torch.equal(out[0], out[2])
+
+
 @pytest.mark.parametrize("M,threads", [(288, 8), (1368, 6), (2600, 4)])
 def test_many_threads(lb, M, threads):
     """Side by side where they fit on the chip, one after the other or leaving where not."""
