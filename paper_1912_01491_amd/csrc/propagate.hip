@@ -934,50 +934,52 @@ __global__ void k_gemv_init(double* const* Vs, int64_t M, double* Wall, int64_t 
 // ---------------------------------------------------------------------------
 
 // RK4 stage combination for one element, given k = (Q x + K)_i and the values
-// of v and of the accumulator loaded beforehand.
+// of v and of the accumulator loaded beforehand; h: the stage's factor. Product
+// and sum rounded separately, whatever the code around makes of it.
 __device__ __forceinline__ void rk4_update(int stage, double h, double k, double v, double acc, int64_t i, double* V,
                                            double* Acc, double* Xout) {
-    double x;
-    if (stage == 1) {
-        Acc[i] = k;
-        x = v + 0.5 * h * k;
-    } else if (stage == 2) {
-        Acc[i] = acc + 2.0 * k;
-        x = v + 0.5 * h * k;
-    } else if (stage == 3) {
-        Acc[i] = acc + 2.0 * k;
-        x = v + h * k;
-    } else {
-        V[i] = v + h / 6.0 * (acc + k);
+#pragma clang fp contract(off)
+    if (stage == 4) {
+        V[i] = v + h * (acc + k);
         return;
     }
-    Xout[i] = x;
+    Acc[i] = stage == 1 ? k : acc + 2.0 * k;
+    Xout[i] = v + h * k;
 }
 
-// The stage vectors of a sparse integration.
+// The stage vectors of a sparse integration, M*B each: stage 1 reads x from V, stage 4 writes only V.
 struct SellStage {
-    int B;
+    int B, stage;
+    double h;  // dt/2, dt/2, dt, dt/6
     const double* K;
     double* V;
-    double* W;  // [accumulator | x ping | x pong], M*B each; stage 1 reads x from V, stage 4 writes only V
+    double* acc;
+    const double* xin;
+    double* xout;
 };
 
 // DRIVE: k = (Q0 x) + eps (Q1 x) + K, the two sums formed separately.
-// SB: states per pass over a slice (1, or 4 for batches).
+// SB: states per pass over a slice (1 for a single state, 4 for batches).
+// A few us long at small sizes, so what precedes the loads of x counts: the stage's pointers and
+// factor come from the host, K is read in the loop over states (read before it, the loop's first
+// loads wait for it), and a single state has no loop. N = 100, us a stage: 4.6 -> 4.2 static,
+// 5.5 -> 5.2 rocked; N = 1000: 19.5 -> 19.2 and 38.4 -> 38.4.
 template <bool DRIVE, int SB>
-__global__ __launch_bounds__(256) void k_sell_stage(SellMat a, SellStage st, int stage, double h, double eps) {
+__global__ __launch_bounds__(256) void k_sell_stage(SellMat a, SellStage st, double eps) {
     const int64_t M = a.M;
-    const int64_t n = M * st.B;
-    double* Acc = st.W;
-    const double* Xin = stage == 1 ? st.V : (stage & 1) ? st.W + n : st.W + 2 * n;
-    double* Xout = (stage & 1) ? st.W + 2 * n : st.W + n;
+    const int B = SB == 1 ? 1 : st.B;
+    const int stage = st.stage;
+    const double h = st.h;
+    double* Acc = st.acc;
+    const double* Xin = st.xin;
+    double* Xout = st.xout;
     const int wk = sell_work(a);
     if (wk < 0) return;
     if (wk < a.nlong) {
         const LongRowPtr lr = (LongRowPtr)(a.longrows + wk);
         const int64_t row = lr->row;
         const double kr = st.K[row];
-        for (int b = 0; b < st.B; ++b) {
+        for (int b = 0; b < B; ++b) {
             const int64_t i = (int64_t)b * M + row;
             const double v = st.V[i], acc = stage > 1 ? Acc[i] : 0.0;
             double q0, q1;
@@ -997,10 +999,17 @@ __global__ __launch_bounds__(256) void k_sell_stage(SellMat a, SellStage st, int
     const int lane = threadIdx.x & (kSlice - 1);
     const int64_t r = (int64_t)sl * kSlice + lane;
     const SellHeadPtr head = (SellHeadPtr)(a.head0 + sl);
-    const bool mine = r < M && !((head->lmask >> lane) & 1);
-    const double kr = mine ? st.K[r] : 0.0;
-    for (int b0 = 0; b0 < st.B; b0 += SB) {
-        const int nb = min(SB, st.B - b0);
+    const SellFirst first = sell_first(head);
+    SellHeadPtr head1 = nullptr;
+    SellFirst first1;
+    if (DRIVE) {
+        head1 = (SellHeadPtr)(a.head1 + sl);
+        first1 = sell_first(head1);
+    }
+    const bool mine = r < M && !((first.lmask >> lane) & 1);
+    for (int b0 = 0; b0 < B; b0 += SB) {
+        const int nb = min(SB, B - b0);
+        const double kr = mine ? st.K[r] : 0.0;
         double vv[SB], aa[SB], acc[SB], accd[SB];
 #pragma unroll
         for (int j = 0; j < SB; ++j) {
@@ -1012,8 +1021,8 @@ __global__ __launch_bounds__(256) void k_sell_stage(SellMat a, SellStage st, int
             }
         }
         const double* xb = Xin + (int64_t)b0 * M;
-        sell_row<SB>(head, a.scol0, a.sval0, lane, xb, M, nb, acc);
-        if (DRIVE) sell_row<SB>((SellHeadPtr)(a.head1 + sl), a.scol1, a.sval1, lane, xb, M, nb, accd);
+        sell_row<SB>(first, head, a.scol0, a.sval0, lane, xb, M, nb, acc);
+        if (DRIVE) sell_row<SB>(first1, head1, a.scol1, a.sval1, lane, xb, M, nb, accd);
 #pragma unroll
         for (int j = 0; j < SB; ++j)
             if (j < nb && mine) {
@@ -1854,9 +1863,12 @@ static int csr_propagate(lb_ctx* c, int64_t M, const int64_t* rowptr, const int6
     int rc = sell_build(c, M, rowptr, col, val, rowptr1, col1, val1, sizeof(double) * 3 * (size_t)n, &m, &o_w);
     if (rc) return rc;
     double* W = (double*)((char*)c->ws + o_w);
-    const SellStage st{B, K, V, W};
+    // W: accumulator, x of the odd stages, x of the even ones
+    const double* xin[4] = {V, W + 2 * n, W + n, W + 2 * n};
+    double* xout[4] = {W + 2 * n, W + n, W + 2 * n, nullptr};
+    const double h[4] = {0.5 * dt, 0.5 * dt, dt, dt / 6.0};
     const unsigned grid = (unsigned)m.nlong8 + 8u * (unsigned)m.per_xcd;
-    typedef void (*stage_fn)(SellMat, SellStage, int, double, double);
+    typedef void (*stage_fn)(SellMat, SellStage, double);
     const stage_fn fn = drive ? (B == 1 ? k_sell_stage<true, 1> : k_sell_stage<true, 4>)
                               : (B == 1 ? k_sell_stage<false, 1> : k_sell_stage<false, 4>);
     for (int64_t k = 0; k < steps; ++k)
@@ -1867,7 +1879,8 @@ static int csr_propagate(lb_ctx* c, int64_t M, const int64_t* rowptr, const int6
                 const double cst = stage == 1 ? 0.0 : (stage == 4 ? 1.0 : 0.5);
                 eps = drive_value(stage_time(t0, k0 + k, cst, dt), E, A, T, stage == 4);
             }
-            hipLaunchKernelGGL(fn, dim3(grid), dim3(256), 0, s, m, st, stage, dt, eps);
+            const SellStage st{B, stage, h[stage - 1], K, V, W, xin[stage - 1], xout[stage - 1]};
+            hipLaunchKernelGGL(fn, dim3(grid), dim3(256), 0, s, m, st, eps);
             LB_CHECK_LAUNCH();
         }
     return LB_OK;

@@ -274,31 +274,55 @@ __device__ __forceinline__ void sell_rest(int r, const int* base, const double* 
     }
 }
 
+// The header up to the first chunk's columns.
+struct SellFirst {
+    int64_t off;
+    uint64_t lmask;
+    int w;
+    int base[kChunk];
+};
+
+// All of it in one go: left to where each field is used, the compiler reads the mask, the
+// offset and the columns one behind the other, and the static dimers of N = 40 to 160, whose
+// slices have few runs of consecutive columns to make up for it, took 4.4 us a stage (3.9 so,
+// with the rest of k_sell_stage's start; 4.2 with per-lane columns only). Where w > kLongRow
+// the columns are not set and not used.
+__device__ __forceinline__ SellFirst sell_first(SellHeadPtr head) {
+    SellFirst f;
+    f.off = head->off;
+    f.lmask = head->lmask;
+    f.w = (int)head->w;
+#pragma unroll
+    for (int u = 0; u < kChunk; ++u) f.base[u] = head->base[u];
+    asm volatile("" ::"s"(f.off), "s"(f.lmask), "s"(f.w), "s"(f.base[0]), "s"(f.base[kChunk - 1]));
+    return f;
+}
+
 template <int SB>
-__device__ __forceinline__ void sell_row(SellHeadPtr head, const int* scol, const double* sval, int lane,
-                                         const double* Xin, int64_t M, int nb, double* acc) {
-    const int64_t o = head->off;
-    const int w = (int)head->w;
-    const int* c = scol + o + lane;
-    const double* v = sval + o + lane;
+__device__ __forceinline__ void sell_row(const SellFirst& f, SellHeadPtr head, const int* scol, const double* sval,
+                                         int lane, const double* Xin, int64_t M, int nb, double* acc) {
+    const int w = f.w;
+    const int* c = scol + f.off + lane;
+    const double* v = sval + f.off + lane;
     if (w > kLongRow) {
         const int none = -1;
         for (int k = 0; k < w; ++k, c += kSlice, v += kSlice) sell_chunk<SB, 1>(&none, v, c, lane, Xin, M, nb, acc);
         return;
     }
+    int base[kChunk];
+#pragma unroll
+    for (int u = 0; u < kChunk; ++u) base[u] = f.base[u];
     int k = 0;
-    for (; k + kChunk <= w; k += kChunk, c += kChunk * kSlice, v += kChunk * kSlice) {
-        int base[kChunk];
-#pragma unroll
-        for (int u = 0; u < kChunk; ++u) base[u] = head->base[k + u];
+    while (k + kChunk <= w) {
         sell_chunk<SB, kChunk>(base, v, c, lane, Xin, M, nb, acc);
-    }
-    if (k < w) {
-        int base[kChunk];
+        k += kChunk;
+        c += kChunk * kSlice;
+        v += kChunk * kSlice;
+        if (k >= w) return;
 #pragma unroll
         for (int u = 0; u < kChunk; ++u) base[u] = head->base[k + u];
-        sell_rest<SB, kChunk - 1>(w - k, base, v, c, lane, Xin, M, nb, acc);
     }
+    sell_rest<SB, kChunk - 1>(w - k, base, v, c, lane, Xin, M, nb, acc);
 }
 
 // Sums of one long row of the matrix (s0) and of the second matrix (s1, when

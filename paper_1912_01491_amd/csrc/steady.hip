@@ -74,9 +74,10 @@ __global__ __launch_bounds__(256) void k_mv_sell(SellMat a, const double* x, dou
     const int lane = threadIdx.x & (kSlice - 1);
     const int64_t r = (int64_t)sl * kSlice + lane;
     const SellHeadPtr head = (SellHeadPtr)(a.head0 + sl);
-    const bool mine = r < a.M && !((head->lmask >> lane) & 1);
+    const SellFirst first = sell_first(head);
+    const bool mine = r < a.M && !((first.lmask >> lane) & 1);
     double acc[1] = {0.0};
-    sell_row<1>(head, a.scol0, a.sval0, lane, x, a.M, 1, acc);
+    sell_row<1>(first, head, a.scol0, a.sval0, lane, x, a.M, 1, acc);
     if (mine) y[r] = acc[0];
 }
 
