@@ -214,9 +214,9 @@ int lindblad_prepare_sparse(lb_ctx* ctx, int N, const lb_csr_c128* H, int P, con
  * processes' kernels keep some of them off for longer than 2 ms (40 us a step, if
  * that is less), they leave and up to 4096 steps are carried out without, in 1.2 to
  * 2.2 times the time of a launch per stage: same result, bit for bit, and V is not
- * written before (lindblad_set_resident_wait). Calls of M > 2048 take the whole GPU and run one
- * after the other; smaller ones run side by side. A stream that is being captured
- * records a launch per stage, with the same bits.
+ * written before (lindblad_set_resident_wait). Calls of M > 2048 take the whole GPU
+ * and run one after the other; smaller ones run side by side. A stream that is being
+ * captured records a launch per stage, with the same bits.
  * When Q (or Q32) starts on a 128-byte boundary and its rows are 128-byte
  * multiples (ldq a multiple of 16 in FP64, 32 in FP32), the stage GEMM stages
  * Q through LDS with full-line streaming loads; otherwise it loads the matrix

@@ -943,7 +943,7 @@ __global__ __launch_bounds__(256) void k_tail(GV v, const double* Lam, double* K
 // the block index). The line lies where the LDS of the largest piece, the diagonal
 // block's table, still lets three workgroups share a CU, as k_quad's does. Time of
 // a whole preparation, 13 launches / launch by launch on two streams / fused: N = 8
-// 90 / 66 / 23 us, N = 33 199 / 91 / 48, N = 64 471 / 247 / 194, N = 80 689 / 479 /
+// 107 / 66 / 18 us, N = 33 199 / 91 / 48, N = 64 471 / 247 / 194, N = 80 689 / 479 /
 // 403; from N = 100 the work order's L2 reuse is worth more (974 and 982 us).
 constexpr int kFuseN = 80;
 
