@@ -519,9 +519,9 @@ int lindblad_autotune(lb_ctx* ctx, int64_t M, const double* Q, const float* Q32,
  * HIP events on the context stream: the stage GEMM (of two kernels the longer by
  * far), the whole stage where that is one launch (lindblad_autotune), the stage
  * GEMV for one FP64 state, or, with Q held on the chip, a stage's share of iters
- * steps. (Systems of up to 256 rows, all of whose run is one launch, are timed as
- * if it were not.) Arguments as for lindblad_propagate_batched; the states are
- * read but not advanced. Synchronizes. */
+ * steps (the GEMV again where the chip is not free in time). (Systems of up to 256
+ * rows, all of whose run is one launch, are timed as if it were not.) Arguments as
+ * for lindblad_propagate_batched; the states are read but not advanced. Synchronizes. */
 int lindblad_time_stage(lb_ctx* ctx, int R, int64_t M, const double* const* Q, const float* const* Q32,
                         int64_t ldq, const double* const* K, double* const* V, int B, int precision,
                         int iters, double* avg_ms);

@@ -1542,36 +1542,66 @@ static int plan_launch(const Plan& p, hipStream_t s, double dt, int64_t steps, c
     return plan_unpack(p, s);
 }
 
+// Stage time of a run with Q on the chip: a run of 2 + iters steps less one of 2. went: both
+// were carried out (a chip that is not free ends them early) and the longer one took longer.
+static int time_resident(const Plan& p, hipStream_t s, int iters, const Rk4Resident& res, double* ms, bool* went) {
+    int rc = resident_piece(p, s, 0.0, 2, res, false);  // warm-up
+    if (rc) return rc;
+    const ResidentCtl* ctl = (const ResidentCtl*)(p.W + 4 * rk4_resident_stride(p.M));
+    float t[2] = {0, 0};
+    *went = true;
+    hipEvent_t e[2];
+    for (hipEvent_t& ev : e) LB_HIP(hipEventCreate(&ev));
+    for (int i = 0; i < 2 && *went && !rc; ++i) {
+        unsigned decision = 0;
+        LB_HIP(hipEventRecord(e[0], s));
+        rc = resident_piece(p, s, 0.0, i == 0 ? 2 : 2 + (int64_t)iters, res, false);
+        LB_HIP(hipEventRecord(e[1], s));
+        LB_HIP(hipMemcpyAsync(&decision, &ctl->decision, sizeof(decision), hipMemcpyDeviceToHost, s));
+        LB_HIP(hipStreamSynchronize(s));
+        LB_HIP(hipEventElapsedTime(&t[i], e[0], e[1]));
+        *went = decision == kGo;
+    }
+    for (hipEvent_t ev : e) (void)hipEventDestroy(ev);
+    *went = *went && t[1] > t[0];
+    *ms = ((double)t[1] - t[0]) / (4.0 * iters);
+    return rc;
+}
+
 // Average duration (ms) of a stage over `iters` launches of the kernel that is most or
 // all of it, measured with HIP events on the context stream; with Q on the chip, of the
 // stages by which a run of iters steps more is longer. The states are packed
 // first; the kernel reads them but the timing loop does not advance them.
 static int plan_time(lb_ctx* c, const Plan& p, int iters, const Rk4Resident& res, double* ms) {
     hipStream_t s = c->stream;
-    int rc = plan_init_state(p, s);
+    int rc = LB_OK;
+    if (res.fn) {
+        bool went = false;
+        rc = time_resident(p, s, iters, res, ms, &went);
+        if (rc || went) return rc;
+    }
+    rc = plan_init_state(p, s);
     if (rc) return rc;
     auto launch = [&](int i) {
         return p.kind == PATH_GEMV ? plan_gemm(p, s, 1 + (i & 1), 0.0)
                : p.whole           ? plan_block(p, s, 1, 0.0)
                                    : plan_gemm(p, s, 1, 0.0);
     };
-    rc = res.fn ? resident_piece(p, s, 0.0, 2, res, false) : launch(0);  // warm-up
+    rc = launch(0);  // warm-up
     if (rc) return rc;
-    hipEvent_t e[3];
-    for (hipEvent_t& ev : e) LB_HIP(hipEventCreate(&ev));
-    LB_HIP(hipEventRecord(e[0], s));
-    if (res.fn) rc = resident_piece(p, s, 0.0, 2, res, false);
-    LB_HIP(hipEventRecord(e[1], s));
-    if (res.fn && !rc) rc = resident_piece(p, s, 0.0, 2 + (int64_t)iters, res, false);
-    for (int i = 0; !res.fn && i < iters && !rc; ++i) rc = launch(i);
-    LB_HIP(hipEventRecord(e[2], s));
-    LB_HIP(hipEventSynchronize(e[2]));
-    float t0 = 0, t1 = 0;
-    LB_HIP(hipEventElapsedTime(&t0, e[0], e[1]));
-    LB_HIP(hipEventElapsedTime(&t1, e[1], e[2]));
-    for (hipEvent_t ev : e) (void)hipEventDestroy(ev);
+    hipEvent_t e0, e1;
+    LB_HIP(hipEventCreate(&e0));
+    LB_HIP(hipEventCreate(&e1));
+    LB_HIP(hipEventRecord(e0, s));
+    for (int i = 0; i < iters && !rc; ++i) rc = launch(i);
+    LB_HIP(hipEventRecord(e1, s));
+    LB_HIP(hipEventSynchronize(e1));
+    float t = 0;
+    LB_HIP(hipEventElapsedTime(&t, e0, e1));
+    (void)hipEventDestroy(e0);
+    (void)hipEventDestroy(e1);
     if (rc) return rc;
-    *ms = res.fn ? ((double)t1 - t0) / (4.0 * iters) : (double)t1 / iters;
+    *ms = (double)t / iters;
     return LB_OK;
 }
 

@@ -150,3 +150,18 @@ def test_bad_waits_are_refused(lb):
         for start, stage in ((float("nan"), 1.0), (1.0, float("nan")), (1.0, -1.0), (1e10, 1.0), (1.0, 1e10)):
             with pytest.raises(lb.LindbladError):
                 lb.lindblad_set_resident_wait(ctx, start, stage)
+
+
+@pytest.mark.parametrize("M,start,stage", [(899, 0.0, 2000.0), (899, 1000.0, 0.0), (4095, 0.0, 0.0)])
+def test_stage_time_of_runs_that_leave(lb, M, start, stage):
+    """Where the timed runs leave, a launch per stage is timed: no less than a read of Q from the
+    last-level cache at 20 TB/s, more than it delivers, takes, and no more than 1 ms (V as it was)."""
+    print("[gpu] stage time of runs that leave M=%d" % M, flush=True)
+    Q, K, V = _system(M, lb.default_ldq(M), M)
+    with lb.Context(0) as ctx:
+        lb.lindblad_set_resident_wait(ctx, start, stage)
+        v = V.clone()
+        for _ in range(3):
+            ms = lb.lindblad_time_stage(ctx, [Q], [K], [v], iters=20)
+            assert 8e3 * M * M / 20e12 < ms < 1.0
+        assert torch.equal(v, V)
