@@ -727,10 +727,18 @@ __global__ __launch_bounds__(256) void k_stage(StageArgs a, int stage) {
 // ---------------------------------------------------------------------------
 constexpr int kBlockWaves = 8;
 
+// Columns of a wave, the length of a slab that gives the same sums (plan_make): whole
+// lines of 16 where such slabs are used (M = 2208, 2600 and 2703 take up to 3 % longer for
+// it alone and 6 % for two or three systems, the other N^2 - 1 have that length anyway).
+static int64_t block_columns(int64_t M) {
+    return M > 2048 ? (M + 16 * kBlockWaves - 1) / (16 * kBlockWaves) * 16
+                    : (M + 8 * kBlockWaves - 1) / (8 * kBlockWaves) * 8;
+}
+
 struct BlockArgs {
     const double* const* Qs;
     const double* const* Ks;
-    int64_t M, ldq;
+    int64_t M, ldq, kw;  // kw: block_columns(M)
     double *V, *Acc;
     int64_t sstride;
     const double* Xin;
@@ -754,8 +762,7 @@ __global__ __launch_bounds__(64 * kBlockWaves, RT == 1 ? 2 : 4) void k_block64(B
         const int64_t row = row0 + 16 * t + lr;
         q[t] = a.Qs[r] + (row < M ? row : M - 1) * a.ldq;
     }
-    const int64_t kw = (M + 8 * kBlockWaves - 1) / (8 * kBlockWaves) * 8;
-    const int64_t k0 = wave * kw, k1 = k0 + kw < M ? k0 + kw : M;
+    const int64_t k0 = wave * a.kw, k1 = k0 + a.kw < M ? k0 + a.kw : M;
     lb_double4 acc[RT][CT];
 #pragma unroll
     for (int t = 0; t < RT; ++t)
@@ -1204,6 +1211,20 @@ struct Plan {
     float* X32;
 };
 
+// Many systems of M > 2048 whose Q exceed the last-level cache are read from memory each
+// stage, faster by the LDS-staged GEMM with a slab for each of k_block64's waves (same
+// sums, same bits), unless the workgroups of 32 rows fit the chip two to a CU (256
+// CUs). In us a stage, k_block64 / GEMM and combination:
+//   16 states:  N = 46, R = 8  75 / 65   R = 16  144 / 130   N = 48, R = 7 (504 workgroups)  60 / 64
+//               N = 50, R = 7  95 / 79   R = 10  134 / 117   R = 20  236 / 226
+//   32 states:  N = 48, R = 8  103 / 97  R = 12  142 / 136   N = 50, R = 10  152 / 138
+// Smaller systems have fewer columns in a slab: N = 42, 16 states, R = 14 92 / 88, R = 32
+// 181 / 189; N = 37, R = 64 216 / 224.
+static bool many_blocks(const Plan& p) {
+    return p.Bp <= 32 && p.M > 2048 && p.R * ((p.M + 31) / 32) > 512 &&
+           (size_t)p.R * p.M * p.ldq * sizeof(double) > ((size_t)256 << 20);
+}
+
 // allow_small: a whole run in one launch where M is small; own_tile: the tile was asked
 // for, and is used.
 static int plan_make(Plan& p, int R, int64_t M, int64_t ldq, int B, int precision, const lb_tile& tile,
@@ -1232,9 +1253,11 @@ static int plan_make(Plan& p, int R, int64_t M, int64_t ldq, int B, int precisio
     } else {
         p.kind = PATH_MFMA;
         p.Bp = bpad(B);
-        p.tile = tile;
+        p.whole = !own_tile && precision == LB_FP64 && M <= whole_limit(p.Bp);
+        p.tile = p.whole && many_blocks(p) ? lb_tile{64, (int)block_columns(M), 1} : tile;
+        p.whole = p.whole && !many_blocks(p);
         p.Mp = (M + 15) / 16 * 16;
-        p.nslab = (int)((M + tile.kslab - 1) / tile.kslab);
+        p.nslab = (int)((M + p.tile.kslab - 1) / p.tile.kslab);
         p.sstride = lb_align(p.Mp * p.Bp, 64);
         p.s32stride = lb_align(p.Mp * p.Bp, 128);
         p.pstride = (int64_t)p.nslab * p.Mp * p.Bp;
@@ -1244,7 +1267,6 @@ static int plan_make(Plan& p, int R, int64_t M, int64_t ldq, int B, int precisio
         p.o_x = take(sizeof(double) * p.sstride * R);
         if (precision == LB_FP32) p.o_x32 = take(sizeof(float) * p.s32stride * R);
         p.o_part = take(sizeof(double) * p.pstride * R);
-        p.whole = !own_tile && precision == LB_FP64 && M <= whole_limit(p.Bp);
         const int RT = tile.rows / 16, CT = p.Bp / 16;
         if (tile.rows % 16 || tile.kslab % 16 || tile.kslab <= 0 || tile.waves < 1 || tile.waves > 4 ||
             (precision == LB_FP64 ? (p.aligned ? pick64<true>(RT, CT) : pick64<false>(RT, CT)) == nullptr
@@ -1414,8 +1436,9 @@ static int plan_unpack(const Plan& p, hipStream_t s) {
 //   16 states:  N = 37, R = 16  64 / 58 / 59   R = 64  238 / 259 / 235
 //               N = 52, R = 4   60 / 46 / 55   R = 6   88 / 90 / 82    R = 8  117 / 131 / 119
 //   32 states:  N = 40, R = 12  84 / 66 / 74   R = 64  391 / 407 / 375
-// (seven to ten systems of N = 40 to 48 remain, which fill the last round badly either
-// way: N = 48, R = 8, 16 states 82 / 92 / 92.)
+// Behind the GEMM remain up to M = 2048 (larger ones: many_blocks) some numbers of systems
+// of 256 to 400 MB, which fill the last round badly either way: 16 states, N = 40, R = 16
+// 78 / 86 / 86; N = 42, R = 14 84 against 92, 64 states, N = 33, R = 40 144 against 157.
 static int block_rows(const Plan& p) {
     if (p.Bp == 64) return (int64_t)p.R * (p.Mp / 16) > 768 ? 32 : 16;
     return (size_t)p.R * p.M * p.ldq * sizeof(double) > ((size_t)256 << 20) ? 32 : 16;
@@ -1438,6 +1461,7 @@ static int plan_block(const Plan& p, hipStream_t s, int stage, double dt) {
     a.Ks = (const double* const*)(p.d + 2 * p.R);
     a.M = p.M;
     a.ldq = p.ldq;
+    a.kw = block_columns(p.M);
     a.V = p.V;
     a.Acc = p.Acc;
     a.sstride = p.sstride;

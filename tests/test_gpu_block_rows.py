@@ -51,3 +51,12 @@ def test_batch_has_the_bits_of_one(lb, M, B, R, pad):
             ctx.sync()
             assert torch.isfinite(one).all() and not torch.equal(one, Vs[r])
             assert torch.equal(out[r], one), r
+
+
+# 2 to 32 states, M > 2048, more than 512 workgroups of 32 rows and 256 MB of Q: the tile GEMM, a slab
+# for each wave of the one launch. Whole and partial last slabs, rows and columns; the fewest systems.
+@pytest.mark.parametrize("M,B,R,pad", [(2049, 16, 8, 15), (2115, 16, 8, 13), (2176, 2, 8, 0), (2208, 9, 8, 1),
+                                       (2303, 32, 8, 1), (2305, 17, 8, 3), (2600, 16, 7, 2), (2704, 32, 7, 16)])
+def test_many_large_systems_have_the_bits_of_one(lb, M, B, R, pad):
+    assert R * ((M + 31) // 32) > 512 and R * M * (M + pad) * 8 > 256 << 20
+    test_batch_has_the_bits_of_one(lb, M, B, R, pad)
